@@ -17,6 +17,7 @@
 // 16 columns, column 4 t + q is stored at position 4 q + t, so that one 16-byte read gives quarter q its operands of four
 // instructions; the 16-byte chunks of a row are XOR-ed with swz(row), which keeps both the 16-byte reads (16 rows, one chunk)
 // and the 4-byte reads of the transposed use (4 rows, 4 chunks) free of bank conflicts.
+#include "attn_rows.h"
 #include "dev.h"
 #include "kernels.h"
 #include "prof.h"
@@ -34,6 +35,13 @@ struct FaF {
   float *o, *dq, *dk, *dv, *lse;
   long ldq, ldk, ldv, ldo, lddo, lddq, lddk, lddv;
 };
+
+// the same call for the row functions
+__device__ __forceinline__ AttnP by_rows() {
+  const late_args_t<FaF> p = late_args<FaF>();
+  return AttnP{p->B, p->A, p->Sq, p->Sk, p->d, p->mask, p->scale, p->kv_len, p->q, p->k, p->v, p->dout, p->o, p->dq, p->dk, p->dv,
+               p->lse, const_cast<float *>(p->delta), p->ldq, p->ldk, p->ldv, p->ldo, p->lddo, p->lddq, p->lddk, p->lddv};
+}
 
 constexpr int kT = 64;  // tile rows
 // floats between rows of a tile with D columns (D a multiple of 32 that holds the head): whole multiples of the 64 banks
@@ -223,9 +231,12 @@ __global__ __launch_bounds__(256, 2) void fa_f32_fwd_k(FaF p) {
     m = mn;
     cols_by_weights<D>(sV, s, lane, acc);
   }
-  if (qi >= p.Sq) return;
-  store_row<D>((T *)p.o + ((long)b * p.Sq + qi) * p.ldo + h * p.d, acc, l > 0.f ? 1.f / l : 0.f, p.d, lq);
-  if (lq == 0) p.lse[((long)b * p.A + h) * p.Sq + qi] = l > 0.f ? m + logf(l) : -INFINITY;
+  const unsigned again = bad_rows<16>(qi < p.Sq && not_finite(acc) != 0.f);
+  if (qi < p.Sq && !(again >> lr & 1)) {
+    store_row<D>((T *)p.o + ((long)b * p.Sq + qi) * p.ldo + h * p.d, acc, l > 0.f ? 1.f / l : 0.f, p.d, lq);
+    if (lq == 0) p.lse[((long)b * p.A + h) * p.Sq + qi] = l > 0.f ? m + logf(l) : -INFINITY;
+  }
+  redo<16>(again, [&](int r, int l64, int wv) { row_fwd<T>(by_rows(), b, h, q0 + r, l64, sK + wv * 128); });
 }
 
 // backward, query side: dQ[i] = scale sum_j dS_ij k_j, 64 queries per workgroup
@@ -275,7 +286,9 @@ __device__ __forceinline__ void f32_dq(const FaF &p, int bx, int h, int b, float
       }
     cols_by_weights<D>(sK, s, lane, acc);
   }
-  if (qi < p.Sq) store_row<D>(p.dq + ((long)b * p.Sq + qi) * p.lddq + h * p.d, acc, p.scale, p.d, lq);
+  const unsigned again = bad_rows<16>(qi < p.Sq && not_finite(acc) != 0.f);
+  if (qi < p.Sq && !(again >> lr & 1)) store_row<D>(p.dq + ((long)b * p.Sq + qi) * p.lddq + h * p.d, acc, p.scale, p.d, lq);
+  redo<16>(again, [&](int r, int l64, int wv) { row_dq<float>(by_rows(), b, h, q0 + r, l64, sK + wv * 256); });
 }
 
 // backward, key side: dK[j] = scale sum_i dS_ij q_i, dV[j] = sum_i P_ij dO_i, 64 keys per workgroup
@@ -330,9 +343,12 @@ __device__ __forceinline__ void f32_dkv(const FaF &p, int bx, int h, int b, floa
     cols_by_weights<D>(sdO, s, lane, dv);
     cols_by_weights<D>(sQ, dp, lane, dk);
   }
-  if (kj >= p.Sk) return;
-  store_row<D>(p.dk + ((long)b * p.Sk + kj) * p.lddk + h * p.d, dk, p.scale, p.d, lq);
-  store_row<D>(p.dv + ((long)b * p.Sk + kj) * p.lddv + h * p.d, dv, 1.f, p.d, lq);
+  const unsigned again = bad_rows<16>(kj < p.Sk && not_finite(dv, not_finite(dk)) != 0.f);
+  if (kj < p.Sk && !(again >> lr & 1)) {
+    store_row<D>(p.dk + ((long)b * p.Sk + kj) * p.lddk + h * p.d, dk, p.scale, p.d, lq);
+    store_row<D>(p.dv + ((long)b * p.Sk + kj) * p.lddv + h * p.d, dv, 1.f, p.d, lq);
+  }
+  redo<16>(again, [&](int r, int l64, int wv) { row_dkv<float>(by_rows(), b, h, k0 + r, l64, sQ + wv * 256); });
 }
 
 // The two sides of the backward do not depend on each other and share a launch: the key side's workgroups first, which

@@ -12,6 +12,7 @@
 // Sec. 2.1 names (attention block, MLP block, norms, residuals).
 #include <algorithm>
 
+#include "attn_rows.h"
 #include "dev.h"
 #include "kernels.h"
 #include "prof.h"
@@ -369,66 +370,11 @@ hipError_t colsum(const void *a, long lda, void *out, float *partial, size_t roo
 // ------------------------------------------------------------------------------------------
 // attention, one wavefront per row
 // ------------------------------------------------------------------------------------------
-struct AttnP {
-  int B, A, Sq, Sk, d, mask;
-  float scale;
-  const int32_t *kv_len;
-  const void *q, *k, *v, *dout;
-  void *o, *dq, *dk, *dv;
-  float *lse, *delta;
-  long ldq, ldk, ldv, ldo, lddo, lddq, lddk, lddv;
-};
-
-__device__ __forceinline__ int key_limit(const AttnP &p, int b, int i) {
-  int lim = p.Sk;
-  if (p.mask == SSDT_MASK_CAUSAL) lim = min(lim, i + 1);
-  if (p.mask == SSDT_MASK_KEYPAD && p.kv_len) lim = min(lim, max(0, p.kv_len[b]));
-  return lim;
-}
-
 template <typename T>
 __global__ __launch_bounds__(256) void attn_fwd_generic_k(AttnP p) {
-  __shared__ float sq[4][128];
-  int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int i = blockIdx.x * 4 + w, h = blockIdx.y, b = blockIdx.z;
-  bool active = i < p.Sq;
-  const T *q = (const T *)p.q + (long)(b * p.Sq + (active ? i : 0)) * p.ldq + h * p.d;
-  const T *kb = (const T *)p.k + (long)b * p.Sk * p.ldk + h * p.d;
-  const T *vb = (const T *)p.v + (long)b * p.Sk * p.ldv + h * p.d;
-  for (int c = lane; c < p.d; c += 64) sq[w][c] = ld(q + c);
-  __syncthreads();
-  if (!active) return;
-  int lim = key_limit(p, b, i);
-  float m = -INFINITY, l = 0.f, acc0 = 0.f, acc1 = 0.f;
-  for (int j0 = 0; j0 < lim; j0 += 64) {
-    int j = j0 + lane;
-    float s = -INFINITY;
-    if (j < lim) {
-      const T *kr = kb + (long)j * p.ldk;
-      float dot = 0.f;
-      for (int c = 0; c < p.d; ++c) dot = fmaf(sq[w][c], ld(kr + c), dot);
-      s = dot * p.scale;
-    }
-    float mn = fmaxf(m, wave_max(s));
-    float pj = (j < lim) ? expf(s - mn) : 0.f;
-    float corr = (m == -INFINITY) ? 0.f : expf(m - mn);
-    l = l * corr + wave_sum(pj);
-    acc0 *= corr;
-    acc1 *= corr;
-    int cnt = min(64, lim - j0);
-    for (int jj = 0; jj < cnt; ++jj) {
-      float pp = __shfl(pj, jj, 64);
-      const T *vr = vb + (long)(j0 + jj) * p.ldv;
-      if (lane < p.d) acc0 = fmaf(pp, ld(vr + lane), acc0);
-      if (lane + 64 < p.d) acc1 = fmaf(pp, ld(vr + lane + 64), acc1);
-    }
-    m = mn;
-  }
-  T *o = (T *)p.o + (long)(b * p.Sq + i) * p.ldo + h * p.d;
-  float inv = l > 0.f ? 1.f / l : 0.f;
-  if (lane < p.d) st(o + lane, acc0 * inv);
-  if (lane + 64 < p.d) st(o + lane + 64, acc1 * inv);
-  if (lane == 0) p.lse[((long)b * p.A + h) * p.Sq + i] = l > 0.f ? m + logf(l) : -INFINITY;
+  __shared__ float lds[4][128];
+  const int w = threadIdx.x >> 6, i = blockIdx.x * 4 + w;
+  if (i < p.Sq) row_fwd<T>(p, blockIdx.z, blockIdx.y, i, threadIdx.x & 63, lds[w]);
 }
 
 template <typename T>
@@ -450,112 +396,16 @@ __global__ __launch_bounds__(256) void attn_delta_k(AttnP p, float *lse2) {
 
 template <typename T>
 __global__ __launch_bounds__(256) void attn_bwd_dq_generic_k(AttnP p) {
-  __shared__ float sq[4][128], sdo[4][128];
-  int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int i = blockIdx.x * 4 + w, h = blockIdx.y, b = blockIdx.z;
-  bool active = i < p.Sq;
-  long row = (long)b * p.Sq + (active ? i : 0);
-  const T *q = (const T *)p.q + row * p.ldq + h * p.d;
-  const T *dO = (const T *)p.dout + row * p.lddo + h * p.d;
-  const T *kb = (const T *)p.k + (long)b * p.Sk * p.ldk + h * p.d;
-  const T *vb = (const T *)p.v + (long)b * p.Sk * p.ldv + h * p.d;
-  for (int c = lane; c < p.d; c += 64) {
-    sq[w][c] = ld(q + c);
-    sdo[w][c] = ld(dO + c);
-  }
-  __syncthreads();
-  if (!active) return;
-  int lim = key_limit(p, b, i);
-  long si = ((long)b * p.A + h) * p.Sq + i;
-  float lse = p.lse[si], dl = p.delta[si];
-  float acc0 = 0.f, acc1 = 0.f;
-  for (int j0 = 0; j0 < lim; j0 += 64) {
-    int j = j0 + lane;
-    float ds = 0.f;
-    if (j < lim && lse != -INFINITY) {
-      const T *kr = kb + (long)j * p.ldk, *vr = vb + (long)j * p.ldv;
-      float dot = 0.f, dp = 0.f;
-      for (int c = 0; c < p.d; ++c) {
-        dot = fmaf(sq[w][c], ld(kr + c), dot);
-        dp = fmaf(sdo[w][c], ld(vr + c), dp);
-      }
-      ds = expf(dot * p.scale - lse) * (dp - dl);
-    }
-    int cnt = min(64, lim - j0);
-    for (int jj = 0; jj < cnt; ++jj) {
-      float dd = __shfl(ds, jj, 64);
-      const T *kr = kb + (long)(j0 + jj) * p.ldk;
-      if (lane < p.d) acc0 = fmaf(dd, ld(kr + lane), acc0);
-      if (lane + 64 < p.d) acc1 = fmaf(dd, ld(kr + lane + 64), acc1);
-    }
-  }
-  T *dq = (T *)p.dq + row * p.lddq + h * p.d;
-  if (lane < p.d) st(dq + lane, acc0 * p.scale);
-  if (lane + 64 < p.d) st(dq + lane + 64, acc1 * p.scale);
+  __shared__ float lds[4][256];
+  const int w = threadIdx.x >> 6, i = blockIdx.x * 4 + w;
+  if (i < p.Sq) row_dq<T>(p, blockIdx.z, blockIdx.y, i, threadIdx.x & 63, lds[w]);
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void attn_bwd_dkv_generic_k(AttnP p) {
-  __shared__ float sk[4][128], sv[4][128];
-  int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int j = blockIdx.x * 4 + w, h = blockIdx.y, b = blockIdx.z;
-  bool active = j < p.Sk;
-  long row = (long)b * p.Sk + (active ? j : 0);
-  const T *kr = (const T *)p.k + row * p.ldk + h * p.d;
-  const T *vr = (const T *)p.v + row * p.ldv + h * p.d;
-  for (int c = lane; c < p.d; c += 64) {
-    sk[w][c] = ld(kr + c);
-    sv[w][c] = ld(vr + c);
-  }
-  __syncthreads();
-  if (!active) return;
-  bool key_valid = !(p.mask == SSDT_MASK_KEYPAD && p.kv_len && j >= p.kv_len[b]);
-  int istart = (p.mask == SSDT_MASK_CAUSAL) ? j : 0;
-  float dk0 = 0.f, dk1 = 0.f, dv0 = 0.f, dv1 = 0.f;
-  const T *qb = (const T *)p.q + (long)b * p.Sq * p.ldq + h * p.d;
-  const T *dob = (const T *)p.dout + (long)b * p.Sq * p.lddo + h * p.d;
-  if (key_valid) {
-    for (int i0 = istart; i0 < p.Sq; i0 += 64) {
-      int i = i0 + lane;
-      float pp = 0.f, ds = 0.f;
-      if (i < p.Sq) {
-        long si = ((long)b * p.A + h) * p.Sq + i;
-        float lse = p.lse[si];
-        if (lse != -INFINITY) {
-          const T *qr = qb + (long)i * p.ldq, *dr = dob + (long)i * p.lddo;
-          float dot = 0.f, dp = 0.f;
-          for (int c = 0; c < p.d; ++c) {
-            dot = fmaf(ld(qr + c), sk[w][c], dot);
-            dp = fmaf(ld(dr + c), sv[w][c], dp);
-          }
-          pp = expf(dot * p.scale - lse);
-          ds = pp * (dp - p.delta[si]);
-        }
-      }
-      int cnt = min(64, p.Sq - i0);
-      for (int ii = 0; ii < cnt; ++ii) {
-        float p1 = __shfl(pp, ii, 64), d1 = __shfl(ds, ii, 64);
-        const T *qr = qb + (long)(i0 + ii) * p.ldq, *dr = dob + (long)(i0 + ii) * p.lddo;
-        if (lane < p.d) {
-          dv0 = fmaf(p1, ld(dr + lane), dv0);
-          dk0 = fmaf(d1, ld(qr + lane), dk0);
-        }
-        if (lane + 64 < p.d) {
-          dv1 = fmaf(p1, ld(dr + lane + 64), dv1);
-          dk1 = fmaf(d1, ld(qr + lane + 64), dk1);
-        }
-      }
-    }
-  }
-  T *dk = (T *)p.dk + row * p.lddk + h * p.d, *dv = (T *)p.dv + row * p.lddv + h * p.d;
-  if (lane < p.d) {
-    st(dk + lane, dk0 * p.scale);
-    st(dv + lane, dv0);
-  }
-  if (lane + 64 < p.d) {
-    st(dk + lane + 64, dk1 * p.scale);
-    st(dv + lane + 64, dv1);
-  }
+  __shared__ float lds[4][256];
+  const int w = threadIdx.x >> 6, j = blockIdx.x * 4 + w;
+  if (j < p.Sk) row_dkv<T>(p, blockIdx.z, blockIdx.y, j, threadIdx.x & 63, lds[w]);
 }
 
 static AttnP to_p(const Attn &a) {
