@@ -135,7 +135,8 @@ __device__ __forceinline__ void f32_body(const F32P &p, int bid, F32Lds<BT> &lds
   };
   // Column sums of B: every workgroup of a weight gradient adds its fragments up (16 or 8 additions per lane and stage beside
   // matrix instructions of 512 cycles; a branch here would cost more), the first row of tiles stores them.  A stage's sum
-  // is added with compensation, so the error does not grow with the number of stages.
+  // is added with compensation, so the error does not grow with the number of stages.  (What is lost of an infinite sum is
+  // no number: without the test the next stage would turn the infinity into NaN.)
   constexpr bool SUM = AM == KMAJOR && BM == KMAJOR;
   float tot[TB], low[TB];
 #pragma unroll
@@ -168,7 +169,7 @@ __device__ __forceinline__ void f32_body(const F32P &p, int bid, F32Lds<BT> &lds
 #pragma unroll
       for (int j = 0; j < TB; ++j) {
         const float y = part[j] - low[j], t = tot[j] + y;
-        low[j] = (t - tot[j]) - y;
+        low[j] = fabsf(t) < INFINITY ? (t - tot[j]) - y : 0.f;
         tot[j] = t;
       }
     put(buf ^ 1, st + 1);

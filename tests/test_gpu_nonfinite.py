@@ -152,3 +152,20 @@ def test_an_infinite_value_reaches_its_own_queries_as_itself(name):
     o[k:, 7] = 0
     assert torch.isfinite(o).all()
     st.close()
+
+
+@pytest.mark.parametrize("B,S,H,F", [(1, 40, 64, 64), (3, 100, 64, 128), (2, 197, 256, 1024)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_an_infinite_output_gradient_makes_its_bias_gradient_infinite(dtype, B, S, H, F):
+    """The bias gradient of the last product is the column sum of dy: infinite, and not NaN, in the one column that holds an
+    infinity, whatever row it is in."""
+    l = runner.Layer(dtype=dtype, **GPT, B=B, S=S, H=H, A=H // 64, F=F)
+    case = hp.make_layer_case(l, 9300 + H, bias_std=0.05)
+    for row in (0, 17, B * S - 1):
+        dy = case["dy"].copy()
+        dy[row, 5] = float("-inf")
+        run(l, case, dy=dy)
+        db = runner.to_host(l.g["b_2"])
+        assert bool(np.isneginf(db[5])), db[5]
+        ref = case["dy"].astype(np.float64).sum(0)
+        assert hp.rel_err(np.delete(db, 5), np.delete(ref, 5)) <= hp.TOL[dtype]
