@@ -2,8 +2,10 @@
 checker.  bf16 widths that are multiples of 8 go through the matrix-core GEMM with 64- and 128-wide tiles, 64-deep
 stages and a split contraction."""
 import pytest
+import torch
 
-from paper_2408_10013_amd import runner
+from paper_2408_10013_amd import binding as sb
+from paper_2408_10013_amd import runner, synth
 
 import helpers as hp
 from test_gpu_layer import check_against_oracle, run_single_layer
@@ -67,3 +69,58 @@ def test_edges_of_tiles(name, dtype):
     # bar of its own.  The output and every gradient depend on all of them.
     on = run_single_layer(l, case, offload=True, fetch=False)
     check_against_oracle(l, case, on, hp.TOL[dtype])
+
+
+PRECISE = {
+    "d32": dict(GPT, B=2, S=333, H=128, A=4, F=64),
+    "d64": dict(BERT, B=2, S=333, H=128, A=2, F=64),
+    "d96": dict(GPT, B=2, S=200, H=192, A=2, F=64),
+    "d128": dict(GPT, B=2, S=300, H=256, A=2, F=64),
+    "d64_cross_lengths": dict(GPT, mask="none", B=3, S=150, H=128, A=2, F=64),
+}
+
+
+@pytest.mark.parametrize("name", list(PRECISE))
+def test_probabilities_enter_the_products_in_fp32(name):
+    """bf16 attention of any size: outputs and value gradients against 64 bits, from the very q, k, v and dO that the kernels
+    read.  Inputs exact, probabilities and sums in fp32: an output can only miss the correctly rounded bf16 where the exact
+    value lies within its fp32 error of a rounding boundary.  Exponents of up to 16 are rounded to 2^-20, boundaries are 2^-8
+    of a value apart: 2 x 2^-20 / 2^-8 = 0.05 % of the outputs (0.02 to 0.06 % measured).  Twice that is the bar;
+    probabilities rounded to 16 bits give 0.2 %, to bf16 30 %."""
+    l = runner.Layer(dtype="bf16", **PRECISE[name])
+    case = hp.make_layer_case(l, 8500 + l.H, bias_std=0.05, kv_len_range=(l.S // 2, l.S) if l.mask == "keypad" else None)
+    case["w"]["w_qkv"] = synth.bf16_round(case["w"]["w_qkv"] * 4)
+    st = runner.Stack([l], 3 * runner.saved_bytes_per_layer(l) + (1 << 20), 0, "cuda:0", budget_bytes=0)
+    hp.load_weights(l, case["w"], st.dev)
+    x, dy = (runner.to_device(case[k], "bf16", st.dev) for k in ("x", "dy"))
+    kv = torch.from_numpy(case["kv_len"]).to(st.dev) if "kv_len" in case else None
+    kvp = kv.data_ptr() if kv is not None else 0
+    dx = torch.empty_like(dy)
+    sb.ssdt_step_begin(st.ctx, 1)
+    _, saved = sb.ssdt_layer_fwd(st.ctx, l.desc, l.wstruct, 0, x.data_ptr(), 0, kvp, st.ws_ptr, st.ws_bytes, st.stream)
+    sb.ssdt_layer_bwd(st.ctx, l.desc, l.wstruct, saved, kvp, dy.data_ptr(), dx.data_ptr(), 0, l.gstruct, st.ws_ptr, st.ws_bytes,
+                      st.stream)
+    torch.cuda.synchronize()
+    tmp, base = sb.ssdt_layer_bwd_temporaries(l.desc), st.ws_ptr - st.ws.data_ptr()
+
+    def heads(t, cols, at):      # [B, A, S, d] of the columns from `at` on
+        t = t.double().cpu().reshape(l.B, l.S, cols)[:, :, at:at + l.H]
+        return t.reshape(l.B, l.S, l.A, -1).transpose(1, 2)
+    qkv = st.view(saved.e[sb.SV_NAMES.index("qkv")].ptr, (l.T, 3 * l.H))
+    q, k, v = (heads(qkv, 3 * l.H, i * l.H) for i in range(3))
+    o = heads(st.view(saved.e[sb.SV_NAMES.index("o")].ptr, (l.T, l.H)), l.H, 0)
+    n = l.T * l.H * 2
+    do = heads(st.ws[base + tmp["t0"]:base + tmp["t0"] + n].view(torch.bfloat16), l.H, 0)   # gradient of o, still there
+    dv = heads(st.ws[base + tmp["d_qkv"]:base + tmp["d_qkv"] + 3 * n].view(torch.bfloat16), 3 * l.H, 2 * l.H)
+    s = q @ k.transpose(2, 3) / (l.H // l.A) ** 0.5
+    if l.mask == "causal":
+        s.masked_fill_(torch.ones(l.S, l.S, dtype=torch.bool).triu(1), float("-inf"))
+    if l.mask == "keypad":
+        for b in range(l.B):
+            s[b, :, :, int(case["kv_len"][b]):] = float("-inf")
+    p = torch.softmax(s, -1)
+    st.close()
+    for what, got, ref in (("o", o, p @ v), ("dv", dv, p.transpose(2, 3) @ do)):
+        missed = float((got != ref.to(torch.bfloat16).double()).double().mean())
+        print(name, what, "%.4f %%" % (100 * missed))
+        assert missed <= 1e-3, (what, missed)
