@@ -341,7 +341,9 @@ typedef struct ssdt_layer_saved {
 } ssdt_layer_saved;
 
 /* Bytes of scratch (DEVICE, 256-byte aligned, contents undefined between calls) that the two calls
- * below need for `desc`.  E_INVAL / E_UNSUPPORTED for an unusable description. */
+ * below need for `desc`.  E_INVAL / E_UNSUPPORTED for an unusable description.
+ * bwd_bytes includes room for partial products where a layer is faster with them; ssdt_layer_bwd also takes a workspace
+ * without it (the products of bf16 weights and inputs are then summed in another order, one and the same for all such sizes). */
 ssdt_status ssdt_layer_workspace(const ssdt_layer_desc *desc, size_t *fwd_bytes, size_t *bwd_bytes);
 
 /* Where ssdt_layer_bwd leaves its intermediate gradients: byte offsets from `ws` (for inspection and for

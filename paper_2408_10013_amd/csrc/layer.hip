@@ -88,7 +88,8 @@ struct BwdBufs {
   float *partial, *delta;
   size_t scratch_bytes, partial_floats;
 };
-void bwd_layout(const Dims &D, Ws &w, BwdBufs *b) {
+// `splits`: with room for partial products
+void bwd_layout(const Dims &D, Ws &w, BwdBufs *b, bool splits = true) {
   size_t TH = (size_t)D.T * D.H * D.e;
   b->dh1 = w.take((size_t)D.T * D.F * D.e);
   b->t0 = w.take(TH); b->t1 = w.take(TH); b->t2 = w.take(TH);
@@ -99,11 +100,11 @@ void bwd_layout(const Dims &D, Ws &w, BwdBufs *b) {
   b->partial_floats = k::colreduce_partial_floats((int)rows, (int)cols);
   b->partial = (float *)w.take(b->partial_floats * 4);
   b->delta = (float *)w.take((size_t)2 * D.B * D.A * D.S * 4);  // delta, and lse in base-2 units behind it
-  // Partial products are a matter of speed only: they do not push a layer beyond what ssdt_layer_bwd_static can serve.
-  // The amount depends on the description alone, so that every caller gets the same sums in the same order.
+  // Partial products are a matter of speed only: they do not push a layer beyond what ssdt_layer_bwd_static can serve, and
+  // a workspace without room for them will do.  All of it or none: sums come in one of two orders, whatever the size.
   const Scratch sc = bwd_scratch(D);
   const size_t base = up(w.used, 256) + 512;
-  b->scratch_bytes = std::max(sc.copies, sc.splits);
+  b->scratch_bytes = splits ? std::max(sc.copies, sc.splits) : sc.copies;
   if (base + sc.copies <= SSDT_STATIC_WS_BYTES) b->scratch_bytes = std::min(b->scratch_bytes, (SSDT_STATIC_WS_BYTES - base) / 256 * 256);
   b->scratch = b->scratch_bytes ? w.take(b->scratch_bytes) : nullptr;
 }
@@ -374,6 +375,10 @@ ssdt_status layer_bwd_impl(ssdt_ctx *ctx, const ssdt_layer_desc *desc, const ssd
   Ws wsa(ws, ws_bytes);
   BwdBufs bf;
   bwd_layout(D, wsa, &bf);
+  if (!wsa.ok) {
+    wsa = Ws(ws, ws_bytes);
+    bwd_layout(D, wsa, &bf, false);
+  }
   if (!wsa.ok) return ctx->fail(SSDT_E_NOMEM, "layer_bwd: workspace of %zu bytes needed, %zu given", wsa.used, ws_bytes);
   hipStream_t st = (hipStream_t)stream;
   const int dt = D.dt;

@@ -1,9 +1,14 @@
 """Layers whose backward just fits the 64 MiB of ssdt_layer_bwd_static stay servable: what the kernels take for speed only
-(partial products of split contractions, finer chunks of column sums) must not push them over the edge."""
+(partial products of split contractions, finer chunks of column sums) must not push them over the edge, nor make a workspace
+too small that holds everything else."""
 import pytest
+import torch
 
 from paper_2408_10013_amd import binding as sb
 from paper_2408_10013_amd import runner
+
+import helpers as hp
+from test_gpu_layer import check_against_oracle
 
 GPT = dict(arch="gpt_preln", act="gelu", norm="layernorm", mask="causal", has_bias=True, eps=1e-5)
 BERT = dict(arch="bert_postln", act="gelu", norm="layernorm", mask="keypad", has_bias=True, eps=1e-5)
@@ -23,3 +28,36 @@ EDGE = [
 def test_backward_workspace_stays_within_the_static_one(case):
     _, bwd = sb.ssdt_layer_workspace(runner.Layer(**case).desc)
     assert bwd <= 64 << 20
+
+
+# (bytes: what ssdt_layer_workspace reported for the backward before products were split)
+SMALL = [
+    (dict(GPT, dtype="bf16", B=2, S=128, H=256, A=2, F=1024), 2003200),
+    (dict(T5_DEC, act="gelu", dtype="bf16", B=2, S=200, S_kv=700, H=256, A=4, F=512), 6075136),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case,nbytes", SMALL, ids=lambda c: c["arch"] if isinstance(c, dict) else "")
+def test_backward_takes_a_workspace_without_room_for_partial_products(case, nbytes):
+    l = runner.Layer(**case)
+    assert sb.ssdt_layer_workspace(l.desc)[1] > nbytes
+    c = hp.make_layer_case(l, 8800 + l.H, bias_std=0.05)
+    st = runner.Stack([l], 3 * runner.saved_bytes_per_layer(l) + (1 << 20), 0, "cuda:0", budget_bytes=0)
+    hp.load_weights(l, c["w"], st.dev)
+    x, dy = (runner.to_device(c[k], l.dtype, st.dev) for k in ("x", "dy"))
+    enc = runner.to_device(c["enc"], l.dtype, st.dev) if "enc" in c else None
+    d_enc = torch.zeros_like(enc) if enc is not None else None
+    ptr = lambda t: t.data_ptr() if t is not None else 0
+    guard = torch.full((nbytes + 4096,), 0xA5, dtype=torch.uint8, device=st.dev)
+    assert guard.data_ptr() % 256 == 0
+    dx = torch.empty_like(dy)
+    sb.ssdt_step_begin(st.ctx, 1)
+    y, saved = sb.ssdt_layer_fwd(st.ctx, l.desc, l.wstruct, 0, x.data_ptr(), ptr(enc), 0, st.ws_ptr, st.ws_bytes, st.stream)
+    sb.ssdt_layer_bwd(st.ctx, l.desc, l.wstruct, saved, 0, dy.data_ptr(), dx.data_ptr(), ptr(d_enc), l.gstruct, guard.data_ptr(),
+                      nbytes, st.stream)
+    torch.cuda.synchronize()
+    assert bool((guard[nbytes:] == 0xA5).all())
+    res = dict(y=runner.to_host(st.view(y, (l.T, l.H))), dx=dx, d_enc=d_enc, grads=l.g)
+    st.close()
+    check_against_oracle(l, c, res, hp.TOL[l.dtype])
