@@ -43,6 +43,13 @@ HEADS = {
     "cross_d112": dict(T5, B=2, S=31, S_kv=129, H=112, A=1, F=64),
     "cross_d12": dict(T5, B=2, S=37, S_kv=21, H=36, A=3, F=52),   # bf16, ReLU: K-contiguous rows element by element
     "cross_d18": dict(T5, B=1, S=40, S_kv=70, H=54, A=3, F=64),   # a head size that is no multiple of 4
+    # bf16: where the row kernels take over, on either side of the lines
+    "causal_5_tokens": dict(GPT, B=64, S=5, H=64, A=8, F=32),
+    "causal_6_tokens": dict(GPT, B=64, S=6, H=64, A=8, F=32),
+    "cross_1_of_32": dict(T5, B=64, S=1, S_kv=32, H=128, A=16, F=32),
+    "cross_1_of_33": dict(T5, B=64, S=1, S_kv=33, H=128, A=16, F=32),
+    "cross_4_of_16": dict(T5, B=64, S=4, S_kv=16, H=128, A=16, F=32),
+    "cross_5_of_16": dict(T5, B=64, S=5, S_kv=16, H=128, A=16, F=32),
     "cross_d64_heads8": dict(T5, B=2, S=150, S_kv=300, H=256, A=4, F=64),
 }
 
