@@ -561,6 +561,9 @@ hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, hipStream_t s) {
   hipError_t e = prepare(w, &pw);
   if (e == hipSuccess) e = prepare(d, &pd);
   if (e != hipSuccess) return e;
+  if (g_tile_cfg >= 0) pp.cfg = g_tile_cfg;
+  if (g_tile_splits > 0 && std::max(split_bytes(pw.M, pw.N, g_tile_splits), split_bytes(pd.M, pd.N, g_tile_splits)) <= half_of(scratch))
+    pp.sw = pp.sd = g_tile_splits;
   choose(&pw, pp.cfg, pp.sw, (float *)w.scratch);
   choose(&pd, pp.cfg, pp.sd, (float *)((char *)w.scratch + half_of(scratch)));
   switch (pp.cfg) {

@@ -1,9 +1,13 @@
 """The kernels that take any size, at the edges of their tiles: forward and backward of small layers against the CPU
-checker.  bf16 widths that are multiples of 8 go through the matrix-core GEMM with 64- and 128-wide tiles, 64-deep
-stages and a split contraction."""
+checker.  bf16 widths that are multiples of 8 go through the matrix-core GEMM with 64-deep stages and a split contraction; sizes as
+small as these choose its 64 x 64 tiles (fp32: 32 x 32), the larger tiles are pinned."""
+import ctypes
+
+import numpy as np
 import pytest
 import torch
 
+from oracle import layer_oracle as lo
 from paper_2408_10013_amd import binding as sb
 from paper_2408_10013_amd import runner, synth
 
@@ -41,7 +45,7 @@ HEADS = {
     "causal_d104": dict(GPT, B=1, S=33, H=104, A=1, F=64),
     "keypad_d120": dict(BERT, B=3, S=161, H=240, A=2, F=64),
     "cross_d112": dict(T5, B=2, S=31, S_kv=129, H=112, A=1, F=64),
-    "cross_d12": dict(T5, B=2, S=37, S_kv=21, H=36, A=3, F=52),   # bf16, ReLU: K-contiguous rows element by element
+    "cross_d12": dict(T5, B=2, S=37, S_kv=21, H=36, A=3, F=52),   # widths that are no multiple of 8
     "cross_d18": dict(T5, B=1, S=40, S_kv=70, H=54, A=3, F=64),   # a head size that is no multiple of 4
     # bf16: where the row kernels take over, on either side of the lines
     "causal_5_tokens": dict(GPT, B=64, S=5, H=64, A=8, F=32),
@@ -64,6 +68,165 @@ def test_attention_of_any_length_and_head_size(name, dtype):
         case["kv_len"][-1] = 0     # a sequence without keys
     on = run_single_layer(l, case, offload=True, fetch=False)
     check_against_oracle(l, case, on, hp.TOL[dtype])
+
+
+# ReLU: at lengths or widths that are not whole tiles the forward keeps the order of additions of the FMA kernels, in bf16 too
+RELU = {
+    "d12": dict(T5, act="relu", B=2, S=37, S_kv=45, H=36, A=3, F=52),           # K-contiguous rows element by element; heads
+    "d20_enc": dict(T5, arch="t5_enc", mask="none", act="relu", B=2, S=70, H=60, A=3, F=72),  # that end inside a 16-byte load
+    "d64": dict(T5, act="relu", B=2, S=65, S_kv=130, H=128, A=2, F=200),
+    "d96": dict(T5, act="relu", B=1, S=100, S_kv=33, H=96, A=1, F=136),
+    "d128": dict(T5, act="relu", B=1, S=67, S_kv=64, H=256, A=2, F=72),
+    "d18": dict(T5, act="relu", B=1, S=40, S_kv=70, H=54, A=3, F=64),
+}
+
+
+@pytest.mark.parametrize("name", list(RELU))
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_relu_layers_of_any_size(name, dtype):
+    """Forward and saved tensors against the checker; the backward against the checker's with ReLU's decisions taken from the
+    stored activations, as the library takes them."""
+    l = runner.Layer(dtype=dtype, **RELU[name])
+    case = hp.make_layer_case(l, 8200 + l.H)
+    on = run_single_layer(l, case, offload=True)
+    check_against_oracle(l, case, on, hp.TOL[dtype], check_bwd=False)
+    d = hp.oracle_desc(l)
+    _, sv = lo.layer_fwd(d, case["w"], case["x"], case.get("enc"), None)
+    dx, denc, gr = hp.layer_bwd_same_relu_decisions(d, case["w"], sv, case["dy"], None, on["saved"]["g"])
+    errs = {"dx": hp.rel_err(runner.to_host(on["dx"]), dx)}
+    if denc is not None:
+        errs["d_enc"] = hp.rel_err(runner.to_host(on["d_enc"]), denc)
+    assert set(on["grads"]) == set(gr)
+    for k in gr:
+        errs["grad." + k] = hp.rel_err(runner.to_host(on["grads"][k]), gr[k])
+    bad = {k: e for k, e in errs.items() if not e <= hp.TOL[dtype]}
+    assert not bad, bad
+
+
+@pytest.mark.parametrize("H,A", [(36, 3), (128, 2)])
+def test_relu_forward_products_add_in_the_order_of_k(H, A):
+    """bf16, ReLU, ragged: every element of the projection is a chain of fused multiply-adds, k ascending, bit for bit.  (In
+    64 bits a product of two bf16 is exact, and so is its sum with an fp32 number but where that outweighs it beyond 2^29.)"""
+    l = runner.Layer("t5_enc", "bf16", B=2, S=37, H=H, A=A, F=64, act="relu", norm="rmsnorm", mask="none", has_bias=False, eps=1e-6)
+    case = hp.make_layer_case(l, 8300 + H)
+    saved = run_single_layer(l, case, offload=False)["saved"]
+    a, w = saved["a"].astype(np.float64), case["w"]["w_qkv"].astype(np.float64)
+    acc = np.zeros((l.T, 3 * H), dtype=np.float32)
+    for k in range(H):
+        acc = (a[:, k:k + 1] * w[k] + acc).astype(np.float32)
+    assert np.array_equal(saved["qkv"], synth.bf16_round(acc))
+
+
+@pytest.fixture
+def pin():
+    """Sets a kernel's test hook for the time of a test."""
+    was = []
+
+    def set_(name, value):
+        v = ctypes.c_int.in_dll(sb.lib(), "_ZN4ssdt1k%d%sE" % (len(name), name))
+        was.append((v, v.value))
+        v.value = value
+    yield set_
+    for v, old in reversed(was):
+        v.value = old
+
+
+# rows 333 (2 tiles of 128 and 77 rows), widths 200 (1 and 72), 264 (2 and 8), 600; contractions with tails of 8 and 13 of 64
+RAGGED = dict(GPT, B=3, S=111, H=200, A=5, F=264)
+
+
+@pytest.mark.parametrize("splits", [1, 2, 3])
+@pytest.mark.parametrize("tile", [0, 1, 2])
+def test_every_bf16_tile_at_ragged_sizes(pin, tile, splits):
+    """128 x 128, 64 x 128 and 64 x 64 tiles, the contraction whole and in parts, both products of a backward together."""
+    pin("g_tile_cfg", tile)
+    pin("g_tile_splits", splits)
+    l = runner.Layer(dtype="bf16", **RAGGED)
+    case = hp.make_layer_case(l, 8400 + tile, bias_std=0.05)
+    check_against_oracle(l, case, run_single_layer(l, case, offload=False, fetch=False), hp.TOL["bf16"])
+
+
+@pytest.mark.parametrize("size", ["ragged", "odd_k"])
+@pytest.mark.parametrize("tile", [64, 32])
+def test_every_f32_tile_at_ragged_sizes(pin, tile, size):
+    pin("g_f32_tile", tile)
+    v = RAGGED if size == "ragged" else dict(RAGGED, H=90, A=3, F=131)
+    l = runner.Layer(dtype="f32", **v)
+    case = hp.make_layer_case(l, 8450 + tile, bias_std=0.05)
+    check_against_oracle(l, case, run_single_layer(l, case, offload=False, fetch=False), hp.TOL["f32"])
+
+
+def run_backward(l, case, x=None, dx=None, passes=1):
+    """Output, dx and gradients of one layer, bypassing the cache; with several passes the gradients add up."""
+    st = runner.Stack([l], 4 * runner.saved_bytes_per_layer(l) + (1 << 20), 0, "cuda:0", budget_bytes=0)
+    if not l.w:
+        hp.load_weights(l, case["w"], st.dev)
+    x = runner.to_device(case["x"], l.dtype, st.dev) if x is None else x
+    dy = runner.to_device(case["dy"], l.dtype, st.dev)
+    dx = torch.empty_like(dy) if dx is None else dx
+    kv = torch.from_numpy(case["kv_len"]).to(st.dev) if "kv_len" in case else None
+    kvp = kv.data_ptr() if kv is not None else 0
+    sb.ssdt_step_begin(st.ctx, 1)
+    y, saved = sb.ssdt_layer_fwd(st.ctx, l.desc, l.wstruct, 0, x.data_ptr(), 0, kvp, st.ws_ptr, st.ws_bytes, st.stream)
+    for i in range(passes):
+        sb.ssdt_layer_bwd(st.ctx, l.desc_acc if i else l.desc, l.wstruct, saved, kvp, dy.data_ptr(), dx.data_ptr(), 0, l.gstruct,
+                          st.ws_ptr, st.ws_bytes, st.stream)
+    torch.cuda.synchronize()
+    res = dict(y=runner.to_host(st.view(y, (l.T, l.H))), dx=dx.clone(), d_enc=None, grads=l.g)
+    st.close()
+    return res
+
+
+@pytest.mark.parametrize("tile", [-1, 0])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_split_products_add_to_what_the_gradients_hold(pin, dtype, tile):
+    """1665 tokens, 64 x 128 weights: the contraction over tokens is split in bf16, and a second backward adds to the gradients
+    in the reduction's epilogue, bias sums included."""
+    if tile >= 0:
+        pin("g_tile_cfg", tile)
+    l = runner.Layer(dtype=dtype, **GPT, **SIZES["split_tokens"])
+    case = hp.make_layer_case(l, 8600, bias_std=0.05)
+    res = run_backward(l, case, passes=2)
+    res["grads"] = {k: v.float() / 2 for k, v in res["grads"].items()}   # (exact)
+    check_against_oracle(l, case, res, hp.TOL[dtype])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_dx_may_overwrite_the_input(dtype):
+    """A post-norm layer whose dx takes the place of x: the weight gradient must have read x by then."""
+    l = runner.Layer(dtype=dtype, **BERT, B=2, S=70, H=128, A=2, F=200)
+    case = hp.make_layer_case(l, 8650, bias_std=0.05, kv_len_range=(40, 70))
+    x = runner.to_device(case["x"], dtype, torch.device("cuda:0"))
+    check_against_oracle(l, case, run_backward(l, case, x=x, dx=x), hp.TOL[dtype])
+
+
+def shifted(t, n):
+    """A copy of t that starts n elements behind an aligned address."""
+    buf = torch.empty(t.numel() + 256, dtype=t.dtype, device=t.device)
+    assert buf.data_ptr() % 256 == 0
+    return buf[n:n + t.numel()].view(t.shape).copy_(t)
+
+
+@pytest.mark.parametrize("what", ["weights", "input", "gradients"])
+@pytest.mark.parametrize("n", [1, 4])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_operands_that_are_not_16_byte_aligned(dtype, n, what):
+    """Whole tiles of 128.  bf16: products with such operands go through transposed copies and the 128 x 128 kernel (weights in
+    the forward, x in the weight gradient), or through the FMA kernel."""
+    l = runner.Layer(dtype=dtype, **BERT, B=2, S=128, H=128, A=1, F=256)
+    case = hp.make_layer_case(l, 8700, bias_std=0.05, kv_len_range=(64, 128))
+    dev = torch.device("cuda:0")
+    hp.load_weights(l, case["w"], dev)
+    x = runner.to_device(case["x"], dtype, dev)
+    if what == "weights":
+        l.w = {k: shifted(v, n) if k.startswith("w_") else v for k, v in l.w.items()}
+        l.wstruct = sb.make_weights({k: v.data_ptr() for k, v in l.w.items()})
+    elif what == "gradients":
+        l.g = {k: shifted(v, n) for k, v in l.g.items()}
+        l.gstruct = sb.make_weights({k: v.data_ptr() for k, v in l.g.items()})
+    else:
+        x = shifted(x, n)
+    check_against_oracle(l, case, run_backward(l, case, x=x), hp.TOL[dtype])
 
 
 @pytest.mark.parametrize("name", list(SIZES))
