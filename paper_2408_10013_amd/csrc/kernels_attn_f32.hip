@@ -397,13 +397,14 @@ hipError_t attn_fwd_f32(const Attn &a, hipStream_t s) {
 }
 
 hipError_t attn_bwd_f32(const Attn &a, hipStream_t s) {
-  if (!f32_supported(a, true) || !f32_worth(a, true)) return hipErrorNotSupported;
+  const int nkb = (a.Sk + 63) / 64, nqb = (a.Sq + 63) / 64;
+  const long workgroups = (long)(nkb + nqb) * a.A * a.B;
+  if (!f32_supported(a, true) || !f32_worth(a, true) || !one_axis(workgroups)) return hipErrorNotSupported;
   prof::Scope ps(prof::ATTN_BWD, 2 * f32_flops(a), 0, s);
   hipError_t e = attn_delta(a, nullptr, s);
   if (e != hipSuccess) return e;
   const FaF p = to_f32(a);
-  const int nkb = (a.Sk + 63) / 64, nqb = (a.Sq + 63) / 64;
-  const dim3 grid((unsigned)((long)(nkb + nqb) * a.A * a.B));
+  const dim3 grid((unsigned)workgroups);
 #define SSDT_GO(D) hipLaunchKernelGGL(fa_f32_bwd_k<D>, grid, dim3(256), 0, s, p, nkb, nqb)
   SSDT_BY_HEAD(a.d, SSDT_GO);
 #undef SSDT_GO

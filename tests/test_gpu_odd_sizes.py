@@ -146,6 +146,14 @@ def test_every_bf16_tile_at_ragged_sizes(pin, tile, splits):
     check_against_oracle(l, case, run_single_layer(l, case, offload=False, fetch=False), hp.TOL["bf16"])
 
 
+@pytest.mark.parametrize("name", ["d12", "d64"])
+def test_relu_products_with_the_larger_tile(pin, name):
+    pin("g_f32_tile", 64)
+    l = runner.Layer(dtype="bf16", **RELU[name])
+    case = hp.make_layer_case(l, 8200 + l.H)
+    check_against_oracle(l, case, run_single_layer(l, case, offload=False), hp.TOL["bf16"], check_bwd=False)
+
+
 @pytest.mark.parametrize("size", ["ragged", "odd_k"])
 @pytest.mark.parametrize("tile", [64, 32])
 def test_every_f32_tile_at_ragged_sizes(pin, tile, size):
@@ -191,9 +199,13 @@ def test_split_products_add_to_what_the_gradients_hold(pin, dtype, tile):
     check_against_oracle(l, case, res, hp.TOL[dtype])
 
 
+@pytest.mark.parametrize("tile", [-1, 0, 1])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_dx_may_overwrite_the_input(dtype):
+def test_dx_may_overwrite_the_input(pin, dtype, tile):
     """A post-norm layer whose dx takes the place of x: the weight gradient must have read x by then."""
+    if tile >= 0:
+        pin("g_tile_cfg", tile)
+        pin("g_f32_tile", 64)
     l = runner.Layer(dtype=dtype, **BERT, B=2, S=70, H=128, A=2, F=200)
     case = hp.make_layer_case(l, 8650, bias_std=0.05, kv_len_range=(40, 70))
     x = runner.to_device(case["x"], dtype, torch.device("cuda:0"))
@@ -239,6 +251,37 @@ def test_edges_of_tiles(name, dtype):
     # bar of its own.  The output and every gradient depend on all of them.
     on = run_single_layer(l, case, offload=True, fetch=False)
     check_against_oracle(l, case, on, hp.TOL[dtype])
+
+
+# (workgroups of the tile kernels at 2^24 and more: forward 65535 x 257, backward 2 x 65535 x 129)
+@pytest.mark.parametrize("S,A", [(6, 257), (9, 129)])
+def test_more_heads_than_one_axis_of_a_grid_holds(S, A):
+    """65535 short sequences: first, middle and last ones against the checker."""
+    v = dict(T5, arch="t5_enc", mask="none", S=S, H=8 * A, A=A, F=8)
+    l, some = runner.Layer(dtype="bf16", B=65535, **v), [0, 1, 32767, 65534]
+    ref = runner.Layer(dtype="bf16", B=len(some), **v)
+    case = hp.make_layer_case(ref, 8900 + A)
+    st = runner.Stack([l], runner.saved_bytes_per_layer(l) + 2 * l.T * l.H * 2 + (64 << 20), 0, "cuda:0", budget_bytes=0)
+    hp.load_weights(l, case["w"], st.dev)
+    rows = torch.cat([torch.arange(b * S, (b + 1) * S) for b in some]).to(st.dev)
+    data = {}
+    for k in ("x", "dy"):
+        data[k] = torch.ones(l.T, l.H, dtype=torch.bfloat16, device=st.dev)
+        data[k][rows] = runner.to_device(case[k], "bf16", st.dev)
+    dx = torch.empty_like(data["dy"])
+    sb.ssdt_step_begin(st.ctx, 1)
+    y, saved = sb.ssdt_layer_fwd(st.ctx, l.desc, l.wstruct, 0, data["x"].data_ptr(), 0, 0, st.ws_ptr, st.ws_bytes, st.stream)
+    sb.ssdt_layer_bwd(st.ctx, l.desc, l.wstruct, saved, 0, data["dy"].data_ptr(), dx.data_ptr(), 0, l.gstruct, st.ws_ptr,
+                      st.ws_bytes, st.stream)
+    torch.cuda.synchronize()
+    d = hp.oracle_desc(ref)
+    y_ref, sv = lo.layer_fwd(d, case["w"], case["x"])
+    dx_ref, _, _ = lo.layer_bwd(d, case["w"], sv, case["dy"])
+    errs = {"y": hp.rel_err(runner.to_host(st.view(y, (l.T, l.H))[rows]), y_ref), "dx": hp.rel_err(runner.to_host(dx[rows]), dx_ref)}
+    o = st.view(saved.e[sb.SV_NAMES.index("o")].ptr, (l.T, l.H))[rows]
+    errs["o"] = hp.rel_err(runner.to_host(o), sv["o"])
+    st.close()
+    assert max(errs.values()) <= hp.TOL["bf16"], errs
 
 
 PRECISE = {
