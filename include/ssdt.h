@@ -291,6 +291,9 @@ ssdt_status ssdt_profile_read(ssdt_ctx *ctx, ssdt_kernel_time *out, uint32_t cap
 enum { SSDT_ARCH_GPT_PRELN = 0, SSDT_ARCH_BERT_POSTLN = 1, SSDT_ARCH_T5_ENC = 2, SSDT_ARCH_T5_DEC = 3 };
 enum { SSDT_ACT_GELU = 0, SSDT_ACT_RELU = 1 };         /* GELU in its erf form */
 enum { SSDT_NORM_LAYERNORM = 0, SSDT_NORM_RMSNORM = 1 };
+/* Infinities and NaN in masked keys, and in queries that a key does not answer to, do not reach what the mask hides them
+ * from; but in bf16 at head size 64 or 128 with S and S_kv multiples of 128 they do, as NaN, within a tile of 64 under
+ * SSDT_MASK_CAUSAL (tokens up to 63 before or after) and in the gradients of padded keys. */
 enum { SSDT_MASK_NONE = 0, SSDT_MASK_CAUSAL = 1, SSDT_MASK_KEYPAD = 2 };
 
 typedef struct ssdt_layer_desc {
@@ -394,8 +397,9 @@ ssdt_status ssdt_layer_bwd(ssdt_ctx *ctx, const ssdt_layer_desc *desc, const ssd
 
 /* ssdt_layer_bwd for callers that cannot allocate device memory or have none to hand over as a workspace (code
  * under stream capture, tight serving or training loops, harnesses that forbid allocation): same arguments, results
- * and ordering rules as ssdt_layer_bwd, bit for bit, but the workspace is an array of SSDT_STATIC_WS_BYTES that is
- * part of the library's device code (one per GPU the library runs on, held until the process ends).  The call
+ * and ordering rules as ssdt_layer_bwd with the workspace that ssdt_layer_workspace asks for, bit for bit, but the
+ * workspace is an array of SSDT_STATIC_WS_BYTES that is part of the library's device code (one per GPU the library runs
+ * on, held until the process ends).  The call
  * allocates and frees no device memory.  A layer whose backward needs more workspace than that
  * (ssdt_layer_workspace says how much) is refused with SSDT_E_NOMEM and a message; nothing is enqueued then.
  * Every call on a GPU shares that GPU's array, whatever the context: calls whose GPU work can overlap in time

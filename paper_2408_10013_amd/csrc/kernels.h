@@ -108,7 +108,7 @@ struct Attn {
   } while (0)
 hipError_t attn_fwd(const Attn &a, hipStream_t s);
 hipError_t attn_bwd(const Attn &a, hipStream_t s);
-// the one-wavefront-per-row kernels, any shape (attn_fwd / attn_bwd fall back to them)
+// the one-wavefront-per-row kernels (attn_rows.h), any shape: where they are faster, and for what the tile kernels do not take
 hipError_t attn_fwd_generic(const Attn &a, hipStream_t s);
 hipError_t attn_bwd_generic(const Attn &a, hipStream_t s);
 // delta[b,h,i] = sum_c o[i,c] dout[i,c]; with lse2 also lse in base-2 units, +inf for a row without keys
@@ -135,7 +135,8 @@ hipError_t gemm_mfma_tile_bf16(const Gemm &g, hipStream_t s);  // any number of 
 bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype);   // shape conditions of that kernel
 bool gemm_large_fits(int M, int N, int K, bool transA, bool transB, int dtype);  // the 256 x 256 kernels should take it
 // A linear's weight gradient w (transA) and input gradient d (transB) in one launch; hipErrorNotSupported (nothing launched)
-// where two launches are better.  Neither may write what the other reads.  w's bias sums as in gemm() for bf16, not for fp32.
+// where two launches are better.  Neither may write what the other reads.  With w.colsum the bias sums fall out of w's kernel, in
+// fp32 here only (gemm() leaves them to colsum() there).
 hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, hipStream_t s);
 hipError_t gemm_pair_f32(const Gemm &w, const Gemm &d, hipStream_t s);
 size_t gemm_pair_scratch_bytes(int rows, int in, int out, int dtype);  // of gemm_pair_bf16 for a linear in -> out

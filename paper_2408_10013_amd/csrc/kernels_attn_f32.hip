@@ -1,11 +1,12 @@
-// fp32 attention (forward also on bf16 storage, see Attn::ordered) on the matrix cores (v_mfma_f32_16x16x4_f32): forward with an online softmax and the two-kernel backward,
-// any sequence length, head sizes that are multiples of 4.
+// fp32 attention (forward also on bf16 storage, see Attn::ordered) on the matrix cores (v_mfma_f32_16x16x4_f32): forward with
+// an online softmax and the backward with both sides in one launch, any sequence length, head sizes that are multiples of 4.
 //
 // The one-wavefront-per-row kernels it replaces read every key and value once per query and add the scores element by
 // element; they were bound by those loads (64 sequences-times-heads of 512 x 512 x 64, causal: 532 us forward, 1670 backward; 16 of
-// 1024 x 1024 x 128: 1085 and 3591).  Here 16 queries share each tile of 64 keys out of LDS: 55 and 174, 128 and 500 (the
-// matrix pipe's fp32 rate, 157 TFLOP/s, is the bound; 0.1 of it on the second, whose wavefronts have few registers left).
-// The results are the same bits: the
+// 1024 x 1024 x 128: 1085 and 3591).  Here 16 queries share each tile of 64 keys out of LDS: 55 and 174, 131 and 343 (the
+// matrix pipe's fp32 rate, 157 TFLOP/s, is the bound; a quarter of it is reached on the first, a sixth to a fifth on the second).  The backward
+// at head sizes above 64 does not fit its registers: 8 vector registers are spilled at 96 and 60 at 128, some of them inside
+// the tile loop.  The results are the same bits: the
 // instruction adds its four products one after the other, k ascending, and everything else is done in the same order
 // (scores over columns, exponentials of the same differences, the sum of a tile's 64 probabilities as the same tree,
 // outputs over keys, gradients over keys or queries, one rescale per tile).

@@ -1,10 +1,9 @@
 // Generic kernels of the layer, templated on the storage type (float / bf16), fp32 math.
 //
-//  - gemm_generic: LDS-tiled FMA matrix multiply for any transposition and any shape; the
-//    fp32 path of the layer and the fallback of the bf16 path for shapes the matrix-core
-//    kernel does not take.
-//  - attn_*_generic: one wavefront per query (or key) row with an online softmax; exact
-//    -inf masking; used for fp32 and for head sizes / lengths the fused kernel does not take.
+//  - gemm_generic: LDS-tiled FMA matrix multiply for any transposition and any shape: the fallback for what
+//    no matrix-core kernel takes (bf16 widths that are no multiple of 8, operands that are not aligned).
+//  - attn_*_generic: one wavefront per query (or key) row with an online softmax (attn_rows.h); exact -inf
+//    masking; for a few tokens, where they are faster, and for head sizes and alignments the tile kernels do not take.
 //  - norm forward/backward (one wavefront per row), deterministic two-stage column
 //    reductions for bias and gain gradients, transpose, add.
 //

@@ -17,8 +17,8 @@
 //   lane).  Loads, LDS reads and all waiting are written out (inline assembly, explicit
 //   `s_waitcnt`): see the kernel for the schedule.
 // gemm_nt128_k -- 128x128 tiles, 4 wavefronts, v_mfma_f32_32x32x16_bf16, register-staged
-//   double-buffered LDS; for operands that gemm_tile_k, which takes all other problems of fewer than
-//   256 tiles of 256x256, cannot load (not 16-byte aligned).
+//   double-buffered LDS; for problems of fewer than 256 tiles of 256x256 that gemm_tile_k cannot load: a k-major
+//   operand that is not 16-byte aligned becomes so in its transposed copy (a K-contiguous one goes to the FMA kernel).
 //
 // The MFMA is issued with the Bt fragment as its first operand, which leaves every lane with 4
 // consecutive columns of one row of C.  Workgroup ids are remapped so that the ids one XCD
