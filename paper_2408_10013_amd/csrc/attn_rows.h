@@ -8,11 +8,6 @@
 namespace ssdt {
 namespace k {
 
-// The tile kernels' workgroups of 256 lie on one axis of the grid, which holds fewer than 2^32 threads: the launch of more is
-// not refused, its upper bits are dropped.  Calls beyond that (short sequences, very many heads) go to the row kernels, whose
-// grid has three axes.
-inline bool one_axis(long workgroups) { return workgroups < (1l << 24); }
-
 struct AttnP {
   int B, A, Sq, Sk, d, mask;
   float scale;

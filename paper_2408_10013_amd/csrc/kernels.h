@@ -67,6 +67,19 @@ inline long nt_copy_ld(int K) { return ((long)K * 2) % 32768 == 0 ? (long)K + 64
 size_t gemm_scratch_bytes(int M, int N, int K, bool transA, bool transB, int dtype);
 size_t gemm_nt_scratch_bytes(int M, int N, int K, bool transA, bool transB, int dtype);  // gemm_mfma_bf16's own need
 
+// An axis of a grid holds fewer than 2^32 threads: the launch of more is not refused, the upper bits of their number are dropped.
+// Whether workgroups of 256 threads fit one axis.  (Attention beyond that, short sequences and very many heads, goes from the tile
+// kernels to the row kernels, whose grid has three axes.)
+inline bool one_axis(long workgroups) { return workgroups < (1l << 24); }
+// The norm backward's workgroups, those of the column sums and those of dx: go(sums, dx_blocks) launches both kinds, or one.
+template <typename F>
+inline void norm_bwd_launch(F go, int chunks, int col_blocks, int rows) {
+  const int dx_blocks = (rows + 3) / 4;
+  if (one_axis((long)chunks * col_blocks + dx_blocks)) return go(chunks, dx_blocks);
+  go(chunks, 0);
+  go(0, dx_blocks);
+}
+
 // Row norm over H.  kind = SSDT_NORM_*.  mean may be null for RMSNorm.
 hipError_t norm_fwd(const void *x, const void *gamma, const void *beta, void *y, float *mean, float *rstd, int rows,
                     int H, float eps, int kind, int dtype, hipStream_t s);

@@ -328,8 +328,11 @@ static hipError_t norm_bwd_t(const T *dy, const T *x, const float *mean, const f
   if (e == hipErrorNotSupported) {
     prof::Scope ps(prof::NORM_BWD, 0, (resid ? 4.0 : 3.0) * rows * H * sizeof(T), s);
     const int col_blocks = (H + 127) / 128;
-    hipLaunchKernelGGL(norm_bwd_k<T>, dim3(chunks * col_blocks + (rows + 3) / 4), dim3(256), 0, s, dy, x, mean, rstd, gamma, resid, dx,
-                       partial, rows, H, kind, (rows + chunks - 1) / chunks, chunks, col_blocks);
+    auto go = [&](int sums, int dx_blocks) {
+      hipLaunchKernelGGL(norm_bwd_k<T>, dim3(sums * col_blocks + dx_blocks), dim3(256), 0, s, dy, x, mean, rstd, gamma, resid, dx,
+                         partial, rows, H, kind, (rows + chunks - 1) / chunks, sums, col_blocks);
+    };
+    norm_bwd_launch(go, chunks, col_blocks, rows);
     e = hipGetLastError();
   }
   if (e != hipSuccess) return e;

@@ -284,11 +284,13 @@ hipError_t norm_bwd_vec(const void *dy, const void *x, const float *mean, const 
   if (!nch || !al16(x) || !al16(dy) || !al16(dx) || !al16(gamma) || (resid && !al16(resid))) return hipErrorNotSupported;
   prof::Scope ps(prof::NORM_BWD, 0, (resid ? 4.0 : 3.0) * rows * H * 2, s);
   const int rpc = (rows + chunks - 1) / chunks, col_blocks = (H + 511) / 512;
-  dim3 grid(chunks * col_blocks + (rows + 3) / 4);
-#define SSDT_GO(N) hipLaunchKernelGGL(norm_bwd_vec_k<N>, grid, dim3(256), 0, s, (const uint16_t *)dy, (const uint16_t *)x, mean, rstd, \
-                                      (const uint16_t *)gamma, (const uint16_t *)resid, (uint16_t *)dx, partial, rows, H, kind, rpc, chunks, col_blocks)
-  switch (nch) { case 1: SSDT_GO(1); break; case 2: SSDT_GO(2); break; case 4: SSDT_GO(4); break; case 8: SSDT_GO(8); break; default: SSDT_GO(16); }
+  auto go = [&](int sums, int dx_blocks) {
+#define SSDT_GO(N) hipLaunchKernelGGL(norm_bwd_vec_k<N>, dim3(sums * col_blocks + dx_blocks), dim3(256), 0, s, (const uint16_t *)dy, (const uint16_t *)x, mean, rstd, \
+                                      (const uint16_t *)gamma, (const uint16_t *)resid, (uint16_t *)dx, partial, rows, H, kind, rpc, sums, col_blocks)
+    switch (nch) { case 1: SSDT_GO(1); break; case 2: SSDT_GO(2); break; case 4: SSDT_GO(4); break; case 8: SSDT_GO(8); break; default: SSDT_GO(16); }
 #undef SSDT_GO
+  };
+  norm_bwd_launch(go, chunks, col_blocks, rows);
   return hipGetLastError();
 }
 
