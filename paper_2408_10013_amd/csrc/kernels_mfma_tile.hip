@@ -4,7 +4,9 @@
 //
 // What bounds such a problem is how many compute units have a tile and how many wavefronts share one, not the matrix
 // pipe, so the tile comes in three sizes, the contraction can be split over workgroups, and the
-// two products of a linear's backward can share a launch (see DISPATCH).
+// two products of a linear's backward can share a launch (see DISPATCH).  Where a compute unit has one or two tiles, a
+// stage is shorter than the trip to memory that fills it: there the stages stand in a ring of three or four instead of two
+// buffers (128 x 1280 x 5120 42 -> 23 us, 1024 x 2048 x 2048 24 -> 17, both products of 256 x 256 -> 1024's backward 12.4 -> 8.9).
 // Operands are read as they are stored, K-contiguous or k-major, as in gemm_km256_k: a stage of 64 k goes to LDS by
 // direct global-to-LDS loads, k-major fragments are fetched with the transposing LDS read.  The loads are buffer
 // loads whose descriptor ends where the operand ends: what lies beyond the last row arrives as zero, so ragged
@@ -14,6 +16,7 @@
 // transposed copies): 4096 x 2048 x 8192 211 -> 137 us, 1024 x 2048 x 2048 45 -> 17, 1024 x 1024 x 8192 150 -> 33.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "dev.h"
 #include "kernels.h"
@@ -86,15 +89,17 @@ struct Side {
     k = k0;
   }
   __device__ __forceinline__ void load(int K, unsigned lds, int wave) {
+    asm volatile("" : "+s"(at), "+s"(left));
     v4i_t rsrc = make_rsrc(at, left);
     // a scalar register written by a vector instruction (readfirstlane) needs five wait states before a vector memory
     // instruction reads it; the compiler does not look into the loads' assembly for that
     asm volatile("s_nop 4" : "+s"(rsrc));
-    const unsigned dst = lds + wave * 1024;
+    unsigned dst = __builtin_amdgcn_readfirstlane(lds + wave * 1024);
+    asm volatile("" : "+s"(dst));  // (the addresses of a ring's loads, computed ahead, would fill the scalar registers)
     // the tail of a K-contiguous row continues in the next row: such chunks are sent out of range
     const bool dead = !KM && k + chunk * 8 >= K;
 #pragma unroll
-    for (int j = 0; j < LJ; ++j) load_lds16(rsrc, dead ? 0x80000000u : voff[j], __builtin_amdgcn_readfirstlane(dst + j * NT * 16));
+    for (int j = 0; j < LJ; ++j) load_lds16(rsrc, dead ? 0x80000000u : voff[j], dst + j * NT * 16);
     at += step;
     left -= step;
     k += kSK;
@@ -129,12 +134,22 @@ __device__ __forceinline__ void store8(uint16_t *dst, const float *v) {
   __builtin_nontemporal_store(q, (u32x4_a8_t *)dst);
 }
 
-// the epilogue on 8 consecutive columns of one row
-__device__ __forceinline__ void tile_epilogue8(const TileP &p, float *v, int m, int n) {
+// the residual or activation input of 8 consecutive columns of one row, as stored (zeros where the epilogue has none)
+__device__ __forceinline__ u32x4_a8_t epilogue_in8(const TileP &p, int m, int n) {
+  if (p.epi == EPI_BIAS_RESID) return *(const u32x4_a8_t *)(p.resid + (long)m * p.ldr + n);
+  if (p.epi == EPI_ACTBWD) return *(const u32x4_a8_t *)(p.aux + (long)m * p.ldc + n);
+  return u32x4_a8_t{0, 0, 0, 0};
+}
+__device__ __forceinline__ u32x4_a8_t bias8(const TileP &p, int n) {
+  if (p.epi != EPI_NONE && p.epi != EPI_ACTBWD && p.bias) return *(const u32x4_a8_t *)(p.bias + n);
+  return u32x4_a8_t{0, 0, 0, 0};
+}
+// the epilogue on 8 consecutive columns of one row, given the two above
+__device__ __forceinline__ void tile_epilogue8(const TileP &p, float *v, int m, int n, u32x4_a8_t bias, u32x4_a8_t in) {
   const long o = (long)m * p.ldc + n;
   if (p.epi != EPI_NONE && p.epi != EPI_ACTBWD && p.bias) {
     float b[8];
-    load8(p.bias + n, b);
+    unpack8f(make_uint4(bias.x, bias.y, bias.z, bias.w), b);
 #pragma unroll
     for (int t = 0; t < 8; ++t) v[t] += b[t];
   }
@@ -147,12 +162,12 @@ __device__ __forceinline__ void tile_epilogue8(const TileP &p, float *v, int m, 
   }
   if (p.epi == EPI_BIAS_RESID) {
     float r[8];
-    load8(p.resid + (long)m * p.ldr + n, r);
+    unpack8f(make_uint4(in.x, in.y, in.z, in.w), r);
 #pragma unroll
     for (int t = 0; t < 8; ++t) v[t] += r[t];
   } else if (p.epi == EPI_ACTBWD) {
     float u[8];
-    load8(p.aux + o, u);
+    unpack8f(make_uint4(in.x, in.y, in.z, in.w), u);
 #pragma unroll
     for (int t = 0; t < 8; ++t) v[t] *= p.act == SSDT_ACT_GELU ? gelu_grad_f(u[t]) : (u[t] > 0.f ? 1.f : 0.f);
   }
@@ -161,7 +176,8 @@ __device__ __forceinline__ void tile_epilogue8(const TileP &p, float *v, int m, 
 
 // One tile: workgroup `bid` of the problem's tiles_m * tiles_n * splits (tiles of a split after each other); 256 threads,
 // 2 x 2 wavefronts.
-template <int BM, int BN, bool AKM, bool BKM>
+// R: stages in the ring.  The kernels differ in nothing but tile, ring and speed: every output is the same sum in the same order.
+template <int BM, int BN, int R, bool AKM, bool BKM>
 __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *smem) {
   constexpr int NT = 256, WGN = 2, WTM = BM / 2, WTN = BN / 2, TM = WTM / 16, TN = WTN / 16;
   typedef Side<BM, AKM, NT> SA;
@@ -196,7 +212,8 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
 
   // A stage is two 32-wide steps.  The fragments of a step are read while the MFMAs of the step before run; the reads
   // of a stage's second step are the last of that stage, so its one barrier sits between the two steps: behind it the
-  // next stage is read and the stage after next is loaded over this one.
+  // next stage is read and the stage R further on is loaded over this one.  (Both steps of the next stage read behind the
+  // barrier, into a second set of registers: 10 % slower.)
   sa.start(p.A, p.lda, m0, p.M, s0 * kSK, p.K);
   sb.start(p.B, p.ldb, n0, p.N, s0 * kSK, p.K);
   bf16x8_t af[2][TM], bf[2][TN];
@@ -220,32 +237,63 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
       for (int j = 0; j < TN; ++j) accs[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[step][j], ones.v, accs[j], 0, 0, 0);
     }
   };
-  auto stage = [&](int st, int buf) {
-    read_step(buf, 1);
-    mfma_step(0);
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  constexpr int L = SA::LJ + SB::LJ;  // a thread's loads per stage
+  // What the epilogue reads is requested at the start of the last stage, when no load of a stage is on its way any more: read
+  // row by row between the stores, every pass was a round trip to memory (4096 x 2048 x 2048 with a residual 50 -> 44 us).
+  constexpr int LPR = WTN / 8, RPP = 64 / LPR, PASSES = 32 / RPP;
+  const int c8 = (lane % LPR) * 8, n = n0 + wn * WTN + c8;
+  u32x4_a8_t ein[TM / 2][PASSES], ebias = {0, 0, 0, 0};
+  auto fetch = [&]() {
+    if (n < p.N && p.splits == 1) ebias = bias8(p, n);
+#pragma unroll
+    for (int I = 0; I < TM / 2; ++I)
+#pragma unroll
+      for (int pass = 0; pass < PASSES; ++pass) {
+        const int m = m0 + wm * WTM + I * 32 + pass * RPP + lane / LPR;
+        ein[I][pass] = u32x4_a8_t{0, 0, 0, 0};
+        if (m < p.M && n < p.N && p.splits == 1) ein[I][pass] = epilogue_in8(p, m, n);
+      }
+  };
+  // waits for every LDS read and for all of the loads on their way but those of the last `later` stages, CAP at most
+  auto wait_stages = [&](int later, auto cap) {
+    constexpr int CAP = decltype(cap)::value;
+    if (CAP >= 3 && later >= 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(3 * L) : "memory");
+    else if (CAP >= 2 && later >= 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * L) : "memory");
+    else if (CAP >= 1 && later >= 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(L) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (st + 2 < nk) load_stage(buf);
-    read_step(buf ^ 1, 0);  // (behind the last stage: whatever is there, not used)
+  };
+  typedef std::integral_constant<int, R - 1> InFlight;
+  typedef std::integral_constant<int, R - 2> InFlight2;
+  // INNER: the stage after the ring exists
+  auto stage = [&](int st, int buf, auto inner) {
+    constexpr bool INNER = decltype(inner)::value;
+    if (!INNER && st + 1 == nk) fetch();
+    read_step(buf, 1);
+    mfma_step(0);
+    if (INNER || st + 1 < nk) {
+      wait_stages(INNER ? R : nk - 2 - st, InFlight2());
+      if (INNER || st + R < nk) load_stage(buf);
+      read_step((buf + 1) % R, 0);
+    }
     mfma_step(1);
   };
-  load_stage(0);
-  if (nk > 1) {
-    load_stage(1);
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(SA::LJ + SB::LJ) : "memory");
-  } else {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  }
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+    if (i < nk) load_stage(i);
+  wait_stages(nk - 1, InFlight());
   read_step(0, 0);
   int st = 0;
-  for (; st + 1 < nk; st += 2) {
-    stage(st, 0);
-    stage(st + 1, 1);
+  for (; st + 2 * R - 1 < nk; st += R) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) stage(st + i, i, std::true_type());
   }
-  if (st < nk) stage(st, 0);
+  for (; st < nk; st += R) {
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+      if (st + i < nk) stage(st + i, i, std::false_type());
+  }
   const int lr = lane & 15, lq = lane >> 4;
   if (AKM && BKM && sum && lr == 0) {  // this lane: columns j*16 + lq*4 + 0..3
 #pragma unroll
@@ -269,9 +317,8 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
   // epilogue through LDS, 32 rows of the wavefront's part at a time: lane l of block (i, j) holds row i*16 + (l & 15),
   // columns j*16 + (l >> 4)*4 + 0..3; read back row by row so that an access is 16 bytes and rows are contiguous
   __syncthreads();
-  constexpr int LD = WTN + 4, LPR = WTN / 8, RPP = 64 / LPR;
+  constexpr int LD = WTN + 4;
   float *stg = (float *)smem + wave * (32 * LD);
-  const int c8 = (lane % LPR) * 8, n = n0 + wn * WTN + c8;
 #pragma unroll
   for (int I = 0; I < TM / 2; ++I) {
 #pragma unroll
@@ -282,7 +329,7 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
         *(float4 *)(stg + (il * 16 + lr) * LD + j * 16 + lq * 4) = make_float4(a[0], a[1], a[2], a[3]);
       }
 #pragma unroll
-    for (int pass = 0; pass < 32 / RPP; ++pass) {
+    for (int pass = 0; pass < PASSES; ++pass) {
       const int row = pass * RPP + lane / LPR, m = m0 + wm * WTM + I * 32 + row;
       const float4 lo = *(const float4 *)(stg + row * LD + c8), hi = *(const float4 *)(stg + row * LD + c8 + 4);
       if (m >= p.M || n >= p.N) continue;
@@ -292,29 +339,29 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
         *(float4 *)(o + 4) = hi;
       } else {
         float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-        tile_epilogue8(p, v, m, n);
+        tile_epilogue8(p, v, m, n, ebias, ein[I][pass]);
       }
     }
   }
 }
 
-template <int BM, int BN, bool AKM, bool BKM>
+template <int BM, int BN, int R, bool AKM, bool BKM>
 __global__ __launch_bounds__(256, 2) void gemm_tile_k(TileP p) {
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
-  tile_body<BM, BN, AKM, BKM>(p, blockIdx.x, smem);
+  tile_body<BM, BN, R, AKM, BKM>(p, blockIdx.x, smem);
 }
 
 // The two products of a linear's backward in one launch: the weight gradient (both operands k-major) and the input
 // gradient (both K-contiguous) read the same dY and do not depend on each other.  Launched one after the other, the
 // second waits until the last workgroup of the first has finished; here the one with the longer tiles goes first and the
 // other fills the machine behind it.
-template <int BM, int BN>
+template <int BM, int BN, int R>
 __global__ __launch_bounds__(256, 2) void gemm_tile_pair_k(TileP w, TileP d, int first, int w_first) {
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   const int bid = blockIdx.x;
   const bool head = bid < first;
-  if (head == (w_first != 0)) tile_body<BM, BN, true, true>(w, head ? bid : bid - first, smem);
-  else tile_body<BM, BN, false, false>(d, head ? bid : bid - first, smem);
+  if (head == (w_first != 0)) tile_body<BM, BN, R, true, true>(w, head ? bid : bid - first, smem);
+  else tile_body<BM, BN, R, false, false>(d, head ? bid : bid - first, smem);
 }
 
 // Second half of a split product: adds the partial products in the order of the splits and applies the epilogue;
@@ -346,11 +393,11 @@ __global__ __launch_bounds__(256) void tile_reduce_k(TileP p) {
     v[0] += lo.x; v[1] += lo.y; v[2] += lo.z; v[3] += lo.w;
     v[4] += hi.x; v[5] += hi.y; v[6] += hi.z; v[7] += hi.w;
   }
-  tile_epilogue8(p, v, m, n);
+  tile_epilogue8(p, v, m, n, bias8(p, n), epilogue_in8(p, m, n));
 }
 
-struct TileCfg { int bm, bn; };
-static const TileCfg kCfg[] = {{128, 128}, {64, 128}, {64, 64}};
+struct TileCfg { int bm, bn, ring; };
+static const TileCfg kCfg[] = {{128, 128, 2}, {64, 128, 2}, {64, 64, 2}, {64, 128, 3}, {64, 64, 3}, {128, 128, 4}};
 int g_tile_cfg = -1, g_tile_splits = 0;  // test hooks: >= 0 pins the tile, > 0 the number of splits
 
 static hipError_t launch_reduce(const TileP &p, hipStream_t s) {
@@ -361,43 +408,46 @@ static hipError_t launch_reduce(const TileP &p, hipStream_t s) {
 }
 static unsigned blocks_of(const TileP &p) { return (unsigned)(p.tiles_m * p.tiles_n * p.splits); }
 
-template <int BM, int BN>
+template <int BM, int BN, int R>
 static constexpr size_t smem_of() {
-  constexpr size_t stg = (size_t)4 * 32 * (BN / 2 + 4) * 4, stages = (size_t)2 * (BM + BN) * kSK * 2;
+  constexpr size_t stg = (size_t)4 * 32 * (BN / 2 + 4) * 4, stages = (size_t)R * (BM + BN) * kSK * 2;
   return stg > stages ? stg : stages;
 }
-template <int BM, int BN, bool AKM, bool BKM>
+template <int BM, int BN, int R, bool AKM, bool BKM>
 static hipError_t launch_tile(const TileP &p, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_k<BM, BN, AKM, BKM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN>());
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_k<BM, BN, R, AKM, BKM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN, R>());
     if (e != hipSuccess) return e;
     attr_set = true;
   }
   prof::Scope ps(prof::GEMM_MFMA_TILE, 2.0 * p.M * p.N * p.K, 0, s);
-  hipLaunchKernelGGL((gemm_tile_k<BM, BN, AKM, BKM>), dim3(blocks_of(p)), dim3(256), (smem_of<BM, BN>()), s, p);
+  hipLaunchKernelGGL((gemm_tile_k<BM, BN, R, AKM, BKM>), dim3(blocks_of(p)), dim3(256), (smem_of<BM, BN, R>()), s, p);
   hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : launch_reduce(p, s);
 }
 template <bool AKM, bool BKM>
 static hipError_t launch_cfg(int cfg, const TileP &p, hipStream_t s) {
   switch (cfg) {
-    case 0: return launch_tile<128, 128, AKM, BKM>(p, s);
-    case 1: return launch_tile<64, 128, AKM, BKM>(p, s);
-    default: return launch_tile<64, 64, AKM, BKM>(p, s);
+    case 0: return launch_tile<128, 128, 2, AKM, BKM>(p, s);
+    case 1: return launch_tile<64, 128, 2, AKM, BKM>(p, s);
+    case 2: return launch_tile<64, 64, 2, AKM, BKM>(p, s);
+    case 3: return launch_tile<64, 128, 3, AKM, BKM>(p, s);
+    case 4: return launch_tile<64, 64, 3, AKM, BKM>(p, s);
+    default: return launch_tile<128, 128, 4, AKM, BKM>(p, s);
   }
 }
-template <int BM, int BN>
+template <int BM, int BN, int R>
 static hipError_t launch_pair(const TileP &w, const TileP &d, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_pair_k<BM, BN>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN>());
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_pair_k<BM, BN, R>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN, R>());
     if (e != hipSuccess) return e;
     attr_set = true;
   }
   prof::Scope ps(prof::GEMM_MFMA_TILE, 2.0 * w.M * w.N * w.K + 2.0 * d.M * d.N * d.K, 0, s);
   const bool w_first = w.stages_per_split >= d.stages_per_split;
-  hipLaunchKernelGGL((gemm_tile_pair_k<BM, BN>), dim3(blocks_of(w) + blocks_of(d)), dim3(256), (smem_of<BM, BN>()), s, w, d,
+  hipLaunchKernelGGL((gemm_tile_pair_k<BM, BN, R>), dim3(blocks_of(w) + blocks_of(d)), dim3(256), (smem_of<BM, BN, R>()), s, w, d,
                      (int)(w_first ? blocks_of(w) : blocks_of(d)), w_first ? 1 : 0);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = launch_reduce(w, s);
@@ -411,22 +461,28 @@ bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
   return !(transA && transB);  // (the layer has no such product)
 }
 
-// DISPATCH.  Predicted time of a problem in microseconds, from what the tiles were measured to take (MI355X, the layer's
-// shapes).  A workgroup's stage of 64 k takes a + b n when n workgroups share a compute unit, and never less than c n:
-//   128 x 128: 0.75 us alone, 1.07 us two together (1.0 PFLOP/s on 4096 x 2048 x 8192, 512 tiles);
-//    64 x 128: 0.58 alone, 0.66 two together, 0.36 each from three on: the better one where it fills a machine that
-//              128 x 128 tiles leave half empty (2048 x 2048 x 4096: 45 against 50 us);
-//    64 x 64 : 0.45 alone, 0.22 each from four on: for the smallest (256 x 768 x 256: 4.2 against 5.5 and 7.7 us).
+// DISPATCH.  Predicted time of a problem in microseconds, fitted to what the tiles were measured to take (MI355X, 78 products
+// of a layer's forms with 128 to 4096 rows; the choice is within 4 % of the best tile for nine in ten of them).  A launch
+// takes 2.5 us and e for each tile of a compute unit, and a workgroup's stage of 64 k takes a + b n when n workgroups
+// share a unit, never less than c n:
+//   128 x 128, ring of 2: 0.8 us alone, 1.07 two together (1.0 PFLOP/s on 4096 x 2048 x 8192, 512 tiles);
+//              ring of 4: 0.6 alone, and alone it is: for 192 tiles and long K (1024 x 3072 x 8192: 77 us against 106);
+//    64 x 128, ring of 2: 0.57 alone, 0.36 each from three on: where three share a unit;
+//              ring of 3: 0.4 alone, 0.6 two together (2331 x 1024 x 4096, 296 tiles: 39 us against 52 and, 128 x 128, 44);
+//    64 x 64,  ring of 2: 0.22 each from four on;
+//              ring of 3: 0.3 alone: for the smallest (256 x 256 x 1024: 7.6 us against 10.5; 128 x 1280 x 5120: 23 against 40).
 // Splitting the contraction costs a second launch and the partial products' way out and back at about 6 TB/s.
-struct TileCost { double a, b, c; int fit; };  // fit: workgroups that share a compute unit at most
-static const TileCost kCost[] = {{0.43, 0.32, 0.535, 2}, {0.50, 0.08, 0.36, 3}, {0.37, 0.08, 0.22, 5}};
+struct TileCost { double a, b, c, e; int fit; };  // fit: workgroups that share a compute unit at most
+static const TileCost kCost[] = {{0.61, 0.19, 0.545, 1.5, 2}, {0.405, 0.17, 0.335, 1.0, 3}, {0.37, 0.11, 0.21, 0.5, 5},
+                                 {0.27, 0.15, 0.345, 1.4, 2}, {0.26, 0.04, 0.23, 0.75, 3}, {0.055, 0.615, 0.67, 2.8, 1}};
+constexpr int kCfgs = sizeof kCfg / sizeof kCfg[0];
 constexpr int kMaxSplits = 8;
 static int stages_of(int K) { return (K + kSK - 1) / kSK; }
 static long tiles_of(int M, int N, int cfg) { return (long)((M + kCfg[cfg].bm - 1) / kCfg[cfg].bm) * ((N + kCfg[cfg].bn - 1) / kCfg[cfg].bn); }
 static double reduce_cost(int M, int N, int splits) { return splits > 1 ? 3.0 + 8.0 * splits * M * N / 6e6 : 0.0; }
 static double tile_cost(int M, int N, int K, int cfg, int splits) {
   const double n = (double)((tiles_of(M, N, cfg) * splits + 255) / 256), t = std::max(kCost[cfg].a + kCost[cfg].b * n, kCost[cfg].c * n);
-  return 3.0 + t * ((stages_of(K) + splits - 1) / splits) + reduce_cost(M, N, splits);
+  return 2.5 + t * ((stages_of(K) + splits - 1) / splits) + kCost[cfg].e * n + reduce_cost(M, N, splits);
 }
 static size_t split_bytes(int M, int N, int splits) { return splits > 1 ? (size_t)splits * ((size_t)M + 1) * N * 4 : 0; }
 static bool split_ok(int K, int splits) { return splits == 1 || splits * 4 <= stages_of(K); }
@@ -434,7 +490,7 @@ static bool split_ok(int K, int splits) { return splits == 1 || splits * 4 <= st
 // The choice for a problem given `scratch` bytes for partial products; returns its predicted time.
 static double tile_plan(int M, int N, int K, size_t scratch, int *cfg, int *splits) {
   double best = 1e30;
-  for (int c = 0; c < 3; ++c)
+  for (int c = 0; c < kCfgs; ++c)
     for (int sp = 1; sp <= kMaxSplits && split_ok(K, sp); sp *= 2) {
       if (split_bytes(M, N, sp) > scratch) break;
       const double t = tile_cost(M, N, K, c, sp);
@@ -451,7 +507,7 @@ static size_t half_of(size_t scratch) { return scratch / 2 / 256 * 256; }
 static double pair_plan(const Shape &w, const Shape &d, size_t scratch, PairPlan *out) {
   const size_t half = half_of(scratch);
   double best = 1e30;
-  for (int c = 0; c < 3; ++c)
+  for (int c = 0; c < kCfgs; ++c)
     for (int sw = 1; sw <= kMaxSplits && split_ok(w.K, sw); sw *= 2) {
       if (split_bytes(w.M, w.N, sw) > half) break;
       for (int sd = 1; sd <= kMaxSplits && split_ok(d.K, sd); sd *= 2) {
@@ -459,8 +515,8 @@ static double pair_plan(const Shape &w, const Shape &d, size_t scratch, PairPlan
         const double nw = (double)tiles_of(w.M, w.N, c) * sw, nd = (double)tiles_of(d.M, d.N, c) * sd;
         const double lw = (stages_of(w.K) + sw - 1) / sw, ld = (stages_of(d.K) + sd - 1) / sd, longest = std::max(lw, ld);
         const double n = std::min((double)kCost[c].fit, std::ceil((nw + nd) / 256.0));
-        const double work = (nw * lw + nd * ld) / 256.0 * kCost[c].c + 0.25 * std::min(lw, ld) * kCost[c].a;
-        const double t = 3.0 + std::max(work, longest * (kCost[c].a + kCost[c].b * n)) + reduce_cost(w.M, w.N, sw) + reduce_cost(d.M, d.N, sd);
+        const double work = ((nw * lw + nd * ld) * kCost[c].c + (nw + nd) * kCost[c].e) / 256.0 + 0.25 * std::min(lw, ld) * (kCost[c].a + kCost[c].b);
+        const double t = 2.5 + std::max(work, longest * (kCost[c].a + kCost[c].b * n) + kCost[c].e) + reduce_cost(w.M, w.N, sw) + reduce_cost(d.M, d.N, sd);
         if (t < best * 0.98) { best = t; out->cfg = c; out->sw = sw; out->sd = sd; }
       }
     }
@@ -567,9 +623,12 @@ hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, hipStream_t s) {
   choose(&pw, pp.cfg, pp.sw, (float *)w.scratch);
   choose(&pd, pp.cfg, pp.sd, (float *)((char *)w.scratch + half_of(scratch)));
   switch (pp.cfg) {
-    case 0: return launch_pair<128, 128>(pw, pd, s);
-    case 1: return launch_pair<64, 128>(pw, pd, s);
-    default: return launch_pair<64, 64>(pw, pd, s);
+    case 0: return launch_pair<128, 128, 2>(pw, pd, s);
+    case 1: return launch_pair<64, 128, 2>(pw, pd, s);
+    case 2: return launch_pair<64, 64, 2>(pw, pd, s);
+    case 3: return launch_pair<64, 128, 3>(pw, pd, s);
+    case 4: return launch_pair<64, 64, 3>(pw, pd, s);
+    default: return launch_pair<128, 128, 4>(pw, pd, s);
   }
 }
 
