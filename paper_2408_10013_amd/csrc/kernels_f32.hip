@@ -1,6 +1,7 @@
 // fp32 GEMM on the matrix cores (v_mfma_f32_16x16x4_f32), any shape, any transposition, any alignment.
 //
-// bf16 storage, forward form only: for products whose order of additions is kept (Gemm::ordered).
+// bf16 storage, forward form only: for products whose order of additions is kept (Gemm::ordered), and for widths and
+// alignments that the bf16 kernels do not take.
 // The instruction multiplies and adds in fp32 with one rounding per step, k ascending (checked against a chain of fmaf on
 // the host), and a tile's contraction is never split, so every output is the same sum in the same order, and the same
 // bits, as a thread of the FMA kernel this replaces would produce.  That kernel was bound by its LDS reads (two bytes

@@ -135,10 +135,8 @@ hipError_t gemm(const Gemm &g, hipStream_t s) {
     if (e != hipErrorNotSupported) return e;
   }
   if (g.colsum) return hipErrorNotSupported;
-  if (g.dtype == SSDT_F32 || ordered) {
-    hipError_t e = gemm_f32(g, s);
-    if (e != hipErrorNotSupported) return e;
-  }
+  hipError_t e = gemm_f32(g, s);  // fp32, and bf16 forward products of any width and alignment
+  if (e != hipErrorNotSupported) return e;
   return gemm_generic(g, s);
 }
 
