@@ -159,6 +159,27 @@ def test_every_ring_of_stages(pin, tile, size):
         check_against_oracle(l, case, run_single_layer(l, case, offload=False, fetch=False), hp.TOL["bf16"])
 
 
+# stages of 64 k (tile 32) or 32 (tile 64): 1 and 2 of either, as many as the ring holds, and more; widths that end inside a tile
+# and inside a stage; the middle size ends a row of k inside a 64-byte unit
+@pytest.mark.parametrize("size", [dict(B=3, S=9, H=24, A=1, F=52), dict(B=3, S=37, H=132, A=2, F=100), dict(B=2, S=185, H=260, A=5, F=516)],
+                         ids=["1", "3", "9"])
+@pytest.mark.parametrize("tile,ring", [(32, 2), (32, 3), (64, 3)])
+def test_every_ring_of_stages_f32(pin, tile, ring, size):
+    """Direct loads, and the same with operands that start at 4 bytes, which go through registers: the same bits."""
+    l = runner.Layer(dtype="f32", **dict(GPT, **size))
+    case = hp.make_layer_case(l, 8470 + tile + ring, bias_std=0.05)
+    pin("g_f32_tile", tile)
+    pin("g_f32_ring", ring)
+    res = run_backward(l, case)
+    check_against_oracle(l, case, res, hp.TOL["f32"])
+    kept = {k: v.clone() for k, v in res["grads"].items()}
+    l.w = {k: shifted(v, 1) if k.startswith("w_") else v for k, v in l.w.items()}
+    l.wstruct = sb.make_weights({k: v.data_ptr() for k, v in l.w.items()})
+    other = run_backward(l, case)
+    assert np.array_equal(res["y"], other["y"]) and torch.equal(res["dx"], other["dx"])
+    assert all(torch.equal(kept[k], other["grads"][k]) for k in kept)
+
+
 @pytest.mark.parametrize("name", ["d12", "d64"])
 def test_relu_products_with_the_larger_tile(pin, name):
     pin("g_f32_tile", 64)
