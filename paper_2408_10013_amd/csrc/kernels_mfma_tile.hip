@@ -77,30 +77,36 @@ struct Side {
       }
     }
   }
-  // where the next stage starts, bytes from there to the end of the operand, the k it starts at
+  // Where the next stage starts, units of 16 bytes from there to the end of the operand (everything is a whole number of them;
+  // prepare() checks that 31 bits hold it) and from stage to stage, the k it starts at.
   uint64_t at;
-  long left, step;
-  int k;
+  int left, step, k;
   // `ext` = the operand's extent in its own dimension, r0 / k0 = the tile's origin
   __device__ __forceinline__ void start(const uint16_t *base, long ld, int r0, int ext, int k0, int K) {
     at = (uint64_t)(uintptr_t)(KM ? base + (long)k0 * ld + r0 : base + (long)r0 * ld + k0);
-    left = KM ? ((long)(K - 1 - k0) * ld + ext - r0) * 2 : ((long)(ext - 1 - r0) * ld + K - k0) * 2;
-    step = KM ? (long)kSK * ld * 2 : (long)kSK * 2;
+    left = (int)((KM ? (long)(K - 1 - k0) * ld + ext - r0 : (long)(ext - 1 - r0) * ld + K - k0) / 8);
+    step = KM ? kSK / 8 * (int)ld : kSK / 8;
     k = k0;
   }
-  __device__ __forceinline__ void load(int K, unsigned lds, int wave) {
-    asm volatile("" : "+s"(at), "+s"(left));
-    v4i_t rsrc = make_rsrc(at, left);
+  // TAIL: the stage may be the last one.  (Scalar instructions count here: a small problem is one wavefront per SIMD, bound by
+  // what it issues.  With the descriptor's extent computed in 64 bits a stage took 30 to 50 ns longer.)
+  __device__ __forceinline__ void load(int K, unsigned lds, int wave, bool tail) {
+    unsigned dst = __builtin_amdgcn_readfirstlane(lds + wave * 1024);
+    asm volatile("" : "+s"(at), "+s"(left), "+s"(dst));  // (addresses computed ahead would fill the scalar registers)
+    v4i_t rsrc;
+    rsrc[0] = (int)(unsigned)at;
+    rsrc[1] = (int)(unsigned)(at >> 32) & 0xffff;
+    const int rest = left & ~(left >> 31);
+    rsrc[2] = (rest >> 27) ? 0x7fffffff : rest << 4;  // (2^31 is out of range)
+    rsrc[3] = 0x00020000;
     // a scalar register written by a vector instruction (readfirstlane) needs five wait states before a vector memory
     // instruction reads it; the compiler does not look into the loads' assembly for that
     asm volatile("s_nop 4" : "+s"(rsrc));
-    unsigned dst = __builtin_amdgcn_readfirstlane(lds + wave * 1024);
-    asm volatile("" : "+s"(dst));  // (the addresses of a ring's loads, computed ahead, would fill the scalar registers)
     // the tail of a K-contiguous row continues in the next row: such chunks are sent out of range
-    const bool dead = !KM && k + chunk * 8 >= K;
+    const bool dead = !KM && tail && k + chunk * 8 >= K;
 #pragma unroll
     for (int j = 0; j < LJ; ++j) load_lds16(rsrc, dead ? 0x80000000u : voff[j], dst + j * NT * 16);
-    at += step;
+    at += 16l * step;
     left -= step;
     k += kSK;
   }
@@ -217,9 +223,9 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
   sa.start(p.A, p.lda, m0, p.M, s0 * kSK, p.K);
   sb.start(p.B, p.ldb, n0, p.N, s0 * kSK, p.K);
   bf16x8_t af[2][TM], bf[2][TN];
-  auto load_stage = [&](int buf) {
-    sa.load(p.K, lds0 + buf * kStage, wave);
-    sb.load(p.K, lds0 + buf * kStage + SA::kBytes, wave);
+  auto load_stage = [&](int buf, bool tail) {
+    sa.load(p.K, lds0 + buf * kStage, wave, tail);
+    sb.load(p.K, lds0 + buf * kStage + SA::kBytes, wave, tail);
   };
   auto read_step = [&](int buf, int step) {
 #pragma unroll
@@ -266,7 +272,7 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
   };
   typedef std::integral_constant<int, R - 1> InFlight;
   typedef std::integral_constant<int, R - 2> InFlight2;
-  // INNER: the stage after the ring exists
+  // INNER: stage st + R exists and is not the last
   auto stage = [&](int st, int buf, auto inner) {
     constexpr bool INNER = decltype(inner)::value;
     if (!INNER && st + 1 == nk) fetch();
@@ -274,18 +280,22 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
     mfma_step(0);
     if (INNER || st + 1 < nk) {
       wait_stages(INNER ? R : nk - 2 - st, InFlight2());
-      if (INNER || st + R < nk) load_stage(buf);
+      // (ring of four, one workgroup per compute unit: reads before loads, 128 x 1280 x 5120 49 -> 44 us; elsewhere the
+      // compiler's own order is the better one)
+      if (R < 4 && (INNER || st + R < nk)) load_stage(buf, !INNER);
       read_step((buf + 1) % R, 0);
+      if (R == 4) __builtin_amdgcn_sched_barrier(0);
+      if (R == 4 && (INNER || st + R < nk)) load_stage(buf, !INNER);
     }
     mfma_step(1);
   };
 #pragma unroll
   for (int i = 0; i < R; ++i)
-    if (i < nk) load_stage(i);
+    if (i < nk) load_stage(i, true);
   wait_stages(nk - 1, InFlight());
   read_step(0, 0);
   int st = 0;
-  for (; st + 2 * R - 1 < nk; st += R) {
+  for (; st + 2 * R < nk; st += R) {
 #pragma unroll
     for (int i = 0; i < R; ++i) stage(st + i, i, std::true_type());
   }
@@ -574,6 +584,9 @@ static hipError_t prepare(const Gemm &g, TileP *p) {
   if (g.ldc % 4 || !al8(g.C) || (g.C2 && !al8(g.C2)) || (g.bias && !al8(g.bias)) || (g.aux && !al8(g.aux)) ||
       (g.resid && (!al8(g.resid) || g.ldr % 4)))
     return hipErrorNotSupported;
+  const long ea = akm ? (long)(g.K - 1) * g.lda + g.M : (long)(g.M - 1) * g.lda + g.K;
+  const long eb = bkm ? (long)(g.K - 1) * g.ldb + g.N : (long)(g.N - 1) * g.ldb + g.K;
+  if ((ea | eb) >> 34) return hipErrorNotSupported;  // (Side::left)
   if (g.epi == EPI_BIAS_ACT && !g.C2) return hipErrorInvalidValue;
   if (g.epi == EPI_BIAS_RESID && !g.resid) return hipErrorInvalidValue;
   if (g.epi == EPI_ACTBWD && !g.aux) return hipErrorInvalidValue;
