@@ -47,7 +47,8 @@ struct Gemm {
   void *scratch = nullptr;      // optional: room for transposed copies of operands, or for partial products (bf16)
   size_t scratch_bytes = 0;
   bool split = false;           // the contraction may be split over workgroups (another order of the fp32 additions)
-  // bf16, every size that is not whole tiles of 128 x 128 x 64: fp32 additions with k ascending, whatever kernel runs.
+  // bf16, every size that is not whole tiles of 128 x 128 x 64: fp32 additions with k ascending, whatever kernel runs (at whole
+  // tiles: in the one order that the tiles with 64 k a stage and the 256 x 256 kernels have).
   // For the forward products of layers with ReLU up to the one that sums the pre-activation.  A pre-activation near zero
   // changes sides with the last bit of what it was summed from, and with it a whole column of the gradients.  A product
   // whose result is rounded to bf16 on the way there makes a difference of 2^-24 into one of 2^-9 wherever a rounding tips

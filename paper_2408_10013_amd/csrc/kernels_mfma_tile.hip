@@ -12,6 +12,8 @@
 // loads whose descriptor ends where the operand ends: what lies beyond the last row arrives as zero, so ragged
 // extents need no second code path and no masks, except the tail of a K-contiguous row (see the loader).
 //
+// For the smallest problems the four wavefronts of a workgroup stand side by side along k instead (kwave_body).
+//
 // Against the form this replaces (128 x 128 tiles, register-staged, operands brought to the K-contiguous form by
 // transposed copies): 4096 x 2048 x 8192 211 -> 137 us, 1024 x 2048 x 2048 45 -> 17, 1024 x 1024 x 8192 150 -> 33.
 #include <algorithm>
@@ -45,7 +47,7 @@ struct TileP {
   int colsum_acc;
 };
 
-constexpr int kSK = 64;  // k per stage
+constexpr int kSK = 64;  // k per stage (SK below: 64, or 128 where the wavefronts share a stage's k)
 
 // One operand's side of the loader and of the fragment reads.  ROWS: the tile's extent in this operand's own
 // dimension; KM: stored k-major.
@@ -54,27 +56,24 @@ constexpr int kSK = 64;  // k per stage
 //   rows of 256 bytes and more; with rows of 128 bytes the row's parity already picks the half of the 64 banks and the key
 //   is ((k >> 1) & 1) | ((k >> 3) & 1) << 1.  Either way the eight k-rows {0..3, 8..11} that 32 lanes of a transposing read
 //   touch at one unit lie in eight different groups of eight banks.
-template <int ROWS, bool KM, int NT>
+//   A stage of 128 k: K-contiguous rows have 256 bytes, chunk c of row r at c ^ (r & 15); k-major rows of 64 bytes, four of
+//   which make up the 64 banks, have key (k >> 3) & 1.
+template <int ROWS, bool KM, int NT, int SK>
 struct Side {
-  static constexpr int LJ = ROWS * 8 / NT, CPR = ROWS / 8;
-  static constexpr unsigned kBytes = ROWS * kSK * 2;
-  static __device__ __forceinline__ int key(int k) {
-    return ROWS >= 128 ? ((k & 3) | (((k >> 3) & 1) << 2)) : (((k >> 1) & 1) | (((k >> 3) & 1) << 1));
+  static constexpr int LJ = ROWS * SK / 8 / NT, CPR = (KM ? ROWS : SK) / 8;
+  static constexpr unsigned kBytes = ROWS * SK * 2;
+  static __device__ __forceinline__ int key(int i) {
+    if (!KM) return SK == 128 ? i & 15 : (i >> 1) & 7;
+    return ROWS >= 128 ? ((i & 3) | (((i >> 3) & 1) << 2)) : ROWS >= 64 ? (((i >> 1) & 1) | (((i >> 3) & 1) << 1)) : ((i >> 3) & 1);
   }
   unsigned voff[LJ];
-  int chunk;  // K-contiguous: this thread's 8-wide chunk of the stage (the same for every j: NT / 8 is a multiple of 16)
+  int chunk;  // K-contiguous: this thread's 8-wide chunk of the stage (the same for every j: NT / CPR is a multiple of 16)
   __device__ __forceinline__ void init(int tid, long ld) {
 #pragma unroll
     for (int j = 0; j < LJ; ++j) {
-      const int q = j * NT + tid;
-      if (KM) {
-        const int kr = q / CPR, pos = q % CPR;
-        voff[j] = (unsigned)(kr * (int)ld) * 2u + (unsigned)((((pos >> 1) ^ key(kr)) << 1) | (pos & 1)) * 16u;
-      } else {
-        const int row = q >> 3, c = (q & 7) ^ ((row >> 1) & 7);
-        voff[j] = (unsigned)(row * (int)ld + c * 8) * 2u;
-        chunk = c;
-      }
+      const int q = j * NT + tid, row = q / CPR, pos = q % CPR;
+      chunk = KM ? (((pos >> 1) ^ key(row)) << 1) | (pos & 1) : pos ^ key(row);
+      voff[j] = (unsigned)(row * (int)ld + chunk * 8) * 2u;
     }
   }
   // Where the next stage starts, units of 16 bytes from there to the end of the operand (everything is a whole number of them;
@@ -85,7 +84,7 @@ struct Side {
   __device__ __forceinline__ void start(const uint16_t *base, long ld, int r0, int ext, int k0, int K) {
     at = (uint64_t)(uintptr_t)(KM ? base + (long)k0 * ld + r0 : base + (long)r0 * ld + k0);
     left = (int)((KM ? (long)(K - 1 - k0) * ld + ext - r0 : (long)(ext - 1 - r0) * ld + K - k0) / 8);
-    step = KM ? kSK / 8 * (int)ld : kSK / 8;
+    step = KM ? SK / 8 * (int)ld : SK / 8;
     k = k0;
   }
   // TAIL: the stage may be the last one.  (Scalar instructions count here: a small problem is one wavefront per SIMD, bound by
@@ -108,7 +107,7 @@ struct Side {
     for (int j = 0; j < LJ; ++j) load_lds16(rsrc, dead ? 0x80000000u : voff[j], dst + j * NT * 16);
     at += 16l * step;
     left -= step;
-    k += kSK;
+    k += SK;
   }
   // fragment of the 16-row block `blk`, 32-wide step `step`: 8 consecutive k of row (lane & 15) per lane
   static __device__ __forceinline__ bf16x8_t frag(unsigned lds, int blk, int step, int lane) {
@@ -122,7 +121,7 @@ struct Side {
       u.s.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(at + 4 * ROWS * 2));
       return u.v;
     }
-    const unsigned a = lds + (blk * 16 + lr) * 128 + (((4 * step + lq) ^ (lr >> 1)) * 16);
+    const unsigned a = lds + (blk * 16 + lr) * (SK * 2) + (((4 * step + lq) ^ key(lr)) * 16);
     union { v4i_t a; bf16x8_t v; } u;
     u.a = *(const lds_v4i_t *)(uintptr_t)a;
     return u.v;
@@ -180,14 +179,41 @@ __device__ __forceinline__ void tile_epilogue8(const TileP &p, float *v, int m, 
   store8(p.C + o, v);
 }
 
+// Waits for every LDS read and for all of the loads on their way but those of the last `later` stages (of L loads a thread; CAP
+// stages at most), then for the other wavefronts.
+template <int L, typename Cap>
+__device__ __forceinline__ void wait_stages(int later, Cap) {
+  constexpr int CAP = Cap::value;
+  if (CAP >= 3 && later >= 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(3 * L) : "memory");
+  else if (CAP >= 2 && later >= 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * L) : "memory");
+  else if (CAP >= 1 && later >= 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(L) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+// four column sums, or partial sums of a split
+__device__ __forceinline__ void store_colsum(const TileP &p, int n, int split, float (&v)[4]) {
+  if (p.splits > 1) {
+    *(float4 *)(p.part + (long)p.splits * p.M * p.N + (long)split * p.N + n) = make_float4(v[0], v[1], v[2], v[3]);
+    return;
+  }
+  if (p.colsum_acc) {
+    float old[4];
+    unpack4(*(const uint2 *)(p.colsum + n), old);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[t] += old[t];
+  }
+  *(uint2 *)(p.colsum + n) = pack4(v);
+}
+
 // One tile: workgroup `bid` of the problem's tiles_m * tiles_n * splits (tiles of a split after each other); 256 threads,
 // 2 x 2 wavefronts.
-// R: stages in the ring.  The kernels differ in nothing but tile, ring and speed: every output is the same sum in the same order.
+// R: stages in the ring.  These kernels differ in nothing but tile, ring and speed: every output is the same sum in the same order.
 template <int BM, int BN, int R, bool AKM, bool BKM>
 __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *smem) {
   constexpr int NT = 256, WGN = 2, WTM = BM / 2, WTN = BN / 2, TM = WTM / 16, TN = WTN / 16;
-  typedef Side<BM, AKM, NT> SA;
-  typedef Side<BN, BKM, NT> SB;
+  typedef Side<BM, AKM, NT, kSK> SA;
+  typedef Side<BN, BKM, NT, kSK> SB;
   constexpr unsigned kStage = SA::kBytes + SB::kBytes;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WGN, wn = wave % WGN;
@@ -260,16 +286,6 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
         if (m < p.M && n < p.N && p.splits == 1) ein[I][pass] = epilogue_in8(p, m, n);
       }
   };
-  // waits for every LDS read and for all of the loads on their way but those of the last `later` stages, CAP at most
-  auto wait_stages = [&](int later, auto cap) {
-    constexpr int CAP = decltype(cap)::value;
-    if (CAP >= 3 && later >= 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(3 * L) : "memory");
-    else if (CAP >= 2 && later >= 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * L) : "memory");
-    else if (CAP >= 1 && later >= 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(L) : "memory");
-    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-  };
   typedef std::integral_constant<int, R - 1> InFlight;
   typedef std::integral_constant<int, R - 2> InFlight2;
   // INNER: stage st + R exists and is not the last
@@ -279,7 +295,7 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
     read_step(buf, 1);
     mfma_step(0);
     if (INNER || st + 1 < nk) {
-      wait_stages(INNER ? R : nk - 2 - st, InFlight2());
+      wait_stages<L>(INNER ? R : nk - 2 - st, InFlight2());
       // (ring of four, one workgroup per compute unit: reads before loads, 128 x 1280 x 5120 49 -> 44 us; elsewhere the
       // compiler's own order is the better one)
       if (R < 4 && (INNER || st + R < nk)) load_stage(buf, !INNER);
@@ -292,7 +308,7 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
 #pragma unroll
   for (int i = 0; i < R; ++i)
     if (i < nk) load_stage(i, true);
-  wait_stages(nk - 1, InFlight());
+  wait_stages<L>(nk - 1, InFlight());
   read_step(0, 0);
   int st = 0;
   for (; st + 2 * R < nk; st += R) {
@@ -311,17 +327,7 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
       const int n = n0 + wn * WTN + j * 16 + lq * 4;
       if (n >= p.N) continue;
       float v[4] = {accs[j][0], accs[j][1], accs[j][2], accs[j][3]};
-      if (p.splits > 1) {
-        *(float4 *)(p.part + (long)p.splits * p.M * p.N + (long)split * p.N + n) = make_float4(v[0], v[1], v[2], v[3]);
-        continue;
-      }
-      if (p.colsum_acc) {
-        float old[4];
-        unpack4(*(const uint2 *)(p.colsum + n), old);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] += old[t];
-      }
-      *(uint2 *)(p.colsum + n) = pack4(v);
+      store_colsum(p, n, split, v);
     }
   }
   // epilogue through LDS, 32 rows of the wavefront's part at a time: lane l of block (i, j) holds row i*16 + (l & 15),
@@ -355,23 +361,174 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
   }
 }
 
+// The same with the wavefronts side by side along k: a stage is 128 k, wavefront w takes its 32-wide step w on the whole tile,
+// and the four partial tiles are added through LDS at the end, in the order of the wavefronts (another order of additions than
+// tile_body's: not where that one is to be kept, see Gemm::ordered).
 template <int BM, int BN, int R, bool AKM, bool BKM>
+__device__ __forceinline__ void kwave_body(const TileP &p, int bid, uint16_t *smem) {
+  constexpr int NT = 256, SK = 128, TM = BM / 16, TN = BN / 16;
+  typedef Side<BM, AKM, NT, SK> SA;
+  typedef Side<BN, BKM, NT, SK> SB;
+  constexpr unsigned kStage = SA::kBytes + SB::kBytes;
+  constexpr int L = SA::LJ + SB::LJ;
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tiles = p.tiles_m * p.tiles_n, split = bid / tiles;
+  NtP q;  // tile_of looks at these only
+  q.tiles_m = p.tiles_m; q.tiles_n = p.tiles_n; q.gm = p.gm;
+  int tile_m, tile_n;
+  tile_of(q, bid - split * tiles, &tile_m, &tile_n);
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int nk_all = (p.K + SK - 1) / SK, s0 = split * p.stages_per_split, nk = min(nk_all - s0, p.stages_per_split);
+  SA sa;
+  SB sb;
+  sa.init(tid, p.lda);
+  sb.init(tid, p.ldb);
+  sa.start(p.A, p.lda, m0, p.M, s0 * SK, p.K);
+  sb.start(p.B, p.ldb, n0, p.N, s0 * SK, p.K);
+  const unsigned lds0 = (unsigned)(uintptr_t)smem;
+  f32x4_t acc[TM][TN], accs[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    accs[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < TM; ++i) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  const bool sum = AKM && BKM && p.colsum && tile_m == 0;  // column sums of B, as in tile_body
+  union { unsigned w[4]; bf16x8_t v; } ones;
+  ones.w[0] = ones.w[1] = ones.w[2] = ones.w[3] = 0x3F803F80u;
+  bf16x8_t af[2][TM], bf[2][TN];
+  auto load_stage = [&](int buf, bool tail) {
+    sa.load(p.K, lds0 + buf * kStage, wave, tail);
+    sb.load(p.K, lds0 + buf * kStage + SA::kBytes, wave, tail);
+  };
+  auto read_stage = [&](int buf, int set) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) bf[set][j] = SB::frag(lds0 + buf * kStage + SA::kBytes, j, wave, lane);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) af[set][i] = SA::frag(lds0 + buf * kStage, i, wave, lane);
+  };
+  auto mfma_stage = [&](int set) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[set][j], af[set][i], acc[i][j], 0, 0, 0);
+    if (AKM && BKM && sum) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) accs[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[set][j], ones.v, accs[j], 0, 0, 0);
+    }
+  };
+  // the epilogue's rows: thread t has 8 columns of rows t / (BN / 8) + it * RPP
+  constexpr int CPT = BN / 8, RPP = NT / CPT, PASSES = (BM + RPP - 1) / RPP;
+  const int c8 = (tid % CPT) * 8, n = n0 + c8, r0 = tid / CPT;
+  u32x4_a8_t ein[PASSES], ebias = {0, 0, 0, 0};
+  auto fetch = [&]() {
+    if (n < p.N && p.splits == 1) ebias = bias8(p, n);
+#pragma unroll
+    for (int it = 0; it < PASSES; ++it) {
+      const int row = r0 + it * RPP, m = m0 + row;
+      ein[it] = u32x4_a8_t{0, 0, 0, 0};
+      if (row < BM && m < p.M && n < p.N && p.splits == 1) ein[it] = epilogue_in8(p, m, n);
+    }
+  };
+  typedef std::integral_constant<int, R - 1> InFlight;
+  typedef std::integral_constant<int, R - 2> InFlight2;
+  // Interval st: stage st is in the registers (set st & 1), the next one is read while its matrix instructions run, and behind
+  // the barrier, where everyone has read stage st, the one R further on is loaded over it.  INNER as in tile_body.
+  auto interval = [&](int st, int buf, int set, auto inner) {
+    constexpr bool INNER = decltype(inner)::value;
+    if (INNER || st + 1 < nk) {
+      wait_stages<L>(INNER ? R : nk - 2 - st, InFlight2());
+      read_stage((buf + 1) % R, set ^ 1);
+      __builtin_amdgcn_sched_barrier(0);
+      if (INNER || st + R < nk) load_stage(buf, !INNER);
+    } else {
+      fetch();
+    }
+    mfma_stage(set);
+  };
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+    if (i < nk) load_stage(i, true);
+  wait_stages<L>(nk - 1, InFlight());
+  read_stage(0, 0);
+  constexpr int U = R % 2 ? 2 * R : R;
+  int st = 0;
+  for (; st + U + R < nk; st += U) {
+#pragma unroll
+    for (int i = 0; i < U; ++i) interval(st + i, i % R, i & 1, std::true_type());
+  }
+  for (; st < nk; st += U) {
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+      if (st + i < nk) interval(st + i, i % R, i & 1, std::false_type());
+  }
+  // partial tiles [wavefront][row][BN + 4], partial sums [wavefront][BN] behind them
+  constexpr int LD = BN + 4;
+  float *parts = (float *)smem, *psum = parts + 4 * BM * LD;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+      *(float4 *)(parts + (wave * BM + i * 16 + lr) * LD + j * 16 + lq * 4) = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+  if (AKM && BKM && sum && lr == 0)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) *(float4 *)(psum + wave * BN + j * 16 + lq * 4) = make_float4(accs[j][0], accs[j][1], accs[j][2], accs[j][3]);
+  __syncthreads();
+  if (AKM && BKM && sum && tid < BN / 4 && n0 + tid * 4 < p.N) {
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] += psum[w * BN + tid * 4 + t];
+    store_colsum(p, n0 + tid * 4, split, v);
+  }
+#pragma unroll
+  for (int it = 0; it < PASSES; ++it) {
+    const int row = r0 + it * RPP, m = m0 + row;
+    if (row >= BM || m >= p.M || n >= p.N) continue;
+    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float *src = parts + (w * BM + row) * LD + c8;
+      const float4 lo = *(const float4 *)src, hi = *(const float4 *)(src + 4);
+      v[0] += lo.x; v[1] += lo.y; v[2] += lo.z; v[3] += lo.w;
+      v[4] += hi.x; v[5] += hi.y; v[6] += hi.z; v[7] += hi.w;
+    }
+    if (p.splits > 1) {
+      float *o = p.part + ((long)split * p.M + m) * p.N + n;
+      *(float4 *)o = make_float4(v[0], v[1], v[2], v[3]);
+      *(float4 *)(o + 4) = make_float4(v[4], v[5], v[6], v[7]);
+    } else {
+      tile_epilogue8(p, v, m, n, ebias, ein[it]);
+    }
+  }
+}
+
+// KW: wavefronts along k
+template <int BM, int BN, int R, bool KW, bool AKM, bool BKM>
+__device__ __forceinline__ void any_body(const TileP &p, int bid, uint16_t *smem) {
+  if constexpr (KW) kwave_body<BM, BN, R, AKM, BKM>(p, bid, smem);
+  else tile_body<BM, BN, R, AKM, BKM>(p, bid, smem);
+}
+template <int BM, int BN, int R, bool KW, bool AKM, bool BKM>
 __global__ __launch_bounds__(256, 2) void gemm_tile_k(TileP p) {
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
-  tile_body<BM, BN, R, AKM, BKM>(p, blockIdx.x, smem);
+  any_body<BM, BN, R, KW, AKM, BKM>(p, blockIdx.x, smem);
 }
 
 // The two products of a linear's backward in one launch: the weight gradient (both operands k-major) and the input
 // gradient (both K-contiguous) read the same dY and do not depend on each other.  Launched one after the other, the
 // second waits until the last workgroup of the first has finished; here the one with the longer tiles goes first and the
 // other fills the machine behind it.
-template <int BM, int BN, int R>
+template <int BM, int BN, int R, bool KW>
 __global__ __launch_bounds__(256, 2) void gemm_tile_pair_k(TileP w, TileP d, int first, int w_first) {
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   const int bid = blockIdx.x;
   const bool head = bid < first;
-  if (head == (w_first != 0)) tile_body<BM, BN, R, true, true>(w, head ? bid : bid - first, smem);
-  else tile_body<BM, BN, R, false, false>(d, head ? bid : bid - first, smem);
+  if (head == (w_first != 0)) any_body<BM, BN, R, KW, true, true>(w, head ? bid : bid - first, smem);
+  else any_body<BM, BN, R, KW, false, false>(d, head ? bid : bid - first, smem);
 }
 
 // Second half of a split product: adds the partial products in the order of the splits and applies the epilogue;
@@ -406,8 +563,11 @@ __global__ __launch_bounds__(256) void tile_reduce_k(TileP p) {
   tile_epilogue8(p, v, m, n, bias8(p, n), epilogue_in8(p, m, n));
 }
 
-struct TileCfg { int bm, bn, ring; };
-static const TileCfg kCfg[] = {{128, 128, 2}, {64, 128, 2}, {64, 64, 2}, {64, 128, 3}, {64, 64, 3}, {128, 128, 4}};
+struct TileCfg { int bm, bn, ring, sk; };  // sk: k per stage, 128 with the wavefronts along k
+static const TileCfg kCfg[] = {{128, 128, 2, 64}, {64, 128, 2, 64}, {64, 64, 2, 64}, {64, 128, 3, 64}, {64, 64, 3, 64}, {128, 128, 4, 64},
+                                {64, 64, 3, 128}, {32, 64, 3, 128}, {32, 32, 4, 128}};
+constexpr int kCfgs = sizeof kCfg / sizeof kCfg[0];
+constexpr int kOneOrder = 6;  // the first six add in the same order
 int g_tile_cfg = -1, g_tile_splits = 0;  // test hooks: >= 0 pins the tile, > 0 the number of splits
 
 static hipError_t launch_reduce(const TileP &p, hipStream_t s) {
@@ -418,46 +578,50 @@ static hipError_t launch_reduce(const TileP &p, hipStream_t s) {
 }
 static unsigned blocks_of(const TileP &p) { return (unsigned)(p.tiles_m * p.tiles_n * p.splits); }
 
-template <int BM, int BN, int R>
+template <int BM, int BN, int R, bool KW>
 static constexpr size_t smem_of() {
-  constexpr size_t stg = (size_t)4 * 32 * (BN / 2 + 4) * 4, stages = (size_t)R * (BM + BN) * kSK * 2;
+  constexpr size_t stg = KW ? (size_t)4 * BM * (BN + 4) * 4 + 4 * BN * 4 : (size_t)4 * 32 * (BN / 2 + 4) * 4;
+  constexpr size_t stages = (size_t)R * (BM + BN) * (KW ? 128 : kSK) * 2;
   return stg > stages ? stg : stages;
 }
-template <int BM, int BN, int R, bool AKM, bool BKM>
+template <int BM, int BN, int R, bool KW, bool AKM, bool BKM>
 static hipError_t launch_tile(const TileP &p, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_k<BM, BN, R, AKM, BKM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN, R>());
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_k<BM, BN, R, KW, AKM, BKM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN, R, KW>());
     if (e != hipSuccess) return e;
     attr_set = true;
   }
   prof::Scope ps(prof::GEMM_MFMA_TILE, 2.0 * p.M * p.N * p.K, 0, s);
-  hipLaunchKernelGGL((gemm_tile_k<BM, BN, R, AKM, BKM>), dim3(blocks_of(p)), dim3(256), (smem_of<BM, BN, R>()), s, p);
+  hipLaunchKernelGGL((gemm_tile_k<BM, BN, R, KW, AKM, BKM>), dim3(blocks_of(p)), dim3(256), (smem_of<BM, BN, R, KW>()), s, p);
   hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : launch_reduce(p, s);
 }
 template <bool AKM, bool BKM>
 static hipError_t launch_cfg(int cfg, const TileP &p, hipStream_t s) {
   switch (cfg) {
-    case 0: return launch_tile<128, 128, 2, AKM, BKM>(p, s);
-    case 1: return launch_tile<64, 128, 2, AKM, BKM>(p, s);
-    case 2: return launch_tile<64, 64, 2, AKM, BKM>(p, s);
-    case 3: return launch_tile<64, 128, 3, AKM, BKM>(p, s);
-    case 4: return launch_tile<64, 64, 3, AKM, BKM>(p, s);
-    default: return launch_tile<128, 128, 4, AKM, BKM>(p, s);
+    case 0: return launch_tile<128, 128, 2, false, AKM, BKM>(p, s);
+    case 1: return launch_tile<64, 128, 2, false, AKM, BKM>(p, s);
+    case 2: return launch_tile<64, 64, 2, false, AKM, BKM>(p, s);
+    case 3: return launch_tile<64, 128, 3, false, AKM, BKM>(p, s);
+    case 4: return launch_tile<64, 64, 3, false, AKM, BKM>(p, s);
+    case 5: return launch_tile<128, 128, 4, false, AKM, BKM>(p, s);
+    case 6: return launch_tile<64, 64, 3, true, AKM, BKM>(p, s);
+    case 7: return launch_tile<32, 64, 3, true, AKM, BKM>(p, s);
+    default: return launch_tile<32, 32, 4, true, AKM, BKM>(p, s);
   }
 }
-template <int BM, int BN, int R>
+template <int BM, int BN, int R, bool KW>
 static hipError_t launch_pair(const TileP &w, const TileP &d, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_pair_k<BM, BN, R>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN, R>());
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_pair_k<BM, BN, R, KW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN, R, KW>());
     if (e != hipSuccess) return e;
     attr_set = true;
   }
   prof::Scope ps(prof::GEMM_MFMA_TILE, 2.0 * w.M * w.N * w.K + 2.0 * d.M * d.N * d.K, 0, s);
   const bool w_first = w.stages_per_split >= d.stages_per_split;
-  hipLaunchKernelGGL((gemm_tile_pair_k<BM, BN, R>), dim3(blocks_of(w) + blocks_of(d)), dim3(256), (smem_of<BM, BN, R>()), s, w, d,
+  hipLaunchKernelGGL((gemm_tile_pair_k<BM, BN, R, KW>), dim3(blocks_of(w) + blocks_of(d)), dim3(256), (smem_of<BM, BN, R, KW>()), s, w, d,
                      (int)(w_first ? blocks_of(w) : blocks_of(d)), w_first ? 1 : 0);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = launch_reduce(w, s);
@@ -481,26 +645,33 @@ bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
 //              ring of 3: 0.4 alone, 0.6 two together (2331 x 1024 x 4096, 296 tiles: 39 us against 52 and, 128 x 128, 44);
 //    64 x 64,  ring of 2: 0.22 each from four on;
 //              ring of 3: 0.3 alone: for the smallest (256 x 256 x 1024: 7.6 us against 10.5; 128 x 1280 x 5120: 23 against 40).
+//   wavefronts along k (a stage of 128 counts twice): 64 x 64 0.25 alone; 32 x 64 0.17; 32 x 32 0.12: for fewer tiles than
+//              compute units, where a stage is bound by the LDS reads of one workgroup: of a 64 x 64 tile four wavefronts side by
+//              side read half as much as four quarters of it, and 32 x 32 tiles leave each unit a quarter of the loads.
+//              (256 x 256 x 1024 7.4 -> 5.2 us, 128 x 1280 x 5120 22.3 -> 14.6, 256 x 1280 x 5120 25.1 -> 17.7 by 32 x 64, 1024 x 1024
+//              x 4096 25.7 -> 21.6 by 64 x 64; both products of 256 x 256 -> 1024's backward 8.5 -> 6.0.)
 // Splitting the contraction costs a second launch and the partial products' way out and back at about 6 TB/s.
 struct TileCost { double a, b, c, e; int fit; };  // fit: workgroups that share a compute unit at most
-static const TileCost kCost[] = {{0.61, 0.19, 0.545, 1.5, 2}, {0.405, 0.17, 0.335, 1.0, 3}, {0.37, 0.11, 0.21, 0.5, 5},
-                                 {0.27, 0.15, 0.345, 1.4, 2}, {0.26, 0.04, 0.23, 0.75, 3}, {0.055, 0.615, 0.67, 2.8, 1}};
-constexpr int kCfgs = sizeof kCfg / sizeof kCfg[0];
+static const TileCost kCost[kCfgs] = {{0.61, 0.19, 0.545, 1.5, 2}, {0.405, 0.17, 0.335, 1.0, 3}, {0.37, 0.11, 0.21, 0.5, 5},
+                                      {0.235, 0.175, 0.337, 1.35, 2}, {0.295, 0.03, 0.232, 0.53, 3}, {0.04, 0.61, 0.67, 2.5, 1},
+                                      {0.135, 0.118, 0.253, 1.95, 1}, {0.098, 0.068, 0.132, 0.97, 2}, {0.065, 0.055, 0.108, 0.82, 2}};
 constexpr int kMaxSplits = 8;
 static int stages_of(int K) { return (K + kSK - 1) / kSK; }
 static long tiles_of(int M, int N, int cfg) { return (long)((M + kCfg[cfg].bm - 1) / kCfg[cfg].bm) * ((N + kCfg[cfg].bn - 1) / kCfg[cfg].bn); }
 static double reduce_cost(int M, int N, int splits) { return splits > 1 ? 3.0 + 8.0 * splits * M * N / 6e6 : 0.0; }
+// stages of 64 k
+static int cost_stages(int K, int cfg) { return (K + kCfg[cfg].sk - 1) / kCfg[cfg].sk * (kCfg[cfg].sk / kSK); }
 static double tile_cost(int M, int N, int K, int cfg, int splits) {
   const double n = (double)((tiles_of(M, N, cfg) * splits + 255) / 256), t = std::max(kCost[cfg].a + kCost[cfg].b * n, kCost[cfg].c * n);
-  return 2.5 + t * ((stages_of(K) + splits - 1) / splits) + kCost[cfg].e * n + reduce_cost(M, N, splits);
+  return 2.5 + t * ((cost_stages(K, cfg) + splits - 1) / splits) + kCost[cfg].e * n + reduce_cost(M, N, splits);
 }
 static size_t split_bytes(int M, int N, int splits) { return splits > 1 ? (size_t)splits * ((size_t)M + 1) * N * 4 : 0; }
 static bool split_ok(int K, int splits) { return splits == 1 || splits * 4 <= stages_of(K); }
 
-// The choice for a problem given `scratch` bytes for partial products; returns its predicted time.
-static double tile_plan(int M, int N, int K, size_t scratch, int *cfg, int *splits) {
+// The choice for a problem given `scratch` bytes for partial products, among the first `cfgs` tiles; returns its predicted time.
+static double tile_plan(int M, int N, int K, size_t scratch, int cfgs, int *cfg, int *splits) {
   double best = 1e30;
-  for (int c = 0; c < kCfgs; ++c)
+  for (int c = 0; c < cfgs; ++c)
     for (int sp = 1; sp <= kMaxSplits && split_ok(K, sp); sp *= 2) {
       if (split_bytes(M, N, sp) > scratch) break;
       const double t = tile_cost(M, N, K, c, sp);
@@ -523,7 +694,7 @@ static double pair_plan(const Shape &w, const Shape &d, size_t scratch, PairPlan
       for (int sd = 1; sd <= kMaxSplits && split_ok(d.K, sd); sd *= 2) {
         if (split_bytes(d.M, d.N, sd) > half) break;
         const double nw = (double)tiles_of(w.M, w.N, c) * sw, nd = (double)tiles_of(d.M, d.N, c) * sd;
-        const double lw = (stages_of(w.K) + sw - 1) / sw, ld = (stages_of(d.K) + sd - 1) / sd, longest = std::max(lw, ld);
+        const double lw = (cost_stages(w.K, c) + sw - 1) / sw, ld = (cost_stages(d.K, c) + sd - 1) / sd, longest = std::max(lw, ld);
         const double n = std::min((double)kCost[c].fit, std::ceil((nw + nd) / 256.0));
         const double work = ((nw * lw + nd * ld) * kCost[c].c + (nw + nd) * kCost[c].e) / 256.0 + 0.25 * std::min(lw, ld) * (kCost[c].a + kCost[c].b);
         const double t = 2.5 + std::max(work, longest * (kCost[c].a + kCost[c].b * n) + kCost[c].e) + reduce_cost(w.M, w.N, sw) + reduce_cost(d.M, d.N, sd);
@@ -546,7 +717,7 @@ bool gemm_large_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
   if (dtype != SSDT_BF16 || !large_possible(M, N, K, transA, transB)) return false;
   if (!gemm_tile_fits(M, N, K, transA, transB, dtype)) return true;
   int cfg, splits;
-  return tile_plan(M, N, K, 0, &cfg, &splits) > 0.9 * large_cost(M, N, K);
+  return tile_plan(M, N, K, 0, kOneOrder, &cfg, &splits) > 0.9 * large_cost(M, N, K);
 }
 
 // Whether the weight gradient w (M x N over K tokens) and the input gradient d of a linear should share a launch, given
@@ -555,7 +726,7 @@ static bool pair_wanted(const Shape &w, const Shape &d, size_t scratch, PairPlan
   if (!gemm_tile_fits(w.M, w.N, w.K, true, false, SSDT_BF16) || !gemm_tile_fits(d.M, d.N, d.K, false, true, SSDT_BF16)) return false;
   if (gemm_large_fits(w.M, w.N, w.K, true, false, SSDT_BF16) || gemm_large_fits(d.M, d.N, d.K, false, true, SSDT_BF16)) return false;
   int c, sp;
-  const double alone = tile_plan(w.M, w.N, w.K, scratch, &c, &sp) + tile_plan(d.M, d.N, d.K, scratch, &c, &sp);
+  const double alone = tile_plan(w.M, w.N, w.K, scratch, kCfgs, &c, &sp) + tile_plan(d.M, d.N, d.K, scratch, kCfgs, &c, &sp);
   return pair_plan(w, d, scratch, out) < alone;
 }
 
@@ -563,7 +734,7 @@ static bool pair_wanted(const Shape &w, const Shape &d, size_t scratch, PairPlan
 size_t gemm_tile_scratch_bytes(int M, int N, int K, bool transA, bool transB, int dtype) {
   if (!gemm_tile_fits(M, N, K, transA, transB, dtype) || gemm_large_fits(M, N, K, transA, transB, dtype)) return 0;
   int cfg = 0, splits = 1;
-  tile_plan(M, N, K, ~(size_t)0, &cfg, &splits);
+  tile_plan(M, N, K, ~(size_t)0, kCfgs, &cfg, &splits);
   return split_bytes(M, N, splits);
 }
 size_t gemm_pair_scratch_bytes(int rows, int in, int out, int dtype) {
@@ -600,7 +771,7 @@ static void choose(TileP *p, int cfg, int splits, float *part) {
   p->tiles_m = (p->M + kCfg[cfg].bm - 1) / kCfg[cfg].bm;
   p->tiles_n = (p->N + kCfg[cfg].bn - 1) / kCfg[cfg].bn;
   p->gm = g_force_waves > 0 ? g_force_waves : (p->tiles_m >= p->tiles_n ? 4 : 8);
-  const int nk = stages_of(p->K);
+  const int nk = (p->K + kCfg[cfg].sk - 1) / kCfg[cfg].sk;
   p->stages_per_split = (nk + splits - 1) / splits;
   p->splits = (nk + p->stages_per_split - 1) / p->stages_per_split;  // (every part has a stage)
   p->part = part;
@@ -612,7 +783,7 @@ hipError_t gemm_mfma_tile_bf16(const Gemm &g, hipStream_t s) {
   hipError_t e = prepare(g, &p);
   if (e != hipSuccess) return e;
   int cfg = 0, splits = 1;
-  tile_plan(g.M, g.N, g.K, usable_scratch(g), &cfg, &splits);
+  tile_plan(g.M, g.N, g.K, usable_scratch(g), g.ordered ? kOneOrder : kCfgs, &cfg, &splits);
   if (g_tile_cfg >= 0) cfg = g_tile_cfg;
   if (g_tile_splits > 0 && split_bytes(g.M, g.N, g_tile_splits) <= g.scratch_bytes) splits = g_tile_splits;
   choose(&p, cfg, splits, (float *)g.scratch);
@@ -636,12 +807,15 @@ hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, hipStream_t s) {
   choose(&pw, pp.cfg, pp.sw, (float *)w.scratch);
   choose(&pd, pp.cfg, pp.sd, (float *)((char *)w.scratch + half_of(scratch)));
   switch (pp.cfg) {
-    case 0: return launch_pair<128, 128, 2>(pw, pd, s);
-    case 1: return launch_pair<64, 128, 2>(pw, pd, s);
-    case 2: return launch_pair<64, 64, 2>(pw, pd, s);
-    case 3: return launch_pair<64, 128, 3>(pw, pd, s);
-    case 4: return launch_pair<64, 64, 3>(pw, pd, s);
-    default: return launch_pair<128, 128, 4>(pw, pd, s);
+    case 0: return launch_pair<128, 128, 2, false>(pw, pd, s);
+    case 1: return launch_pair<64, 128, 2, false>(pw, pd, s);
+    case 2: return launch_pair<64, 64, 2, false>(pw, pd, s);
+    case 3: return launch_pair<64, 128, 3, false>(pw, pd, s);
+    case 4: return launch_pair<64, 64, 3, false>(pw, pd, s);
+    case 5: return launch_pair<128, 128, 4, false>(pw, pd, s);
+    case 6: return launch_pair<64, 64, 3, true>(pw, pd, s);
+    case 7: return launch_pair<32, 64, 3, true>(pw, pd, s);
+    default: return launch_pair<32, 32, 4, true>(pw, pd, s);
   }
 }
 
