@@ -136,14 +136,14 @@ hipError_t transpose(const void *in, long ldi, void *out, long ldo, int rows, in
 // y += x  (elementwise, n elements)
 hipError_t add_inplace(void *y, const void *x, size_t n, int dtype, hipStream_t s);
 
-// 16-byte-vectorised bf16 row kernels; return hipErrorNotSupported when the shape / alignment does not fit
+// 16-byte-vectorised row kernels; return hipErrorNotSupported when the shape / alignment does not fit
 hipError_t norm_fwd_vec(const void *x, const void *gamma, const void *beta, void *y, float *mean, float *rstd, int rows,
-                        int H, float eps, int kind, hipStream_t s);
+                        int H, float eps, int kind, int dtype, hipStream_t s);
 hipError_t norm_bwd_vec(const void *dy, const void *x, const float *mean, const float *rstd, const void *gamma,
-                        const void *resid, void *dx, float *partial, int rows, int H, int kind, int chunks, hipStream_t s);
+                        const void *resid, void *dx, float *partial, int rows, int H, int kind, int chunks, int dtype, hipStream_t s);
 hipError_t attn_delta_vec(const void *o, long ldo, const void *dout, long lddo, float *delta, const float *lse, float *lse2,
-                          int B, int Sq, int A, int d, hipStream_t s);
-hipError_t colreduce1_vec(const void *a, long lda, float *partial, int rows, int cols, int chunks, hipStream_t s);
+                          int B, int Sq, int A, int d, int dtype, hipStream_t s);
+hipError_t colreduce1_vec(const void *a, long lda, float *partial, int rows, int cols, int chunks, hipStream_t s);  // (bf16)
 
 // fast paths (bf16 on the matrix cores); return hipErrorNotSupported when the shape does not fit
 hipError_t gemm_mfma_bf16(const Gemm &g, hipStream_t s);

@@ -175,10 +175,8 @@ __global__ __launch_bounds__(256) void norm_fwd_k(const T *x, const T *gamma, co
 
 hipError_t norm_fwd(const void *x, const void *gamma, const void *beta, void *y, float *mean, float *rstd, int rows,
                     int H, float eps, int kind, int dtype, hipStream_t s) {
-  if (dtype == SSDT_BF16) {
-    hipError_t e = norm_fwd_vec(x, gamma, beta, y, mean, rstd, rows, H, eps, kind, s);
-    if (e != hipErrorNotSupported) return e;
-  }
+  hipError_t e = norm_fwd_vec(x, gamma, beta, y, mean, rstd, rows, H, eps, kind, dtype, s);
+  if (e != hipErrorNotSupported) return e;
   dim3 grid((rows + 3) / 4);
   prof::Scope ps(prof::NORM_FWD, 0, 2.0 * rows * H * (dtype == SSDT_F32 ? 4 : 2), s);
   if (dtype == SSDT_F32)
@@ -322,7 +320,7 @@ static hipError_t norm_bwd_t(const T *dy, const T *x, const float *mean, const f
                              void *dgamma, void *dbeta, float *partial, size_t room, int rows, int H, int kind, bool accumulate, hipStream_t s) {
   if (room < (size_t)2 * H) return hipErrorInvalidValue;
   const int chunks = colreduce_chunks(rows, room / ((size_t)2 * H));
-  hipError_t e = sizeof(T) == 2 ? norm_bwd_vec(dy, x, mean, rstd, gamma, resid, dx, partial, rows, H, kind, chunks, s) : hipErrorNotSupported;
+  hipError_t e = norm_bwd_vec(dy, x, mean, rstd, gamma, resid, dx, partial, rows, H, kind, chunks, sizeof(T) == 4 ? SSDT_F32 : SSDT_BF16, s);
   if (e == hipErrorNotSupported) {
     prof::Scope ps(prof::NORM_BWD, 0, (resid ? 4.0 : 3.0) * rows * H * sizeof(T), s);
     const int col_blocks = (H + 127) / 128;
@@ -456,10 +454,8 @@ hipError_t attn_bwd(const Attn &a, hipStream_t s) {
 
 hipError_t attn_delta(const Attn &a, float *lse2, hipStream_t s) {
   AttnP p = to_p(a);
-  if (a.dtype == SSDT_BF16) {
-    hipError_t e = attn_delta_vec(a.o, a.ldo, a.dout, a.lddo, a.delta, a.lse, lse2, a.B, a.Sq, a.A, a.d, s);
-    if (e != hipErrorNotSupported) return e;
-  }
+  hipError_t e = attn_delta_vec(a.o, a.ldo, a.dout, a.lddo, a.delta, a.lse, lse2, a.B, a.Sq, a.A, a.d, a.dtype, s);
+  if (e != hipErrorNotSupported) return e;
   dim3 gq((a.Sq + 3) / 4, a.A, a.B);
   if (a.dtype == SSDT_F32) hipLaunchKernelGGL(attn_delta_k<float>, gq, dim3(256), 0, s, p, lse2);
   else hipLaunchKernelGGL(attn_delta_k<bf16>, gq, dim3(256), 0, s, p, lse2);

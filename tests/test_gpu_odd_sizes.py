@@ -288,6 +288,17 @@ def test_edges_of_tiles(name, dtype):
     check_against_oracle(l, case, on, hp.TOL[dtype])
 
 
+# fp32 rows of 2, 4, 8 and 16 chunks of 256 floats, and one beyond what the vector kernels hold
+@pytest.mark.parametrize("H,A", [(260, 5), (516, 6), (1028, 257), (2052, 18), (4100, 50)])
+@pytest.mark.parametrize("kind", ["gpt_preln", "bert_postln", "t5_enc"])
+def test_f32_norms_of_any_width(kind, H, A):
+    """Forward and backward, with and without a residual gradient and shift; 70 rows: two chunks of the gains' sums, one ragged."""
+    v = dict(gpt_preln=GPT, bert_postln=dict(BERT, mask="none"), t5_enc=dict(T5, arch="t5_enc", mask="none"))[kind]
+    l = runner.Layer(dtype="f32", **dict(v, B=2, S=35, H=H, A=A, F=64))
+    case = hp.make_layer_case(l, 8900 + H, bias_std=0.05)
+    check_against_oracle(l, case, run_single_layer(l, case, offload=False, fetch=False), hp.TOL["f32"])
+
+
 # One axis of a grid holds fewer than 2^24 workgroups of 256.  Attention by tiles: forward 65535 x 257 workgroups, backward
 # 2 x 65535 x 129.  Norm backward: one workgroup for four rows, and up to 128 for the first stage of the gain gradient.
 @pytest.mark.parametrize("dtype,B,S,A", [("bf16", 65535, 6, 257), ("bf16", 65535, 9, 129), ("bf16", 262143, 256, 1), ("f32", 262143, 256, 1)])
