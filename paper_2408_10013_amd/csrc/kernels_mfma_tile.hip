@@ -568,7 +568,7 @@ static const TileCfg kCfg[] = {{128, 128, 2, 64}, {64, 128, 2, 64}, {64, 64, 2, 
                                 {64, 64, 3, 128}, {32, 64, 3, 128}, {32, 32, 4, 128}};
 constexpr int kCfgs = sizeof kCfg / sizeof kCfg[0];
 constexpr int kOneOrder = 6;  // the first six add in the same order
-int g_tile_cfg = -1, g_tile_splits = 0;  // test hooks: >= 0 pins the tile, > 0 the number of splits
+int g_tile_cfg = -1, g_tile_splits = 0;  // test hooks: >= 0 pins the tile, > 0 the number of splits (of a pair's input gradient: the tens, if any)
 
 static hipError_t launch_reduce(const TileP &p, hipStream_t s) {
   if (p.splits == 1) return hipSuccess;
@@ -637,8 +637,9 @@ bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
 
 // DISPATCH.  Predicted time of a problem in microseconds, fitted to what the tiles were measured to take (MI355X, 78 products
 // of a layer's forms with 128 to 4096 rows; the choice is within 4 % of the best tile for nine in ten of them).  A launch
-// takes 2.5 us and e for each tile of a compute unit, and a workgroup's stage of 64 k takes a + b n when n workgroups
-// share a unit, never less than c n:
+// takes 2.5 us and e for each tile of a compute unit.  Whole rounds of as many workgroups as fit take c for each of a unit's
+// and stage of 64 k; in the last one a stage takes a + b n when n workgroups share a unit, and never less than c for each of
+// them, averaged over the machine (which they share too: 384 tiles of 128 x 128 take 0.9 us a stage, 512 take 1.1):
 //   128 x 128, ring of 2: 0.8 us alone, 1.07 two together (1.0 PFLOP/s on 4096 x 2048 x 8192, 512 tiles);
 //              ring of 4: 0.6 alone, and alone it is: for 192 tiles and long K (1024 x 3072 x 8192: 77 us against 106);
 //    64 x 128, ring of 2: 0.57 alone, 0.36 each from three on: where three share a unit;
@@ -650,20 +651,22 @@ bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
 //              side read half as much as four quarters of it, and 32 x 32 tiles leave each unit a quarter of the loads.
 //              (256 x 256 x 1024 7.4 -> 5.2 us, 128 x 1280 x 5120 22.3 -> 14.6, 256 x 1280 x 5120 25.1 -> 17.7 by 32 x 64, 1024 x 1024
 //              x 4096 25.7 -> 21.6 by 64 x 64; both products of 256 x 256 -> 1024's backward 8.5 -> 6.0.)
-// Splitting the contraction costs a second launch and the partial products' way out and back at about 6 TB/s.
+// Splitting the contraction costs a second launch and the partial products' way out and back, from the caches at about 8.6 TB/s.
 struct TileCost { double a, b, c, e; int fit; };  // fit: workgroups that share a compute unit at most
-static const TileCost kCost[kCfgs] = {{0.61, 0.19, 0.545, 1.5, 2}, {0.405, 0.17, 0.335, 1.0, 3}, {0.37, 0.11, 0.21, 0.5, 5},
-                                      {0.235, 0.175, 0.337, 1.35, 2}, {0.295, 0.03, 0.232, 0.53, 3}, {0.04, 0.61, 0.67, 2.5, 1},
-                                      {0.135, 0.118, 0.253, 1.95, 1}, {0.098, 0.068, 0.132, 0.97, 2}, {0.065, 0.055, 0.108, 0.82, 2}};
+static const TileCost kCost[kCfgs] = {{0.61, 0.155, 0.56, 1.9, 2}, {0.41, 0.165, 0.34, 1.0, 3}, {0.39, 0.107, 0.21, 0.39, 5},
+                                      {0.28, 0.155, 0.34, 1.55, 2}, {0.255, 0.115, 0.213, 0.45, 3}, {0.06, 0.52, 0.655, 3.5, 1},
+                                      {0.17, 0.077, 0.263, 3.0, 1}, {0.142, 0.066, 0.139, 1.05, 2}, {0.077, 0.068, 0.107, 0.78, 2}};
 constexpr int kMaxSplits = 8;
 static int stages_of(int K) { return (K + kSK - 1) / kSK; }
 static long tiles_of(int M, int N, int cfg) { return (long)((M + kCfg[cfg].bm - 1) / kCfg[cfg].bm) * ((N + kCfg[cfg].bn - 1) / kCfg[cfg].bn); }
-static double reduce_cost(int M, int N, int splits) { return splits > 1 ? 3.0 + 8.0 * splits * M * N / 6e6 : 0.0; }
+static double reduce_cost(int M, int N, int splits) { return splits > 1 ? 3.1 + 8.0 * splits * M * N / 8.6e6 : 0.0; }
 // stages of 64 k
 static int cost_stages(int K, int cfg) { return (K + kCfg[cfg].sk - 1) / kCfg[cfg].sk * (kCfg[cfg].sk / kSK); }
 static double tile_cost(int M, int N, int K, int cfg, int splits) {
-  const double n = (double)((tiles_of(M, N, cfg) * splits + 255) / 256), t = std::max(kCost[cfg].a + kCost[cfg].b * n, kCost[cfg].c * n);
-  return 2.5 + t * ((cost_stages(K, cfg) + splits - 1) / splits) + kCost[cfg].e * n + reduce_cost(M, N, splits);
+  const TileCost &q = kCost[cfg];
+  const long tiles = tiles_of(M, N, cfg) * splits, round = 256l * q.fit, full = tiles / round, rest = tiles - full * round;
+  const double t = full * q.c * q.fit + (rest ? std::max(q.a + q.b * ((rest + 255) / 256), q.c * rest / 256.0) : 0.0);
+  return 2.5 + t * ((cost_stages(K, cfg) + splits - 1) / splits) + q.e * tiles / 256.0 + reduce_cost(M, N, splits);
 }
 static size_t split_bytes(int M, int N, int splits) { return splits > 1 ? (size_t)splits * ((size_t)M + 1) * N * 4 : 0; }
 static bool split_ok(int K, int splits) { return splits == 1 || splits * 4 <= stages_of(K); }
@@ -681,7 +684,12 @@ static double tile_plan(int M, int N, int K, size_t scratch, int cfgs, int *cfg,
 }
 
 // The same for two problems in one launch (one tile size, each its own split; half of the scratch for each).  The tiles
-// of both share the machine: it is done when the work is (c per tile and stage), or when the longest tile is.
+// of both share the machine: it is done when the work is (c per tile and stage, and what of the shorter tiles runs beside
+// nothing at the end), or when the longest tile is.  Fitted by itself, to 27 linears' backwards in every tile and split: the
+// choice costs 1.3 % more than the best on average (with the table above 3.8 %; 1536 x 1280 -> 2560 44 against 35 us).
+static const TileCost kPairCost[kCfgs] = {{0.69, 0.13, 0.497, 2.2, 2}, {0.454, 0.155, 0.354, 0.73, 3}, {0.376, 0.068, 0.206, 0.6, 5},
+                                          {0.268, 0.121, 0.353, 1.68, 2}, {0.198, 0.112, 0.252, 0.354, 3}, {0.034, 0.6, 0.7, 3.9, 1},
+                                          {0.19, 0.042, 0.302, 2.93, 1}, {0.117, 0.065, 0.147, 1.12, 2}, {0.073, 0.048, 0.139, 0.86, 2}};
 struct PairPlan { int cfg = 0, sw = 1, sd = 1; };
 struct Shape { int M, N, K; };
 static size_t half_of(size_t scratch) { return scratch / 2 / 256 * 256; }
@@ -695,9 +703,11 @@ static double pair_plan(const Shape &w, const Shape &d, size_t scratch, PairPlan
         if (split_bytes(d.M, d.N, sd) > half) break;
         const double nw = (double)tiles_of(w.M, w.N, c) * sw, nd = (double)tiles_of(d.M, d.N, c) * sd;
         const double lw = (cost_stages(w.K, c) + sw - 1) / sw, ld = (cost_stages(d.K, c) + sd - 1) / sd, longest = std::max(lw, ld);
-        const double n = std::min((double)kCost[c].fit, std::ceil((nw + nd) / 256.0));
-        const double work = ((nw * lw + nd * ld) * kCost[c].c + (nw + nd) * kCost[c].e) / 256.0 + 0.25 * std::min(lw, ld) * (kCost[c].a + kCost[c].b);
-        const double t = 2.5 + std::max(work, longest * (kCost[c].a + kCost[c].b * n) + kCost[c].e) + reduce_cost(w.M, w.N, sw) + reduce_cost(d.M, d.N, sd);
+        const TileCost &q = kPairCost[c];
+        const double n = std::min((double)q.fit, std::ceil((nw + nd) / 256.0));
+        const double tail = (nw + nd > 256.0 * q.fit ? 0.35 : 0.29) * std::min(lw, ld) * (q.a + q.b);
+        const double work = ((nw * lw + nd * ld) * q.c + (nw + nd) * q.e) / 256.0 + tail;
+        const double t = 2.7 + std::max(work, longest * (q.a + q.b * n) + q.e) + reduce_cost(w.M, w.N, sw) + reduce_cost(d.M, d.N, sd);
         if (t < best * 0.98) { best = t; out->cfg = c; out->sw = sw; out->sd = sd; }
       }
     }
@@ -802,8 +812,10 @@ hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, hipStream_t s) {
   if (e == hipSuccess) e = prepare(d, &pd);
   if (e != hipSuccess) return e;
   if (g_tile_cfg >= 0) pp.cfg = g_tile_cfg;
-  if (g_tile_splits > 0 && std::max(split_bytes(pw.M, pw.N, g_tile_splits), split_bytes(pd.M, pd.N, g_tile_splits)) <= half_of(scratch))
-    pp.sw = pp.sd = g_tile_splits;
+  if (g_tile_splits > 0) {
+    const int sw = g_tile_splits % 10, sd = g_tile_splits >= 10 ? g_tile_splits / 10 : sw;
+    if (std::max(split_bytes(pw.M, pw.N, sw), split_bytes(pd.M, pd.N, sd)) <= half_of(scratch)) { pp.sw = sw; pp.sd = sd; }
+  }
   choose(&pw, pp.cfg, pp.sw, (float *)w.scratch);
   choose(&pd, pp.cfg, pp.sd, (float *)((char *)w.scratch + half_of(scratch)));
   switch (pp.cfg) {
