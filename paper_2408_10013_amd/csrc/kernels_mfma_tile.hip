@@ -87,6 +87,27 @@ struct Side {
     step = KM ? SK / 8 * (int)ld : SK / 8;
     k = k0;
   }
+  // The next stage piece by piece: its descriptor, piece j, and on to the stage behind it.
+  __device__ __forceinline__ v4i_t desc() {
+    asm volatile("" : "+s"(at), "+s"(left));
+    v4i_t rsrc;
+    rsrc[0] = (int)(unsigned)at;
+    rsrc[1] = (int)(unsigned)(at >> 32) & 0xffff;
+    const int rest = left & ~(left >> 31);
+    rsrc[2] = (rest >> 27) ? 0x7fffffff : rest << 4;
+    rsrc[3] = 0x00020000;
+    asm volatile("s_nop 4" : "+s"(rsrc));
+    return rsrc;
+  }
+  __device__ __forceinline__ void piece(const v4i_t &rsrc, int j, int K, unsigned dst, bool tail) {
+    const bool dead = !KM && tail && k + chunk * 8 >= K;
+    load_lds16(rsrc, dead ? 0x80000000u : voff[j], dst + j * NT * 16);
+  }
+  __device__ __forceinline__ void next() {
+    at += 16l * step;
+    left -= step;
+    k += SK;
+  }
   // TAIL: the stage may be the last one.  (Scalar instructions count here: a small problem is one wavefront per SIMD, bound by
   // what it issues.  With the descriptor's extent computed in 64 bits a stage took 30 to 50 ns longer.)
   __device__ __forceinline__ void load(int K, unsigned lds, int wave, bool tail) {
@@ -506,6 +527,153 @@ __device__ __forceinline__ void kwave_body(const TileP &p, int bid, uint16_t *sm
   }
 }
 
+// ---- 256 x 128 -----------------------------------------------------------------------------------------------------
+// For one to a few tiles of 256 x 128 per compute unit, fewer than 256 tiles of 256 x 256.  Such a problem by 128 x 128 tiles, two
+// workgroups on a unit, is bound by LDS: a wavefront's 64 x 64 part reads 8 KiB of fragments for sixteen matrix instructions, 128
+// bytes a cycle for the unit, all there is, and the loads write as much again as half of that.  Here eight wavefronts share a
+// tile and each has 128 x 64, a quarter less to read per instruction: four side by side on one half of a stage's k, four on the
+// other, and the two sums are added through LDS at the end (another order of additions than tile_body's: not where that one is
+// to be kept).  The schedule is that of gemm_km256_k: the first operand's fragments refilled block by block, the second's in two
+// sets, one barrier a stage behind the first block, no two LDS reads back to back; the loads are buffer loads, six a
+// wavefront, dealt out between the blocks, three stages in a ring.
+// 4096 x 2048 x 8192 156 -> 136 us with a residual, K-contiguous 150 -> 129 (1.07 PFLOP/s; 145 at best by four-deep rings of 128 x
+// 128), 8192 x 1024 x 4096 81 -> 67, 4096 x 2048 x 2048 47 -> 39.  Both operands k-major only 103 -> 99: every fragment is two reads there.
+#define SSDT_FENCE __builtin_amdgcn_sched_barrier(0)
+template <bool BKM>
+__global__ __launch_bounds__(512) void gemm_wide_k(TileP p) {
+  constexpr int BM = 256, BN = 128, NT = 512, R = 3, MB = 8, NB = 4;
+  typedef Side<BM, false, NT, kSK> SA;
+  typedef Side<BN, BKM, NT, kSK> SB;
+  constexpr unsigned kStage = SA::kBytes + SB::kBytes;
+  constexpr int L = SA::LJ + SB::LJ;  // 4 + 2
+  extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), kg = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+  NtP q;  // tile_of looks at these only
+  q.tiles_m = p.tiles_m; q.tiles_n = p.tiles_n; q.gm = p.gm;
+  int tile_m, tile_n;
+  tile_of(q, blockIdx.x, &tile_m, &tile_n);
+  const int m0 = tile_m * BM, n0 = tile_n * BN, nk = (p.K + kSK - 1) / kSK;
+  SA sa;
+  SB sb;
+  sa.init(tid, p.lda);
+  sb.init(tid, p.ldb);
+  sa.start(p.A, p.lda, m0, p.M, 0, p.K);
+  sb.start(p.B, p.ldb, n0, p.N, 0, p.K);
+  const unsigned lds0 = (unsigned)(uintptr_t)smem;
+  f32x4_t acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  bf16x8_t Af[MB], Bf[2][NB];
+  auto load_all = [&](unsigned at, bool tail) {
+    const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + at + wave * 1024);
+    const v4i_t ra = sa.desc(), rb = sb.desc();
+#pragma unroll
+    for (int j = 0; j < SA::LJ; ++j) sa.piece(ra, j, p.K, dst, tail);
+#pragma unroll
+    for (int j = 0; j < SB::LJ; ++j) sb.piece(rb, j, p.K, dst + SA::kBytes, tail);
+    sa.next();
+    sb.next();
+  };
+  auto rdA = [&](int i, unsigned at) { return SA::frag(lds0 + at, wm * MB + i, kg, lane); };
+  auto rdB = [&](int j, unsigned at) { return SB::frag(lds0 + at + SA::kBytes, wn * NB + j, kg, lane); };
+  auto mfma_block = [&](int i, int set, int j0, int j1) {
+    SSDT_FENCE;
+#pragma unroll
+    for (int j = j0; j < j1; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Bf[set][j], Af[i], acc[i][j], 0, 0, 0);
+    SSDT_FENCE;
+  };
+  unsigned rd = kStage, wr = 0;  // where the next stage is, where the stage R further on goes: bytes of LDS
+  auto advance = [&](unsigned x) { return x == (R - 1) * kStage ? 0u : x + kStage; };
+  // stage st, in the registers but for what its own reads still bring; behind the barrier the next one is read
+  auto stage = [&](int st, int set, auto inner) {
+    constexpr bool INNER = decltype(inner)::value;
+    mfma_block(0, set, 0, NB);
+    const bool more = INNER || st + 1 < nk, load = INNER || st + R < nk;
+    if (more) wait_stages<L>(INNER ? R : nk - 2 - st, std::integral_constant<int, R - 2>());
+    SSDT_FENCE;
+    v4i_t ra, rb;
+    const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + wr + wave * 1024);
+#pragma unroll
+    for (int i = 1; i < MB; ++i) {
+      mfma_block(i, set, 0, 1);
+      if (more && i <= NB) Bf[set ^ 1][i - 1] = rdB(i - 1, rd);
+      mfma_block(i, set, 1, 3);
+      if (more && i == 1) Af[0] = rdA(0, rd);
+      if (load) {
+        if (i == 1) ra = sa.desc();
+        if (i >= 1 && i <= 4) sa.piece(ra, i - 1, p.K, dst, !INNER);
+        if (i == 5) rb = sb.desc();
+        if (i >= 5 && i <= 6) sb.piece(rb, i - 5, p.K, dst + SA::kBytes, !INNER);
+      }
+      mfma_block(i, set, 3, NB);
+      if (more) Af[i] = rdA(i, rd);
+    }
+    sa.next();
+    sb.next();
+    rd = advance(rd);
+    wr = advance(wr);
+  };
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+    if (i < nk) load_all(i * kStage, true);
+  wait_stages<L>(nk - 1, std::integral_constant<int, R - 1>());
+#pragma unroll
+  for (int j = 0; j < NB; ++j) Bf[0][j] = rdB(j, 0);
+#pragma unroll
+  for (int i = 0; i < MB; ++i) Af[i] = rdA(i, 0);
+  int st = 0;
+  for (; st + 2 + R < nk; st += 2) {
+    stage(st, 0, std::true_type());
+    stage(st + 1, 1, std::true_type());
+  }
+  for (; st < nk; st += 2) {
+    stage(st, 0, std::false_type());
+    if (st + 1 < nk) stage(st + 1, 1, std::false_type());
+  }
+  // The two halves of the contraction: each wavefront keeps 64 of its 128 rows and hands the others to the wavefront that has the
+  // other half of k, through that one's part of LDS; from there row by row, 16 bytes per lane.
+  constexpr int LD = 68;
+  u32x4_a8_t ein[8], ebias = {0, 0, 0, 0};
+  const int c8 = (lane & 7) * 8, n = n0 + wn * 64 + c8, mb = m0 + wm * 128 + kg * 64;
+  if (n < p.N) ebias = bias8(p, n);
+#pragma unroll
+  for (int pass = 0; pass < 8; ++pass) {
+    const int m = mb + pass * 8 + (lane >> 3);
+    ein[pass] = u32x4_a8_t{0, 0, 0, 0};
+    if (m < p.M && n < p.N) ein[pass] = epilogue_in8(p, m, n);
+  }
+  float *own = (float *)smem + wave * (64 * LD), *other = (float *)smem + (wave ^ 4) * (64 * LD);
+  __syncthreads();
+#pragma unroll
+  for (int il = 0; il < 4; ++il)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const f32x4_t a = kg ? acc[il][j] : acc[4 + il][j];
+      *(float4 *)(other + (il * 16 + lr) * LD + j * 16 + lq * 4) = make_float4(a[0], a[1], a[2], a[3]);
+    }
+  __syncthreads();
+#pragma unroll
+  for (int il = 0; il < 4; ++il)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const f32x4_t a = kg ? acc[4 + il][j] : acc[il][j];
+      float4 *at = (float4 *)(own + (il * 16 + lr) * LD + j * 16 + lq * 4);
+      const float4 o = *at;
+      *at = make_float4(a[0] + o.x, a[1] + o.y, a[2] + o.z, a[3] + o.w);
+    }
+#pragma unroll
+  for (int pass = 0; pass < 8; ++pass) {
+    const int row = pass * 8 + (lane >> 3), m = mb + row;
+    const float4 lo = *(const float4 *)(own + row * LD + c8), hi = *(const float4 *)(own + row * LD + c8 + 4);
+    if (m >= p.M || n >= p.N) continue;
+    float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    tile_epilogue8(p, v, m, n, ebias, ein[pass]);
+  }
+}
+
 // KW: wavefronts along k
 template <int BM, int BN, int R, bool KW, bool AKM, bool BKM>
 __device__ __forceinline__ void any_body(const TileP &p, int bid, uint16_t *smem) {
@@ -565,8 +733,9 @@ __global__ __launch_bounds__(256) void tile_reduce_k(TileP p) {
 
 struct TileCfg { int bm, bn, ring, sk; };  // sk: k per stage, 128 with the wavefronts along k
 static const TileCfg kCfg[] = {{128, 128, 2, 64}, {64, 128, 2, 64}, {64, 64, 2, 64}, {64, 128, 3, 64}, {64, 64, 3, 64}, {128, 128, 4, 64},
-                                {64, 64, 3, 128}, {32, 64, 3, 128}, {32, 32, 4, 128}};
+                                {64, 64, 3, 128}, {32, 64, 3, 128}, {32, 32, 4, 128}, {256, 128, 3, 64}};
 constexpr int kCfgs = sizeof kCfg / sizeof kCfg[0];
+constexpr int kWide = kCfgs - 1;  // first operand K-contiguous, not split, alone in a launch
 constexpr int kOneOrder = 6;  // the first six add in the same order
 int g_tile_cfg = -1, g_tile_splits = 0;  // test hooks: >= 0 pins the tile, > 0 the number of splits (of a pair's input gradient: the tens, if any)
 
@@ -597,6 +766,19 @@ static hipError_t launch_tile(const TileP &p, hipStream_t s) {
   hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : launch_reduce(p, s);
 }
+template <bool BKM>
+static hipError_t launch_wide(const TileP &p, hipStream_t s) {
+  constexpr size_t smem = (size_t)3 * (256 + 128) * kSK * 2;
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_wide_k<BKM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  prof::Scope ps(prof::GEMM_MFMA_TILE, 2.0 * p.M * p.N * p.K, 0, s);
+  hipLaunchKernelGGL((gemm_wide_k<BKM>), dim3(p.tiles_m * p.tiles_n), dim3(512), smem, s, p);
+  return hipGetLastError();
+}
 template <bool AKM, bool BKM>
 static hipError_t launch_cfg(int cfg, const TileP &p, hipStream_t s) {
   switch (cfg) {
@@ -608,7 +790,10 @@ static hipError_t launch_cfg(int cfg, const TileP &p, hipStream_t s) {
     case 5: return launch_tile<128, 128, 4, false, AKM, BKM>(p, s);
     case 6: return launch_tile<64, 64, 3, true, AKM, BKM>(p, s);
     case 7: return launch_tile<32, 64, 3, true, AKM, BKM>(p, s);
-    default: return launch_tile<32, 32, 4, true, AKM, BKM>(p, s);
+    case 8: return launch_tile<32, 32, 4, true, AKM, BKM>(p, s);
+    default:
+      if constexpr (AKM) return hipErrorInvalidValue;
+      else return launch_wide<BKM>(p, s);
   }
 }
 template <int BM, int BN, int R, bool KW>
@@ -651,11 +836,12 @@ bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
 //              side read half as much as four quarters of it, and 32 x 32 tiles leave each unit a quarter of the loads.
 //              (256 x 256 x 1024 7.4 -> 5.2 us, 128 x 1280 x 5120 22.3 -> 14.6, 256 x 1280 x 5120 25.1 -> 17.7 by 32 x 64, 1024 x 1024
 //              x 4096 25.7 -> 21.6 by 64 x 64; both products of 256 x 256 -> 1024's backward 8.5 -> 6.0.)
+//  256 x 128: 0.96 us a stage, 0.84 where a third of the machine is left over.
 // Splitting the contraction costs a second launch and the partial products' way out and back, from the caches at about 8.6 TB/s.
 struct TileCost { double a, b, c, e; int fit; };  // fit: workgroups that share a compute unit at most
 static const TileCost kCost[kCfgs] = {{0.61, 0.155, 0.56, 1.9, 2}, {0.41, 0.165, 0.34, 1.0, 3}, {0.39, 0.107, 0.21, 0.39, 5},
                                       {0.28, 0.155, 0.34, 1.55, 2}, {0.255, 0.115, 0.213, 0.45, 3}, {0.06, 0.52, 0.655, 3.5, 1},
-                                      {0.17, 0.077, 0.263, 3.0, 1}, {0.142, 0.066, 0.139, 1.05, 2}, {0.077, 0.068, 0.107, 0.78, 2}};
+                                      {0.17, 0.077, 0.263, 3.0, 1}, {0.142, 0.066, 0.139, 1.05, 2}, {0.077, 0.068, 0.107, 0.78, 2}, {0.84, 0.0, 0.96, 6.3, 1}};
 constexpr int kMaxSplits = 8;
 static int stages_of(int K) { return (K + kSK - 1) / kSK; }
 static long tiles_of(int M, int N, int cfg) { return (long)((M + kCfg[cfg].bm - 1) / kCfg[cfg].bm) * ((N + kCfg[cfg].bn - 1) / kCfg[cfg].bn); }
@@ -675,7 +861,7 @@ static bool split_ok(int K, int splits) { return splits == 1 || splits * 4 <= st
 static double tile_plan(int M, int N, int K, size_t scratch, int cfgs, int *cfg, int *splits) {
   double best = 1e30;
   for (int c = 0; c < cfgs; ++c)
-    for (int sp = 1; sp <= kMaxSplits && split_ok(K, sp); sp *= 2) {
+    for (int sp = 1; sp <= (c == kWide ? 1 : kMaxSplits) && split_ok(K, sp); sp *= 2) {
       if (split_bytes(M, N, sp) > scratch) break;
       const double t = tile_cost(M, N, K, c, sp);
       if (t < best * 0.98) { best = t; *cfg = c; *splits = sp; }
@@ -687,7 +873,7 @@ static double tile_plan(int M, int N, int K, size_t scratch, int cfgs, int *cfg,
 // of both share the machine: it is done when the work is (c per tile and stage, and what of the shorter tiles runs beside
 // nothing at the end), or when the longest tile is.  Fitted by itself, to 27 linears' backwards in every tile and split: the
 // choice costs 1.3 % more than the best on average (with the table above 3.8 %; 1536 x 1280 -> 2560 44 against 35 us).
-static const TileCost kPairCost[kCfgs] = {{0.69, 0.13, 0.497, 2.2, 2}, {0.454, 0.155, 0.354, 0.73, 3}, {0.376, 0.068, 0.206, 0.6, 5},
+static const TileCost kPairCost[kWide] = {{0.69, 0.13, 0.497, 2.2, 2}, {0.454, 0.155, 0.354, 0.73, 3}, {0.376, 0.068, 0.206, 0.6, 5},
                                           {0.268, 0.121, 0.353, 1.68, 2}, {0.198, 0.112, 0.252, 0.354, 3}, {0.034, 0.6, 0.7, 3.9, 1},
                                           {0.19, 0.042, 0.302, 2.93, 1}, {0.117, 0.065, 0.147, 1.12, 2}, {0.073, 0.048, 0.139, 0.86, 2}};
 struct PairPlan { int cfg = 0, sw = 1, sd = 1; };
@@ -696,7 +882,7 @@ static size_t half_of(size_t scratch) { return scratch / 2 / 256 * 256; }
 static double pair_plan(const Shape &w, const Shape &d, size_t scratch, PairPlan *out) {
   const size_t half = half_of(scratch);
   double best = 1e30;
-  for (int c = 0; c < kCfgs; ++c)
+  for (int c = 0; c < kWide; ++c)
     for (int sw = 1; sw <= kMaxSplits && split_ok(w.K, sw); sw *= 2) {
       if (split_bytes(w.M, w.N, sw) > half) break;
       for (int sd = 1; sd <= kMaxSplits && split_ok(d.K, sd); sd *= 2) {
@@ -736,7 +922,7 @@ static bool pair_wanted(const Shape &w, const Shape &d, size_t scratch, PairPlan
   if (!gemm_tile_fits(w.M, w.N, w.K, true, false, SSDT_BF16) || !gemm_tile_fits(d.M, d.N, d.K, false, true, SSDT_BF16)) return false;
   if (gemm_large_fits(w.M, w.N, w.K, true, false, SSDT_BF16) || gemm_large_fits(d.M, d.N, d.K, false, true, SSDT_BF16)) return false;
   int c, sp;
-  const double alone = tile_plan(w.M, w.N, w.K, scratch, kCfgs, &c, &sp) + tile_plan(d.M, d.N, d.K, scratch, kCfgs, &c, &sp);
+  const double alone = tile_plan(w.M, w.N, w.K, scratch, kWide, &c, &sp) + tile_plan(d.M, d.N, d.K, scratch, kCfgs, &c, &sp);
   return pair_plan(w, d, scratch, out) < alone;
 }
 
@@ -744,7 +930,7 @@ static bool pair_wanted(const Shape &w, const Shape &d, size_t scratch, PairPlan
 size_t gemm_tile_scratch_bytes(int M, int N, int K, bool transA, bool transB, int dtype) {
   if (!gemm_tile_fits(M, N, K, transA, transB, dtype) || gemm_large_fits(M, N, K, transA, transB, dtype)) return 0;
   int cfg = 0, splits = 1;
-  tile_plan(M, N, K, ~(size_t)0, kCfgs, &cfg, &splits);
+  tile_plan(M, N, K, ~(size_t)0, transA ? kWide : kCfgs, &cfg, &splits);
   return split_bytes(M, N, splits);
 }
 size_t gemm_pair_scratch_bytes(int rows, int in, int out, int dtype) {
@@ -793,9 +979,10 @@ hipError_t gemm_mfma_tile_bf16(const Gemm &g, hipStream_t s) {
   hipError_t e = prepare(g, &p);
   if (e != hipSuccess) return e;
   int cfg = 0, splits = 1;
-  tile_plan(g.M, g.N, g.K, usable_scratch(g), g.ordered ? kOneOrder : kCfgs, &cfg, &splits);
-  if (g_tile_cfg >= 0) cfg = g_tile_cfg;
+  tile_plan(g.M, g.N, g.K, usable_scratch(g), g.ordered ? kOneOrder : g.transA ? kWide : kCfgs, &cfg, &splits);
+  if (g_tile_cfg >= 0 && !(g_tile_cfg == kWide && g.transA)) cfg = g_tile_cfg;
   if (g_tile_splits > 0 && split_bytes(g.M, g.N, g_tile_splits) <= g.scratch_bytes) splits = g_tile_splits;
+  if (cfg == kWide) splits = 1;
   choose(&p, cfg, splits, (float *)g.scratch);
   if (g.transA) return launch_cfg<true, true>(cfg, p, s);
   if (!g.transB) return launch_cfg<false, true>(cfg, p, s);
@@ -807,7 +994,7 @@ hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, hipStream_t s) {
   PairPlan pp;
   const size_t scratch = std::min(usable_scratch(w), usable_scratch(d));
   if (w.transA != true || w.transB || d.transA || !d.transB || w.dtype != SSDT_BF16 || d.dtype != SSDT_BF16) return hipErrorNotSupported;
-  if (w.scratch != d.scratch || !pair_wanted(Shape{w.M, w.N, w.K}, Shape{d.M, d.N, d.K}, scratch, &pp)) return hipErrorNotSupported;
+  if (g_tile_cfg == kWide || w.scratch != d.scratch || !pair_wanted(Shape{w.M, w.N, w.K}, Shape{d.M, d.N, d.K}, scratch, &pp)) return hipErrorNotSupported;
   hipError_t e = prepare(w, &pw);
   if (e == hipSuccess) e = prepare(d, &pd);
   if (e != hipSuccess) return e;

@@ -148,10 +148,10 @@ def test_every_bf16_tile_at_ragged_sizes(pin, tile, splits):
 
 # contractions of 1 and 2 stages of 64 (H 40, F 72, 111 tokens), of 4, 5, 6 and 10 (RAGGED), of 3, 9 and 25 (H 520, F 136)
 @pytest.mark.parametrize("size", [dict(B=3, S=37, H=40, A=1, F=72), RAGGED, dict(B=2, S=70, H=520, A=5, F=136)], ids=["1", "4", "9"])
-@pytest.mark.parametrize("tile", [3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("tile", [3, 4, 5, 6, 7, 8, 9])
 def test_every_ring_of_stages(pin, tile, size):
-    """Tiles whose stages stand in a ring of three or four, from 6 on with the wavefronts side by side along k (stages of 128): fewer
-    stages than the ring holds, as many, and more; whole and split."""
+    """Tiles whose stages stand in a ring of three or four, from 6 on with the wavefronts side by side along k (6 to 8: stages of 128;
+    9: 256 x 128, forward and input gradients): fewer stages than the ring holds, as many, and more; whole and split."""
     l = runner.Layer(dtype="bf16", **dict(GPT, **{k: size[k] for k in "BSHAF"}))
     case = hp.make_layer_case(l, 8420 + tile, bias_std=0.05)
     pin("g_tile_cfg", tile)
