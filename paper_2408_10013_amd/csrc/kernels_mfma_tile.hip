@@ -130,6 +130,26 @@ struct Side {
     left -= step;
     k += SK;
   }
+  // The same fragments from a lane's base of a step (k-major, a row of 256 bytes and more: the block is XOR-ed into it): one address
+  // register instead of one for each block.
+  static __device__ __forceinline__ unsigned base(int step, int lane) {
+    const int lr = lane & 15, lq = lane >> 4;
+    if (KM) return (unsigned)((step * 32 + 8 * lq + (lr >> 2)) * (ROWS * 2) + key(8 * lq + (lr >> 2)) * 32 + 8 * (lr & 3));
+    return (unsigned)(lr * (SK * 2) + ((4 * step + lq) ^ key(lr)) * 16);
+  }
+  static __device__ __forceinline__ bf16x8_t frag_from(unsigned base, unsigned lds, int blk) {
+    static_assert(!KM || ROWS >= 128, "a block's 32 bytes must be bits of their own");
+    if (KM) {
+      const lds_char_t *at = (const lds_char_t *)(uintptr_t)((base ^ (unsigned)(blk * 32)) + lds);
+      union { struct { s16x4_t a, b; } s; bf16x8_t v; } u;
+      u.s.a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)at);
+      u.s.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(at + 4 * ROWS * 2));
+      return u.v;
+    }
+    union { v4i_t a; bf16x8_t v; } u;
+    u.a = *(const lds_v4i_t *)(uintptr_t)(base + lds + (unsigned)(blk * 16 * SK * 2));
+    return u.v;
+  }
   // fragment of the 16-row block `blk`, 32-wide step `step`: 8 consecutive k of row (lane & 15) per lane
   static __device__ __forceinline__ bf16x8_t frag(unsigned lds, int blk, int step, int lane) {
     const int lr = lane & 15, lq = lane >> 4;
@@ -539,20 +559,19 @@ __device__ __forceinline__ void kwave_body(const TileP &p, int bid, uint16_t *sm
 // 4096 x 2048 x 8192 156 -> 136 us with a residual, K-contiguous 150 -> 129 (1.07 PFLOP/s; 145 at best by four-deep rings of 128 x
 // 128), 8192 x 1024 x 4096 81 -> 67, 4096 x 2048 x 2048 47 -> 39.  Both operands k-major only 103 -> 99: every fragment is two reads there.
 #define SSDT_FENCE __builtin_amdgcn_sched_barrier(0)
-template <bool BKM>
-__global__ __launch_bounds__(512) void gemm_wide_k(TileP p) {
+template <bool AKM, bool BKM>
+__device__ __forceinline__ void wide_body(const TileP &p, int bid, uint16_t *smem) {
   constexpr int BM = 256, BN = 128, NT = 512, R = 3, MB = 8, NB = 4;
-  typedef Side<BM, false, NT, kSK> SA;
+  typedef Side<BM, AKM, NT, kSK> SA;
   typedef Side<BN, BKM, NT, kSK> SB;
   constexpr unsigned kStage = SA::kBytes + SB::kBytes;
   constexpr int L = SA::LJ + SB::LJ;  // 4 + 2
-  extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), kg = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
   NtP q;  // tile_of looks at these only
   q.tiles_m = p.tiles_m; q.tiles_n = p.tiles_n; q.gm = p.gm;
   int tile_m, tile_n;
-  tile_of(q, blockIdx.x, &tile_m, &tile_n);
+  tile_of(q, bid, &tile_m, &tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN, nk = (p.K + kSK - 1) / kSK;
   SA sa;
   SB sb;
@@ -567,6 +586,9 @@ __global__ __launch_bounds__(512) void gemm_wide_k(TileP p) {
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   bf16x8_t Af[MB], Bf[2][NB];
+  // column sums of B, as in tile_body: the wavefronts of the first tile row with distinct fragments, in a loop of their own
+  const bool sum = AKM && BKM && p.colsum && tile_m == 0 && wm == 0;
+  float *psum = (float *)((char *)smem + R * kStage) + wn * 64;  // [half of k][wn][64] behind the stages
   auto load_all = [&](unsigned at, bool tail) {
     const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + at + wave * 1024);
     const v4i_t ra = sa.desc(), rb = sb.desc();
@@ -577,8 +599,9 @@ __global__ __launch_bounds__(512) void gemm_wide_k(TileP p) {
     sa.next();
     sb.next();
   };
-  auto rdA = [&](int i, unsigned at) { return SA::frag(lds0 + at, wm * MB + i, kg, lane); };
-  auto rdB = [&](int j, unsigned at) { return SB::frag(lds0 + at + SA::kBytes, wn * NB + j, kg, lane); };
+  unsigned ba = SA::base(kg, lane), bb = SB::base(kg, lane);
+  auto rdA = [&](int i, unsigned at) { return SA::frag_from(ba, lds0 + at, wm * MB + i); };
+  auto rdB = [&](int j, unsigned at) { return SB::frag_from(bb, lds0 + at + SA::kBytes, wn * NB + j); };
   auto mfma_block = [&](int i, int set, int j0, int j1) {
     SSDT_FENCE;
 #pragma unroll
@@ -588,12 +611,14 @@ __global__ __launch_bounds__(512) void gemm_wide_k(TileP p) {
   unsigned rd = kStage, wr = 0;  // where the next stage is, where the stage R further on goes: bytes of LDS
   auto advance = [&](unsigned x) { return x == (R - 1) * kStage ? 0u : x + kStage; };
   // stage st, in the registers but for what its own reads still bring; behind the barrier the next one is read
-  auto stage = [&](int st, int set, auto inner) {
+  auto stage = [&](int st, int set, auto inner, auto sum_block) {
     constexpr bool INNER = decltype(inner)::value;
     mfma_block(0, set, 0, NB);
+    sum_block(set);
     const bool more = INNER || st + 1 < nk, load = INNER || st + R < nk;
     if (more) wait_stages<L>(INNER ? R : nk - 2 - st, std::integral_constant<int, R - 2>());
     SSDT_FENCE;
+    asm volatile("" : "+v"(ba), "+v"(bb));  // (the blocks' addresses, kept from stage to stage, would not leave enough registers)
     v4i_t ra, rb;
     const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + wr + wave * 1024);
 #pragma unroll
@@ -624,14 +649,32 @@ __global__ __launch_bounds__(512) void gemm_wide_k(TileP p) {
   for (int j = 0; j < NB; ++j) Bf[0][j] = rdB(j, 0);
 #pragma unroll
   for (int i = 0; i < MB; ++i) Af[i] = rdA(i, 0);
-  int st = 0;
-  for (; st + 2 + R < nk; st += 2) {
-    stage(st, 0, std::true_type());
-    stage(st + 1, 1, std::true_type());
-  }
-  for (; st < nk; st += 2) {
-    stage(st, 0, std::false_type());
-    if (st + 1 < nk) stage(st + 1, 1, std::false_type());
+  auto stages = [&](auto sum_block) {
+    int st = 0;
+    for (; st + 2 + R < nk; st += 2) {
+      stage(st, 0, std::true_type(), sum_block);
+      stage(st + 1, 1, std::true_type(), sum_block);
+    }
+    for (; st < nk; st += 2) {
+      stage(st, 0, std::false_type(), sum_block);
+      if (st + 1 < nk) stage(st + 1, 1, std::false_type(), sum_block);
+    }
+  };
+  if (AKM && BKM && sum) {
+    f32x4_t accs[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) accs[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    stages([&](int set) {
+      union { unsigned w[4]; bf16x8_t v; } ones;
+      ones.w[0] = ones.w[1] = ones.w[2] = ones.w[3] = 0x3F803F80u;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) accs[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Bf[set][j], ones.v, accs[j], 0, 0, 0);
+    });
+    if (lr == 0)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) *(float4 *)(psum + kg * 128 + j * 16 + lq * 4) = make_float4(accs[j][0], accs[j][1], accs[j][2], accs[j][3]);
+  } else {
+    stages([](int) {});
   }
   // The two halves of the contraction: each wavefront keeps 64 of its 128 rows and hands the others to the wavefront that has the
   // other half of k, through that one's part of LDS; from there row by row, 16 bytes per lane.
@@ -655,6 +698,11 @@ __global__ __launch_bounds__(512) void gemm_wide_k(TileP p) {
       *(float4 *)(other + (il * 16 + lr) * LD + j * 16 + lq * 4) = make_float4(a[0], a[1], a[2], a[3]);
     }
   __syncthreads();
+  if (AKM && BKM && sum && !kg && lane < 16 && n0 + wn * 64 + lane * 4 < p.N) {
+    const float4 lo = *(const float4 *)(psum + lane * 4), hi = *(const float4 *)(psum + 128 + lane * 4);
+    float v[4] = {lo.x + hi.x, lo.y + hi.y, lo.z + hi.z, lo.w + hi.w};
+    store_colsum(p, n0 + wn * 64 + lane * 4, 0, v);
+  }
 #pragma unroll
   for (int il = 0; il < 4; ++il)
 #pragma unroll
@@ -672,6 +720,20 @@ __global__ __launch_bounds__(512) void gemm_wide_k(TileP p) {
     float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
     tile_epilogue8(p, v, m, n, ebias, ein[pass]);
   }
+}
+
+template <bool AKM, bool BKM>
+__global__ __launch_bounds__(512) void gemm_wide_k(TileP p) {
+  extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
+  wide_body<AKM, BKM>(p, blockIdx.x, smem);
+}
+// as gemm_tile_pair_k
+__global__ __launch_bounds__(512) void gemm_wide_pair_k(TileP w, TileP d, int first, int w_first) {
+  extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
+  const int bid = blockIdx.x;
+  const bool head = bid < first;
+  if (head == (w_first != 0)) wide_body<true, true>(w, head ? bid : bid - first, smem);
+  else wide_body<false, false>(d, head ? bid : bid - first, smem);
 }
 
 // KW: wavefronts along k
@@ -735,7 +797,7 @@ struct TileCfg { int bm, bn, ring, sk; };  // sk: k per stage, 128 with the wave
 static const TileCfg kCfg[] = {{128, 128, 2, 64}, {64, 128, 2, 64}, {64, 64, 2, 64}, {64, 128, 3, 64}, {64, 64, 3, 64}, {128, 128, 4, 64},
                                 {64, 64, 3, 128}, {32, 64, 3, 128}, {32, 32, 4, 128}, {256, 128, 3, 64}};
 constexpr int kCfgs = sizeof kCfg / sizeof kCfg[0];
-constexpr int kWide = kCfgs - 1;  // first operand K-contiguous, not split, alone in a launch
+constexpr int kWide = kCfgs - 1;  // not split
 constexpr int kOneOrder = 6;  // the first six add in the same order
 int g_tile_cfg = -1, g_tile_splits = 0;  // test hooks: >= 0 pins the tile, > 0 the number of splits (of a pair's input gradient: the tens, if any)
 
@@ -766,17 +828,30 @@ static hipError_t launch_tile(const TileP &p, hipStream_t s) {
   hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : launch_reduce(p, s);
 }
-template <bool BKM>
+constexpr size_t kWideLds = (size_t)3 * (256 + 128) * kSK * 2 + 4 * 64 * 4;  // stages (the partial tiles need less), column sums
+template <bool AKM, bool BKM>
 static hipError_t launch_wide(const TileP &p, hipStream_t s) {
-  constexpr size_t smem = (size_t)3 * (256 + 128) * kSK * 2;
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_wide_k<BKM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_wide_k<AKM, BKM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWideLds);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
   prof::Scope ps(prof::GEMM_MFMA_TILE, 2.0 * p.M * p.N * p.K, 0, s);
-  hipLaunchKernelGGL((gemm_wide_k<BKM>), dim3(p.tiles_m * p.tiles_n), dim3(512), smem, s, p);
+  hipLaunchKernelGGL((gemm_wide_k<AKM, BKM>), dim3(p.tiles_m * p.tiles_n), dim3(512), kWideLds, s, p);
+  return hipGetLastError();
+}
+static hipError_t launch_wide_pair(const TileP &w, const TileP &d, hipStream_t s) {
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_wide_pair_k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWideLds);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  prof::Scope ps(prof::GEMM_MFMA_TILE, 2.0 * w.M * w.N * w.K + 2.0 * d.M * d.N * d.K, 0, s);
+  const bool w_first = w.stages_per_split >= d.stages_per_split;
+  hipLaunchKernelGGL(gemm_wide_pair_k, dim3(blocks_of(w) + blocks_of(d)), dim3(512), kWideLds, s, w, d,
+                     (int)(w_first ? blocks_of(w) : blocks_of(d)), w_first ? 1 : 0);
   return hipGetLastError();
 }
 template <bool AKM, bool BKM>
@@ -791,9 +866,7 @@ static hipError_t launch_cfg(int cfg, const TileP &p, hipStream_t s) {
     case 6: return launch_tile<64, 64, 3, true, AKM, BKM>(p, s);
     case 7: return launch_tile<32, 64, 3, true, AKM, BKM>(p, s);
     case 8: return launch_tile<32, 32, 4, true, AKM, BKM>(p, s);
-    default:
-      if constexpr (AKM) return hipErrorInvalidValue;
-      else return launch_wide<BKM>(p, s);
+    default: return launch_wide<AKM, BKM>(p, s);
   }
 }
 template <int BM, int BN, int R, bool KW>
@@ -877,6 +950,25 @@ static const TileCost kPairCost[kWide] = {{0.69, 0.13, 0.497, 2.2, 2}, {0.454, 0
                                           {0.268, 0.121, 0.353, 1.68, 2}, {0.198, 0.112, 0.252, 0.354, 3}, {0.034, 0.6, 0.7, 3.9, 1},
                                           {0.19, 0.042, 0.302, 2.93, 1}, {0.117, 0.065, 0.147, 1.12, 2}, {0.073, 0.048, 0.139, 0.86, 2}};
 struct PairPlan { int cfg = 0, sw = 1, sd = 1; };
+// When `slots` workers are done that take n1 pieces of t1 each and then n2 of t2.
+static double deal(long n1, double t1, long n2, double t2, long slots) {
+  struct { double at; long n; } g[64] = {{0.0, slots}};  // workers by the time they are free
+  int groups = 1;
+  double end = 0;
+  for (int kind = 0; kind < 2; ++kind)
+    for (long rem = kind ? n2 : n1; rem > 0;) {
+      int i = 0;
+      for (int j = 1; j < groups; ++j)
+        if (g[j].at < g[i].at) i = j;
+      const double done = g[i].at + (kind ? t2 : t1);
+      const long n = std::min(rem, g[i].n);
+      rem -= n;
+      end = std::max(end, done);
+      if (n == g[i].n) g[i].at = done;
+      else if (groups < 64) { g[i].n -= n; g[groups].at = done; g[groups++].n = n; }
+    }
+  return end;
+}
 struct Shape { int M, N, K; };
 static size_t half_of(size_t scratch) { return scratch / 2 / 256 * 256; }
 static double pair_plan(const Shape &w, const Shape &d, size_t scratch, PairPlan *out) {
@@ -897,6 +989,19 @@ static double pair_plan(const Shape &w, const Shape &d, size_t scratch, PairPlan
         if (t < best * 0.98) { best = t; out->cfg = c; out->sw = sw; out->sd = sd; }
       }
     }
+  // Tiles of 256 x 128, one to a compute unit, where they are done before that: there and for unsplit 128 x 128 tiles, the other
+  // choice at such sizes, by dealing the tiles out (4096 x 2048 -> 6144 219 -> 201 us, predicted 222 and 212; 8192 x 1024 -> 4096
+  // 136 -> 124; 4096 x 2048 -> 2048 73 -> 67; 5785 x 2048 -> 2048 103 -> 95; but 3000 x 1536 -> 4608, taken too, 88 -> 98).
+  const auto dealt = [&](int c, long slots, double stage, double e) {
+    const long nw = tiles_of(w.M, w.N, c), nd = tiles_of(d.M, d.N, c);
+    const double tw = stages_of(w.K) * stage + e, td = stages_of(d.K) * stage + e;
+    return 2.7 + (stages_of(w.K) >= stages_of(d.K) ? deal(nw, tw, nd, td, slots) : deal(nd, td, nw, tw, slots));
+  };
+  if (tiles_of(w.M, w.N, kWide) + tiles_of(d.M, d.N, kWide) <= 2048) {
+    const double t = dealt(kWide, 256, 0.88, 4.0);
+    if (out->cfg == 0 && out->sw == 1 && out->sd == 1) best = dealt(0, 512, 0.95, 2.2);
+    if (t < best * 0.99) { best = t; out->cfg = kWide; out->sw = out->sd = 1; }
+  }
   return best;
 }
 
@@ -922,7 +1027,7 @@ static bool pair_wanted(const Shape &w, const Shape &d, size_t scratch, PairPlan
   if (!gemm_tile_fits(w.M, w.N, w.K, true, false, SSDT_BF16) || !gemm_tile_fits(d.M, d.N, d.K, false, true, SSDT_BF16)) return false;
   if (gemm_large_fits(w.M, w.N, w.K, true, false, SSDT_BF16) || gemm_large_fits(d.M, d.N, d.K, false, true, SSDT_BF16)) return false;
   int c, sp;
-  const double alone = tile_plan(w.M, w.N, w.K, scratch, kWide, &c, &sp) + tile_plan(d.M, d.N, d.K, scratch, kCfgs, &c, &sp);
+  const double alone = tile_plan(w.M, w.N, w.K, scratch, kCfgs, &c, &sp) + tile_plan(d.M, d.N, d.K, scratch, kCfgs, &c, &sp);
   return pair_plan(w, d, scratch, out) < alone;
 }
 
@@ -930,7 +1035,7 @@ static bool pair_wanted(const Shape &w, const Shape &d, size_t scratch, PairPlan
 size_t gemm_tile_scratch_bytes(int M, int N, int K, bool transA, bool transB, int dtype) {
   if (!gemm_tile_fits(M, N, K, transA, transB, dtype) || gemm_large_fits(M, N, K, transA, transB, dtype)) return 0;
   int cfg = 0, splits = 1;
-  tile_plan(M, N, K, ~(size_t)0, transA ? kWide : kCfgs, &cfg, &splits);
+  tile_plan(M, N, K, ~(size_t)0, kCfgs, &cfg, &splits);
   return split_bytes(M, N, splits);
 }
 size_t gemm_pair_scratch_bytes(int rows, int in, int out, int dtype) {
@@ -979,8 +1084,8 @@ hipError_t gemm_mfma_tile_bf16(const Gemm &g, hipStream_t s) {
   hipError_t e = prepare(g, &p);
   if (e != hipSuccess) return e;
   int cfg = 0, splits = 1;
-  tile_plan(g.M, g.N, g.K, usable_scratch(g), g.ordered ? kOneOrder : g.transA ? kWide : kCfgs, &cfg, &splits);
-  if (g_tile_cfg >= 0 && !(g_tile_cfg == kWide && g.transA)) cfg = g_tile_cfg;
+  tile_plan(g.M, g.N, g.K, usable_scratch(g), g.ordered ? kOneOrder : kCfgs, &cfg, &splits);
+  if (g_tile_cfg >= 0) cfg = g_tile_cfg;
   if (g_tile_splits > 0 && split_bytes(g.M, g.N, g_tile_splits) <= g.scratch_bytes) splits = g_tile_splits;
   if (cfg == kWide) splits = 1;
   choose(&p, cfg, splits, (float *)g.scratch);
@@ -994,7 +1099,7 @@ hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, hipStream_t s) {
   PairPlan pp;
   const size_t scratch = std::min(usable_scratch(w), usable_scratch(d));
   if (w.transA != true || w.transB || d.transA || !d.transB || w.dtype != SSDT_BF16 || d.dtype != SSDT_BF16) return hipErrorNotSupported;
-  if (g_tile_cfg == kWide || w.scratch != d.scratch || !pair_wanted(Shape{w.M, w.N, w.K}, Shape{d.M, d.N, d.K}, scratch, &pp)) return hipErrorNotSupported;
+  if (w.scratch != d.scratch || !pair_wanted(Shape{w.M, w.N, w.K}, Shape{d.M, d.N, d.K}, scratch, &pp)) return hipErrorNotSupported;
   hipError_t e = prepare(w, &pw);
   if (e == hipSuccess) e = prepare(d, &pd);
   if (e != hipSuccess) return e;
@@ -1003,6 +1108,7 @@ hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, hipStream_t s) {
     const int sw = g_tile_splits % 10, sd = g_tile_splits >= 10 ? g_tile_splits / 10 : sw;
     if (std::max(split_bytes(pw.M, pw.N, sw), split_bytes(pd.M, pd.N, sd)) <= half_of(scratch)) { pp.sw = sw; pp.sd = sd; }
   }
+  if (pp.cfg == kWide) pp.sw = pp.sd = 1;
   choose(&pw, pp.cfg, pp.sw, (float *)w.scratch);
   choose(&pd, pp.cfg, pp.sd, (float *)((char *)w.scratch + half_of(scratch)));
   switch (pp.cfg) {
@@ -1014,7 +1120,8 @@ hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, hipStream_t s) {
     case 5: return launch_pair<128, 128, 4, false>(pw, pd, s);
     case 6: return launch_pair<64, 64, 3, true>(pw, pd, s);
     case 7: return launch_pair<32, 64, 3, true>(pw, pd, s);
-    default: return launch_pair<32, 32, 4, true>(pw, pd, s);
+    case 8: return launch_pair<32, 32, 4, true>(pw, pd, s);
+    default: return launch_wide_pair(pw, pd, s);
   }
 }
 
