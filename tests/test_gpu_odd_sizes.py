@@ -151,13 +151,26 @@ def test_every_bf16_tile_at_ragged_sizes(pin, tile, splits):
 @pytest.mark.parametrize("tile", [3, 4, 5, 6, 7, 8, 9])
 def test_every_ring_of_stages(pin, tile, size):
     """Tiles whose stages stand in a ring of three or four, from 6 on with the wavefronts side by side along k (6 to 8: stages of 128;
-    9: 256 x 128, forward and input gradients): fewer stages than the ring holds, as many, and more; whole and split."""
+    9: 256 x 128): fewer stages than the ring holds, as many, and more; whole and split."""
     l = runner.Layer(dtype="bf16", **dict(GPT, **{k: size[k] for k in "BSHAF"}))
     case = hp.make_layer_case(l, 8420 + tile, bias_std=0.05)
     pin("g_tile_cfg", tile)
     for splits in (1, 2):
         pin("g_tile_splits", splits)
         check_against_oracle(l, case, run_single_layer(l, case, offload=False, fetch=False), hp.TOL["bf16"])
+
+
+@pytest.mark.parametrize("kind", ["t5_enc", "t5_dec"])
+@pytest.mark.parametrize("size", [dict(B=2, S=128, H=256, A=2, F=512), dict(B=8, S=128, H=1024, A=16, F=2560), dict(B=8, S=256, H=2048, A=32, F=4096)],
+                         ids=["256", "1024", "2048"])
+def test_relu_layers_of_whole_tiles_add_in_one_order(pin, kind, size):
+    """The output of a layer with ReLU, which the next layer's ReLU decides on, has the same bits whatever tile the products take by
+    themselves: those of 128 x 128 tiles (two decoder layers moved by 5 % with the MLP's products in another order)."""
+    l = runner.Layer(dtype="bf16", **dict(T5, arch=kind, act="relu", mask="none" if kind == "t5_enc" else "causal", S_kv=0 if kind == "t5_enc" else 128, **size))
+    case = hp.make_layer_case(l, 8460, bias_std=0.05)
+    own = run_single_layer(l, case, offload=False, fetch=False)["y"]
+    pin("g_tile_cfg", 0)
+    assert np.array_equal(own, run_single_layer(l, case, offload=False, fetch=False)["y"])
 
 
 # stages of 64 k (tile 32) or 32 (tile 64): 1 and 2 of either, as many as the ring holds, and more; widths that end inside a tile
