@@ -54,7 +54,8 @@ struct Gemm {
   // whose result is rounded to bf16 on the way there makes a difference of 2^-24 into one of 2^-9 wherever a rounding tips
   // over, and every further rounding spreads it: two orders of addition, equally far from the exact result (4 to 5 %), lie
   // up to 4 % apart at width 4096.  The pre-activation's own product tips one sign in 10^7 and the one behind it none: with
-  // those two in any order the gradients move by 0.3 % at most (22 layers, widths 128 to 4096, 45 to 2800 tokens).
+  // those two in any order the gradients move by 0.3 % at most (22 layers, widths 128 to 4096, 45 to 2800 tokens).  The layer
+  // behind decides on their result, though (a stack of four layers: 5 %): at whole tiles the order holds for these two as well.
   bool ordered = false;
 };
 hipError_t gemm(const Gemm &g, hipStream_t s);

@@ -202,7 +202,7 @@ ssdt_status ssdt_layer_fwd(ssdt_ctx *ctx, const ssdt_layer_desc *desc, const ssd
   // decides: the output reaches a ReLU's pre-activation of this layer through further roundings to bf16 (see Gemm::ordered); the
   // MLP's own two products do not, and at ragged sizes go by the bf16 kernels instead of at the fp32 rate (7 x 333 tokens, H 4096, F
   // 10240 7971 -> 5245 us forward + backward, 3 x 263, H 1536, F 6144 804 -> 532).  But they reach the ReLU of the layer behind:
-  // at whole tiles, where the order costs no more than a choice of tile (T5 decoder layer 8 x 128, H 2048: see kOneOrder), they keep it.
+  // at whole tiles, where the order costs no more than a choice of tile (T5 decoder layer 8 x 128, H 2048: 795 us against 791), they keep it.
   auto linear = [&](const void *in, int M, int K, const void *W, const void *bias, int N, void *out, int epi,
                     const void *resid, void *out2, bool decides = true) {
     k::Gemm g;
