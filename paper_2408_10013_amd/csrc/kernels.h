@@ -47,15 +47,17 @@ struct Gemm {
   void *scratch = nullptr;      // optional: room for transposed copies of operands, or for partial products (bf16)
   size_t scratch_bytes = 0;
   bool split = false;           // the contraction may be split over workgroups (another order of the fp32 additions)
-  // bf16, every size that is not whole tiles of 128 x 128 x 64: fp32 additions with k ascending, whatever kernel runs (at whole
-  // tiles: in the one order that the tiles with 64 k a stage and the 256 x 256 kernels have).
-  // For the forward products of layers with ReLU up to the one that sums the pre-activation.  A pre-activation near zero
-  // changes sides with the last bit of what it was summed from, and with it a whole column of the gradients.  A product
-  // whose result is rounded to bf16 on the way there makes a difference of 2^-24 into one of 2^-9 wherever a rounding tips
-  // over, and every further rounding spreads it: two orders of addition, equally far from the exact result (4 to 5 %), lie
-  // up to 4 % apart at width 4096.  The pre-activation's own product tips one sign in 10^7 and the one behind it none: with
-  // those two in any order the gradients move by 0.3 % at most (22 layers, widths 128 to 4096, 45 to 2800 tokens).  The layer
-  // behind decides on their result, though (a stack of four layers: 5 %): at whole tiles the order holds for these two as well.
+  // The forward products of layers with ReLU, bf16.  A pre-activation near zero changes sides with the last bit of what it was
+  // summed from, and with it a whole column of the gradients.  A product whose result is rounded to bf16 on the way there
+  // makes a difference of 2^-24 into one of 2^-9 wherever a rounding tips over, and every further rounding spreads it: two
+  // orders of addition, equally far from the exact result (4 to 5 %), lie up to 4 % apart at width 4096.
+  // one_order: all of them.  Among the bf16 kernels only those that add like gemm_tile_k's tiles with 64 k a stage, so that the
+  // bits do not hang on the choice of a tile.  (The 256 x 256 kernels add like them too, but where gemm_km256_k staggers its
+  // loop over k, N >= 16384 and K <= 8192: there each XCD starts elsewhere.)
+  bool one_order = false;
+  // ordered: the ones in front of the pre-activation's own.  At every size that is not whole tiles of 128 x 128 x 64: k ascending,
+  // whatever kernel runs.  The pre-activation's product tips one sign in 10^7 and the one behind it none: with these two in
+  // any order the gradients of a layer move by 0.3 % at most (22 layers, widths 128 to 4096, 45 to 2800 tokens).
   bool ordered = false;
 };
 hipError_t gemm(const Gemm &g, hipStream_t s);

@@ -404,7 +404,7 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
 
 // The same with the wavefronts side by side along k: a stage is 128 k, wavefront w takes its 32-wide step w on the whole tile,
 // and the four partial tiles are added through LDS at the end, in the order of the wavefronts (another order of additions than
-// tile_body's: not where that one is to be kept, see Gemm::ordered).
+// tile_body's: not where that one is to be kept, see Gemm::one_order).
 template <int BM, int BN, int R, bool AKM, bool BKM>
 __device__ __forceinline__ void kwave_body(const TileP &p, int bid, uint16_t *smem) {
   constexpr int NT = 256, SK = 128, TM = BM / 16, TN = BN / 16;
@@ -1091,7 +1091,7 @@ hipError_t gemm_mfma_tile_bf16(const Gemm &g, hipStream_t s) {
   hipError_t e = prepare(g, &p);
   if (e != hipSuccess) return e;
   int cfg = 0, splits = 1;
-  tile_plan(g.M, g.N, g.K, usable_scratch(g), g.ordered ? kOneOrder : kCfgs, &cfg, &splits);
+  tile_plan(g.M, g.N, g.K, usable_scratch(g), g.one_order ? kOneOrder : kCfgs, &cfg, &splits);
   if (g_tile_cfg >= 0) cfg = g_tile_cfg;
   if (g_tile_splits > 0 && split_bytes(g.M, g.N, g_tile_splits) <= g.scratch_bytes) splits = g_tile_splits;
   if (cfg == kWide) splits = 1;

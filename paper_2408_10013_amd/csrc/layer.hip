@@ -199,16 +199,17 @@ ssdt_status ssdt_layer_fwd(ssdt_ctx *ctx, const ssdt_layer_desc *desc, const ssd
   auto norm = [&](const void *in, const void *g, const void *b, void *out, float *mean, float *rstd) {
     return k::norm_fwd(in, g, b, out, D.ln ? mean : nullptr, rstd, D.T, D.H, desc->eps, desc->norm, dt, st);
   };
-  // decides: the output reaches a ReLU's pre-activation of this layer through further roundings to bf16 (see Gemm::ordered); the
+  // decides: the output reaches a ReLU's pre-activation of this layer through further roundings to bf16 (see Gemm::ordered).  The
   // MLP's own two products do not, and at ragged sizes go by the bf16 kernels instead of at the fp32 rate (7 x 333 tokens, H 4096, F
-  // 10240 7971 -> 5245 us forward + backward, 3 x 263, H 1536, F 6144 804 -> 532).  But they reach the ReLU of the layer behind:
-  // at whole tiles, where the order costs no more than a choice of tile (T5 decoder layer 8 x 128, H 2048: 795 us against 791), they keep it.
+  // 10240 7971 -> 5245 us forward + backward, 3 x 263, H 1536, F 6144 804 -> 532).  But the ReLU of the layer behind decides on their
+  // result: by tiles that add in another order the gradients of two encoder and two decoder layers move by 5 % at whole tiles
+  // (8 x 128, H 2048) and 1 to 3.5 % at ragged ones (3 x 197, H 512 to 5 x 131, H 2048), so the order is theirs too.
   auto linear = [&](const void *in, int M, int K, const void *W, const void *bias, int N, void *out, int epi,
                     const void *resid, void *out2, bool decides = true) {
     k::Gemm g;
     g.M = M; g.N = N; g.K = K; g.A = in; g.lda = K; g.B = W; g.ldb = N; g.transB = false; g.C = out; g.ldc = N;
     g.epi = epi; g.bias = bias; g.resid = resid; g.ldr = N; g.C2 = out2; g.act = desc->act; g.dtype = dt;
-    g.scratch = ws; g.scratch_bytes = ws_bytes; g.ordered = !D.gelu && (decides || (M % 128 == 0 && N % 128 == 0 && K % 64 == 0));
+    g.scratch = ws; g.scratch_bytes = ws_bytes; g.one_order = !D.gelu; g.ordered = !D.gelu && decides;
     return k::gemm(g, st);
   };
   auto attention = [&](const void *q, long ldq, const void *kk, const void *v, long ldkv, int Sq, int Sk, int mask,

@@ -12,6 +12,7 @@ from paper_2408_10013_amd import binding as sb
 from paper_2408_10013_amd import runner, synth
 
 import helpers as hp
+import test_gpu_stack as ts
 from test_gpu_layer import check_against_oracle, run_single_layer
 
 pytestmark = pytest.mark.gpu
@@ -70,7 +71,8 @@ def test_attention_of_any_length_and_head_size(name, dtype):
     check_against_oracle(l, case, on, hp.TOL[dtype])
 
 
-# ReLU: at lengths or widths that are not whole tiles the forward keeps the order of additions of the FMA kernels, in bf16 too
+# ReLU: at lengths or widths that are not whole tiles the forward keeps the order of additions of the FMA kernels, in bf16 too, but
+# for the MLP's two products, which have the one order of the bf16 tiles with 64 k a stage
 RELU = {
     "d12": dict(T5, act="relu", B=2, S=37, S_kv=45, H=36, A=3, F=52),           # K-contiguous rows element by element; heads
     "d20_enc": dict(T5, arch="t5_enc", mask="none", act="relu", B=2, S=70, H=60, A=3, F=72),  # that end inside a 16-byte load
@@ -171,6 +173,55 @@ def test_relu_layers_of_whole_tiles_add_in_one_order(pin, kind, size):
     own = run_single_layer(l, case, offload=False, fetch=False)["y"]
     pin("g_tile_cfg", 0)
     assert np.array_equal(own, run_single_layer(l, case, offload=False, fetch=False)["y"])
+
+
+# by themselves these products take the wavefronts along k (the first three) and 256 x 128 tiles (the last)
+RAGGED_RELU = {
+    "45x256": dict(T5, arch="t5_enc", mask="none", act="relu", B=3, S=15, H=256, A=4, F=1024),
+    "200x512": dict(T5, act="relu", B=2, S=100, S_kv=77, H=512, A=8, F=1280),
+    "655x1024": dict(T5, act="relu", B=5, S=131, S_kv=60, H=1024, A=16, F=2560),
+    "3000x2048": dict(T5, arch="t5_enc", mask="none", act="relu", B=3, S=1000, H=2048, A=16, F=8192),
+}
+
+
+@pytest.mark.parametrize("name", list(RAGGED_RELU))
+def test_relu_layers_of_ragged_sizes_add_in_one_order(pin, name):
+    """As above, and the layer behind decides as much as at whole tiles."""
+    l = runner.Layer(dtype="bf16", **RAGGED_RELU[name])
+    case = hp.make_layer_case(l, 8465, bias_std=0.05)
+    own = run_single_layer(l, case, offload=False, fetch=False)["y"]
+    for tile in (0, 4):
+        pin("g_tile_cfg", tile)
+        assert np.array_equal(own, run_single_layer(l, case, offload=False, fetch=False)["y"])
+
+
+def test_ragged_relu_stack(pin):
+    """Two encoder and two decoder layers: every layer's output has the bits of 128 x 128 tiles; outputs and gradients against the
+    checker, ReLU's decisions taken from the stored activations."""
+    kw = dict(T5, act="relu", dtype="bf16", B=3, H=256, A=4, F=512)
+    mk = lambda: [runner.Layer(**dict(kw, arch="t5_enc", mask="none", S=111)) for _ in range(2)] + [runner.Layer(**kw, S=67, S_kv=111) for _ in range(2)]
+    layers = mk()
+    cases = [hp.make_layer_case(l, 8470 + i, bias_std=0.05) for i, l in enumerate(layers)]
+    x, dy, enc_x = (runner.to_device(a, "bf16", "cuda:0") for a in (cases[2]["x"], cases[2]["dy"], cases[0]["x"]))
+    per = max(runner.saved_bytes_per_layer(l) for l in layers)
+    caps = []
+    for tile in (-1, 0):
+        pin("g_tile_cfg", tile)
+        ls = mk()
+        st = ts.build(ls, cases, 8 * per, 6 * per, keep_last=1, min_offload_elems=0, budget_bytes=0)
+        y, dx, dxe, grads = ts.run_gpu(st, ls, x, dy, enc_x=enc_x, capture=True)[:4]
+        caps.append(st.capture)
+        if tile < 0:
+            relu_g = {i: runner.to_host(t) for i, t in st.capture["g"].items()}
+            got = dict(y=y, dx=dx, dx_enc=dxe, **{"l%d.%s" % (i, k): v for i, g in enumerate(grads) for k, v in g.items()})
+            got = {k: runner.to_host(v) for k, v in got.items()}
+        st.close()
+    for i in range(4):
+        assert torch.equal(caps[0]["y"][i], caps[1]["y"][i]), i
+    y_ref, dx_ref, dxe_ref, g_ref = ts.oracle_stack(layers, cases, cases[2]["x"], cases[2]["dy"], enc_x=cases[0]["x"], relu_g=relu_g)
+    ref = dict(y=y_ref, dx=dx_ref, dx_enc=dxe_ref, **{"l%d.%s" % (i, k): v for i, g in enumerate(g_ref) for k, v in g.items()})
+    bad = {k: e for k, e in ((k, hp.rel_err(got[k], ref[k])) for k in ref) if not e <= hp.TOL["bf16"]}
+    assert not bad, bad
 
 
 # stages of 64 k (tile 32) or 32 (tile 64): 1 and 2 of either, as many as the ring holds, and more; widths that end inside a tile
