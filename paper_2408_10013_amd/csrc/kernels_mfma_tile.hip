@@ -17,6 +17,7 @@
 // Against the form this replaces (128 x 128 tiles, register-staged, operands brought to the K-contiguous form by
 // transposed copies): 4096 x 2048 x 8192 211 -> 137 us, 1024 x 2048 x 2048 45 -> 17, 1024 x 1024 x 8192 150 -> 33.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <type_traits>
 
@@ -799,12 +800,17 @@ static const TileCfg kCfg[] = {{128, 128, 2, 64}, {64, 128, 2, 64}, {64, 64, 2, 
 constexpr int kCfgs = sizeof kCfg / sizeof kCfg[0];
 constexpr int kWide = kCfgs - 1;  // not split
 constexpr int kOneOrder = 6;  // the first six add in the same order
-int g_tile_cfg = -1, g_tile_splits = 0;  // test hooks: >= 0 pins the tile, > 0 the number of splits (of a pair's input gradient: the tens, if any)
+// Test hooks: >= 0 pins the tile, > 0 the number of splits (of a pair's input gradient: the tens, if any; workspaces are reported with
+// room for them); launches of tile_reduce_k so far.
+int g_tile_cfg = -1, g_tile_splits = 0;
+std::atomic<int> g_tile_reduces{0};
+static int pinned_splits(bool input_grad) { return input_grad && g_tile_splits >= 10 ? g_tile_splits / 10 : g_tile_splits % 10; }
 
 static hipError_t launch_reduce(const TileP &p, hipStream_t s) {
   if (p.splits == 1) return hipSuccess;
   const long items = (long)p.M * (p.N / 8) + (p.colsum ? p.N / 8 : 0);
   hipLaunchKernelGGL(tile_reduce_k, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, p);
+  g_tile_reduces.fetch_add(1, std::memory_order_relaxed);
   return hipGetLastError();
 }
 static unsigned blocks_of(const TileP &p) { return (unsigned)(p.tiles_m * p.tiles_n * p.splits); }
@@ -1043,13 +1049,14 @@ size_t gemm_tile_scratch_bytes(int M, int N, int K, bool transA, bool transB, in
   if (!gemm_tile_fits(M, N, K, transA, transB, dtype) || gemm_large_fits(M, N, K, transA, transB, dtype)) return 0;
   int cfg = 0, splits = 1, one_order = 1;
   tile_plan(M, N, K, ~(size_t)0, kCfgs, &cfg, &splits, &one_order);
-  return split_bytes(M, N, std::max(splits, one_order));
+  return split_bytes(M, N, std::max({splits, one_order, pinned_splits(transB)}));
 }
 size_t gemm_pair_scratch_bytes(int rows, int in, int out, int dtype) {
   PairPlan pp;
   const Shape w{in, out, rows}, d{rows, in, out};
   if (dtype != SSDT_BF16 || !pair_wanted(w, d, ~(size_t)0, &pp)) return 0;
-  return 2 * std::max(split_bytes(w.M, w.N, std::max(pp.sw, pp.one_order_sw)), split_bytes(d.M, d.N, std::max(pp.sd, pp.one_order_sd))) + 512;
+  return 2 * std::max(split_bytes(w.M, w.N, std::max({pp.sw, pp.one_order_sw, pinned_splits(false)})),
+                      split_bytes(d.M, d.N, std::max({pp.sd, pp.one_order_sd, pinned_splits(true)}))) + 512;
 }
 
 // Checks what the kernel needs beyond the shape and fills its arguments, the choice of tile aside.
@@ -1093,7 +1100,7 @@ hipError_t gemm_mfma_tile_bf16(const Gemm &g, hipStream_t s) {
   int cfg = 0, splits = 1;
   tile_plan(g.M, g.N, g.K, usable_scratch(g), g.one_order ? kOneOrder : kCfgs, &cfg, &splits);
   if (g_tile_cfg >= 0) cfg = g_tile_cfg;
-  if (g_tile_splits > 0 && split_bytes(g.M, g.N, g_tile_splits) <= g.scratch_bytes) splits = g_tile_splits;
+  if (g_tile_splits > 0 && split_bytes(g.M, g.N, pinned_splits(g.transB)) <= g.scratch_bytes) splits = pinned_splits(g.transB);
   if (cfg == kWide) splits = 1;
   choose(&p, cfg, splits, (float *)g.scratch);
   if (g.transA) return launch_cfg<true, true>(cfg, p, s);
@@ -1112,7 +1119,7 @@ hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, hipStream_t s) {
   if (e != hipSuccess) return e;
   if (g_tile_cfg >= 0) pp.cfg = g_tile_cfg;
   if (g_tile_splits > 0) {
-    const int sw = g_tile_splits % 10, sd = g_tile_splits >= 10 ? g_tile_splits / 10 : sw;
+    const int sw = pinned_splits(false), sd = pinned_splits(true);
     if (std::max(split_bytes(pw.M, pw.N, sw), split_bytes(pd.M, pd.N, sd)) <= half_of(scratch)) { pp.sw = sw; pp.sd = sd; }
   }
   if (pp.cfg == kWide) pp.sw = pp.sd = 1;

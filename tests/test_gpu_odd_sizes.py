@@ -119,13 +119,28 @@ def test_relu_forward_products_add_in_the_order_of_k(H, A):
     assert np.array_equal(saved["qkv"], synth.bf16_round(acc))
 
 
+def hook(name):
+    return ctypes.c_int.in_dll(sb.lib(), "_ZN4ssdt1k%d%sE" % (len(name), name))
+
+
+def split_products(l, tile, splits, passes=1):
+    """How many of a bf16 layer's products are split where a tile and a number of splits are pinned: those with a stage for a second
+    part; in the forward, if the workspace that was reported holds the parts."""
+    ws, stage, n = max(sb.ssdt_layer_workspace(l.desc)), 128 if tile in (6, 7, 8) else 64, 0
+    parts = lambda k: -(-(s := -(-k // stage)) // -(-s // splits))
+    for rows, i, o in ((l.T, l.H, 3 * l.H), (l.T, l.H, l.H), (l.T, l.H, l.F), (l.T, l.F, l.H)):
+        n += parts(i) > 1 and splits * (rows + 1) * o * 4 <= ws
+        n += passes * ((parts(rows) > 1) + (parts(o) > 1))
+    return n if tile != 9 else 0
+
+
 @pytest.fixture
 def pin():
     """Sets a kernel's test hook for the time of a test."""
     was = []
 
     def set_(name, value):
-        v = ctypes.c_int.in_dll(sb.lib(), "_ZN4ssdt1k%d%sE" % (len(name), name))
+        v = hook(name)
         was.append((v, v.value))
         v.value = value
     yield set_
@@ -145,7 +160,9 @@ def test_every_bf16_tile_at_ragged_sizes(pin, tile, splits):
     pin("g_tile_splits", splits)
     l = runner.Layer(dtype="bf16", **RAGGED)
     case = hp.make_layer_case(l, 8400 + tile, bias_std=0.05)
+    before = hook("g_tile_reduces").value
     check_against_oracle(l, case, run_single_layer(l, case, offload=False, fetch=False), hp.TOL["bf16"])
+    assert hook("g_tile_reduces").value - before == split_products(l, tile, splits) == (12 if splits > 1 else 0)
 
 
 # contractions of 1 and 2 stages of 64 (H 40, F 72, 111 tokens), of 4, 5, 6 and 10 (RAGGED), of 3, 9 and 25 (H 520, F 136)
@@ -157,9 +174,12 @@ def test_every_ring_of_stages(pin, tile, size):
     l = runner.Layer(dtype="bf16", **dict(GPT, **{k: size[k] for k in "BSHAF"}))
     case = hp.make_layer_case(l, 8420 + tile, bias_std=0.05)
     pin("g_tile_cfg", tile)
-    for splits in (1, 2):
+    for splits in (1, 2) if tile != 9 else (1,):
         pin("g_tile_splits", splits)
+        before = hook("g_tile_reduces").value
         check_against_oracle(l, case, run_single_layer(l, case, offload=False, fetch=False), hp.TOL["bf16"])
+        done = hook("g_tile_reduces").value - before
+        assert done == split_products(l, tile, splits) and (done > 0) == (splits > 1 and (l.H > 40 or tile < 6))
 
 
 @pytest.mark.parametrize("kind", ["t5_enc", "t5_dec"])
@@ -284,16 +304,20 @@ def run_backward(l, case, x=None, dx=None, passes=1):
     return res
 
 
-@pytest.mark.parametrize("tile", [-1, 0])
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_split_products_add_to_what_the_gradients_hold(pin, dtype, tile):
-    """1665 tokens, 64 x 128 weights: the contraction over tokens is split in bf16, and a second backward adds to the gradients
-    in the reduction's epilogue, bias sums included."""
-    if tile >= 0:
-        pin("g_tile_cfg", tile)
+@pytest.mark.parametrize("dtype,tile,splits", [("f32", -1, 0), ("bf16", -1, 0)] + [("bf16", t, 1) for t in range(10)] +
+                         [("bf16", t, 4) for t in range(9)])
+def test_split_products_add_to_what_the_gradients_hold(pin, dtype, tile, splits):
+    """1665 tokens, 64 x 128 weights: a second backward adds to the gradients, bias sums included, in the product's own epilogue
+    or, where the contraction over tokens is split, in the reduction's."""
+    pin("g_tile_cfg", tile)
+    pin("g_tile_splits", splits)
     l = runner.Layer(dtype=dtype, **GPT, **SIZES["split_tokens"])
     case = hp.make_layer_case(l, 8600, bias_std=0.05)
+    before = hook("g_tile_reduces").value
     res = run_backward(l, case, passes=2)
+    if tile >= 0:
+        done = hook("g_tile_reduces").value - before
+        assert done == split_products(l, tile, splits, passes=2) and (done >= 8) == (splits > 1)
     res["grads"] = {k: v.float() / 2 for k, v in res["grads"].items()}   # (exact)
     check_against_oracle(l, case, res, hp.TOL[dtype])
 
