@@ -937,11 +937,9 @@ static size_t split_bytes(int M, int N, int splits) { return splits > 1 ? (size_
 static bool split_ok(int K, int splits) { return splits == 1 || splits * 4 <= stages_of(K); }
 
 // The choice for a problem given `scratch` bytes for partial products, among the first `cfgs` tiles; returns its predicted time.
-// one_order: set to the splits of the choice among the tiles of one order.
-static double tile_plan(int M, int N, int K, size_t scratch, int cfgs, int *cfg, int *splits, int *one_order = nullptr) {
+static double tile_plan(int M, int N, int K, size_t scratch, int cfgs, int *cfg, int *splits) {
   double best = 1e30;
   for (int c = 0; c < cfgs; ++c) {
-    if (c == kOneOrder && one_order) *one_order = *splits;
     for (int sp = 1; sp <= (c == kWide ? 1 : kMaxSplits) && split_ok(K, sp); sp *= 2) {
       if (split_bytes(M, N, sp) > scratch) break;
       const double t = tile_cost(M, N, K, c, sp);
@@ -958,7 +956,7 @@ static double tile_plan(int M, int N, int K, size_t scratch, int cfgs, int *cfg,
 static const TileCost kPairCost[kWide] = {{0.69, 0.13, 0.497, 2.2, 2}, {0.454, 0.155, 0.354, 0.73, 3}, {0.376, 0.068, 0.206, 0.6, 5},
                                           {0.268, 0.121, 0.353, 1.68, 2}, {0.198, 0.112, 0.252, 0.354, 3}, {0.034, 0.6, 0.7, 3.9, 1},
                                           {0.19, 0.042, 0.302, 2.93, 1}, {0.117, 0.065, 0.147, 1.12, 2}, {0.073, 0.048, 0.139, 0.86, 2}};
-struct PairPlan { int cfg = 0, sw = 1, sd = 1, one_order_sw = 1, one_order_sd = 1; };
+struct PairPlan { int cfg = 0, sw = 1, sd = 1; };
 // When `slots` workers are done that take n1 pieces of t1 each and then n2 of t2.
 static double deal(long n1, double t1, long n2, double t2, long slots) {
   struct { double at; long n; } g[64] = {{0.0, slots}};  // workers by the time they are free
@@ -984,7 +982,6 @@ static double pair_plan(const Shape &w, const Shape &d, size_t scratch, PairPlan
   const size_t half = half_of(scratch);
   double best = 1e30;
   for (int c = 0; c < kWide; ++c) {
-    if (c == kOneOrder) { out->one_order_sw = out->sw; out->one_order_sd = out->sd; }
     for (int sw = 1; sw <= kMaxSplits && split_ok(w.K, sw); sw *= 2) {
       if (split_bytes(w.M, w.N, sw) > half) break;
       for (int sd = 1; sd <= kMaxSplits && split_ok(d.K, sd); sd *= 2) {
@@ -1042,21 +1039,19 @@ static bool pair_wanted(const Shape &w, const Shape &d, size_t scratch, PairPlan
   return pair_plan(w, d, scratch, out) < alone;
 }
 
-// Scratch that the best choices would use: a problem alone, and a linear's two backward products (rows tokens, in -> out); and no
-// less than the best among the tiles of one order would, so that what is reported for a small layer, whose wavefronts now stand along k
-// instead of its contraction being split, has not become less than what callers may have set aside and counted on.
+// Scratch that the choices use where there is enough of it: a problem alone, and a linear's two backward products (rows tokens, in -> out).
 size_t gemm_tile_scratch_bytes(int M, int N, int K, bool transA, bool transB, int dtype) {
   if (!gemm_tile_fits(M, N, K, transA, transB, dtype) || gemm_large_fits(M, N, K, transA, transB, dtype)) return 0;
-  int cfg = 0, splits = 1, one_order = 1;
-  tile_plan(M, N, K, ~(size_t)0, kCfgs, &cfg, &splits, &one_order);
-  return split_bytes(M, N, std::max({splits, one_order, pinned_splits(transB)}));
+  int cfg = 0, splits = 1;
+  tile_plan(M, N, K, ~(size_t)0, kCfgs, &cfg, &splits);
+  return split_bytes(M, N, std::max(splits, pinned_splits(transB)));
 }
 size_t gemm_pair_scratch_bytes(int rows, int in, int out, int dtype) {
   PairPlan pp;
   const Shape w{in, out, rows}, d{rows, in, out};
   if (dtype != SSDT_BF16 || !pair_wanted(w, d, ~(size_t)0, &pp)) return 0;
-  return 2 * std::max(split_bytes(w.M, w.N, std::max({pp.sw, pp.one_order_sw, pinned_splits(false)})),
-                      split_bytes(d.M, d.N, std::max({pp.sd, pp.one_order_sd, pinned_splits(true)}))) + 512;
+  return 2 * std::max(split_bytes(w.M, w.N, std::max(pp.sw, pinned_splits(false))),
+                      split_bytes(d.M, d.N, std::max(pp.sd, pinned_splits(true)))) + 512;
 }
 
 // Checks what the kernel needs beyond the shape and fills its arguments, the choice of tile aside.

@@ -30,10 +30,16 @@ def test_backward_workspace_stays_within_the_static_one(case):
     assert bwd <= 64 << 20
 
 
-# (bytes: what ssdt_layer_workspace reported for the backward before products were split)
+def test_no_room_is_reported_for_splits_that_do_not_happen():
+    """2 x 128 tokens, H 256: no product is split (buffers, column sums and, for operands that are not aligned, a transposed copy)."""
+    l = runner.Layer(**dict(GPT, dtype="bf16", B=2, S=128, H=256, A=2, F=1024))
+    assert sb.ssdt_layer_workspace(l.desc)[1] == 1986816
+
+
+# Layers whose backward is split further if the workspace has room for it, and the bytes that it takes without
 SMALL = [
-    (dict(GPT, dtype="bf16", B=2, S=128, H=256, A=2, F=1024), 2003200),
-    (dict(T5_DEC, act="gelu", dtype="bf16", B=2, S=200, S_kv=700, H=256, A=4, F=512), 6075136),
+    (dict(GPT, dtype="bf16", B=32, S=128, H=256, A=2, F=1024), 31784960),
+    (dict(T5_DEC, act="gelu", dtype="bf16", B=32, S=128, S_kv=100, H=256, A=4, F=1024), 36765696),
 ]
 
 
@@ -54,10 +60,16 @@ def test_backward_takes_a_workspace_without_room_for_partial_products(case, nbyt
     dx = torch.empty_like(dy)
     sb.ssdt_step_begin(st.ctx, 1)
     y, saved = sb.ssdt_layer_fwd(st.ctx, l.desc, l.wstruct, 0, x.data_ptr(), ptr(enc), 0, st.ws_ptr, st.ws_bytes, st.stream)
+    sb.ssdt_layer_bwd(st.ctx, l.desc, l.wstruct, saved, 0, dy.data_ptr(), dx.data_ptr(), ptr(d_enc), l.gstruct, st.ws_ptr, st.ws_bytes,
+                      st.stream)
+    with_room = {k: v.clone() for k, v in l.g.items()}
+    if d_enc is not None:
+        d_enc.zero_()
     sb.ssdt_layer_bwd(st.ctx, l.desc, l.wstruct, saved, 0, dy.data_ptr(), dx.data_ptr(), ptr(d_enc), l.gstruct, guard.data_ptr(),
                       nbytes, st.stream)
     torch.cuda.synchronize()
     assert bool((guard[nbytes:] == 0xA5).all())
+    assert any(not torch.equal(with_room[k], v) for k, v in l.g.items())     # (the other order of additions)
     res = dict(y=runner.to_host(st.view(y, (l.T, l.H))), dx=dx, d_enc=d_enc, grads=l.g)
     st.close()
     check_against_oracle(l, c, res, hp.TOL[l.dtype])
