@@ -899,39 +899,64 @@ bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
   return !(transA && transB);  // (the layer has no such product)
 }
 
-// DISPATCH.  Predicted time of a problem in microseconds, fitted to what the tiles were measured to take (MI355X, 78 products
-// of a layer's forms with 128 to 4096 rows; the choice is within 4 % of the best tile for nine in ten of them).  A launch
-// takes 2.5 us and e for each tile of a compute unit.  Whole rounds of as many workgroups as fit take c for each of a unit's
+// DISPATCH.  Predicted time of a problem in microseconds, fitted to what the products of 470 layers took inside the layer, weights and
+// activations where the layer has them (MI355X; 32 to 16000 tokens, widths 128 to 4200): 2288 products by themselves and 1476
+// linears' backwards, every tile and split.  The choice costs 1.3 % more than the best tile on average, a linear's backward 2.0 %.
+// (Fitted to products by themselves, operands in the caches and widths to 2048, it cost 4.4 and 5.6 %: 944 x 9984 x 3328 took 64 x
+// 128 tiles, 150 us, for 128 x 128, 84; the layer of 4 x 236 tokens, H 3328 1217 us against 1125 before those tiles came.)
+// A launch takes z us and e for each tile of a compute unit.  Whole rounds of as many workgroups as fit take c for each of a unit's
 // and stage of 64 k; in the last one a stage takes a + b n when n workgroups share a unit, and never less than c for each of
-// them, averaged over the machine (which they share too: 384 tiles of 128 x 128 take 0.9 us a stage, 512 take 1.1):
-//   128 x 128, ring of 2: 0.8 us alone, 1.07 two together (1.0 PFLOP/s on 4096 x 2048 x 8192, 512 tiles);
-//              ring of 4: 0.6 alone, and alone it is: for 192 tiles and long K (1024 x 3072 x 8192: 77 us against 106);
-//    64 x 128, ring of 2: 0.57 alone, 0.36 each from three on: where three share a unit;
-//              ring of 3: 0.4 alone, 0.6 two together (2331 x 1024 x 4096, 296 tiles: 39 us against 52 and, 128 x 128, 44);
-//    64 x 64,  ring of 2: 0.22 each from four on;
-//              ring of 3: 0.3 alone: for the smallest (256 x 256 x 1024: 7.6 us against 10.5; 128 x 1280 x 5120: 23 against 40).
-//   wavefronts along k (a stage of 128 counts twice): 64 x 64 0.25 alone; 32 x 64 0.17; 32 x 32 0.12: for fewer tiles than
+// them, averaged over the machine.  f: us for each megabyte that a stage's panels bring from memory to the XCDs (panels()): small tiles
+// read an operand more often than the L2s catch.
+//   128 x 128, ring of 2: 0.80 us alone, 0.56 each together (1.0 PFLOP/s on 4096 x 2048 x 8192, 512 tiles);
+//              ring of 4: 0.64, and alone it is: for 192 tiles and long K (1024 x 3072 x 8192: 77 us against 106);
+//    64 x 128, ring of 2: 0.34 each from three on: where three share a unit;
+//              ring of 3: 0.30 alone (2331 x 1024 x 4096, 296 tiles: 39 us against 52 and, 128 x 128, 44);
+//    64 x 64,  ring of 2: 0.18 each, four to a unit (160 KiB of LDS would hold a fifth, but it waits: 1056 tiles of 33 stages 47 us,
+//              1014 of 52 50);
+//              ring of 3: 0.19 alone: for the smaller (512 x 2304 x 576: 9 us, by 64 x 128 13).
+//   wavefronts along k (a stage of 128 counts twice): 64 x 64 0.17 alone; 32 x 64 0.11; 32 x 32 0.11: for fewer tiles than
 //              compute units, where a stage is bound by the LDS reads of one workgroup: of a 64 x 64 tile four wavefronts side by
 //              side read half as much as four quarters of it, and 32 x 32 tiles leave each unit a quarter of the loads.
 //              (256 x 256 x 1024 7.4 -> 5.2 us, 128 x 1280 x 5120 22.3 -> 14.6, 256 x 1280 x 5120 25.1 -> 17.7 by 32 x 64, 1024 x 1024
 //              x 4096 25.7 -> 21.6 by 64 x 64; both products of 256 x 256 -> 1024's backward 8.5 -> 6.0.)
-//  256 x 128: 0.96 us a stage, 0.84 where a third of the machine is left over.
+//  256 x 128: 0.97 us a stage, 0.70 in a last round that leaves much of the machine over.
 // Splitting the contraction costs a second launch and the partial products' way out and back, from the caches at about 8.6 TB/s.
-struct TileCost { double a, b, c, e; int fit; };  // fit: workgroups that share a compute unit at most
-static const TileCost kCost[kCfgs] = {{0.61, 0.155, 0.56, 1.9, 2}, {0.41, 0.165, 0.34, 1.0, 3}, {0.39, 0.107, 0.21, 0.39, 5},
-                                      {0.28, 0.155, 0.34, 1.55, 2}, {0.255, 0.115, 0.213, 0.45, 3}, {0.06, 0.52, 0.655, 3.5, 1},
-                                      {0.17, 0.077, 0.263, 3.0, 1}, {0.142, 0.066, 0.139, 1.05, 2}, {0.077, 0.068, 0.107, 0.78, 2}, {0.84, 0.0, 0.96, 6.3, 1}};
+struct TileCost { double a, b, c, e, f, z; int fit; };  // fit: workgroups that share a compute unit at most
+static const TileCost kCost[kCfgs] = {{0.797, 0.003, 0.561, 2.467, 0, 6.771, 2},     {0.513, 0.054, 0.342, 0.76, 0.042, 5.291, 3},
+                                      {0.414, 0.034, 0.183, 0.627, 0.045, 4.394, 4}, {0.121, 0.18, 0.341, 1.685, 0.056, 6.116, 2},
+                                      {0.036, 0.151, 0.198, 0.506, 0.067, 4.985, 3}, {0.077, 0.436, 0.643, 5.364, 0, 6.31, 1},
+                                      {0.125, 0.044, 0.186, 1.233, 0.044, 5.442, 1}, {0.073, 0.04, 0.141, 0.498, 0.068, 4.251, 2},
+                                      {0.054, 0.057, 0.088, 0.561, 0.072, 3.782, 2}, {0.665, 0.03, 0.971, 9.136, 0, 6.072, 1}};
 constexpr int kMaxSplits = 8;
 static int stages_of(int K) { return (K + kSK - 1) / kSK; }
 static long tiles_of(int M, int N, int cfg) { return (long)((M + kCfg[cfg].bm - 1) / kCfg[cfg].bm) * ((N + kCfg[cfg].bn - 1) / kCfg[cfg].bn); }
 static double reduce_cost(int M, int N, int splits) { return splits > 1 ? 3.1 + 8.0 * splits * M * N / 8.6e6 : 0.0; }
 // stages of 64 k
 static int cost_stages(int K, int cfg) { return (K + kCfg[cfg].sk - 1) / kCfg[cfg].sk * (kCfg[cfg].sk / kSK); }
+// Megabytes that the panels of one stage bring to the eight XCDs, each panel once to every XCD that has a tile of it, times the rounds
+// of workgroups.  tile_of deals a number of tiles that is a multiple of eight out in eight compact pieces; others go round the XCDs
+// one by one, and each XCD reads every panel of B.
+static double panels(long tiles_m, long tiles_n, int cfg, int splits, int fit) {
+  const double tm = (double)tiles_m, tn = (double)tiles_n, nt = tm * tn, n = nt * splits, round = 256.0 * fit;
+  const int g = (int)std::min<long>(tiles_m >= tiles_n ? 4 : 8, tiles_m);  // rows of tiles in a group, see choose
+  const double at = std::min(n, round), one = std::min(nt, at), beside = at / one, w = std::max(one / 8, 1.0);  // tiles of an XCD
+  double rows, cols;
+  if (tiles_m * tiles_n % 8 == 0) {
+    rows = std::min(tm, g * std::ceil(w / (g * tn)));
+    cols = std::min(tn, std::ceil(w / g));
+  } else {
+    rows = std::min(std::min(tm, w), g / (g % 8 == 0 ? 8.0 : g % 4 == 0 ? 4.0 : g % 2 == 0 ? 2.0 : 1.0) * std::ceil(one / (g * tn)));
+    cols = std::min(tn, w);
+  }
+  return (rows * kCfg[cfg].bm + cols * kCfg[cfg].bn) * 8 * (2 * kSK) * 1e-6 * std::max(n / round, beside);
+}
 static double tile_cost(int M, int N, int K, int cfg, int splits) {
   const TileCost &q = kCost[cfg];
-  const long tiles = tiles_of(M, N, cfg) * splits, round = 256l * q.fit, full = tiles / round, rest = tiles - full * round;
-  const double t = full * q.c * q.fit + (rest ? std::max(q.a + q.b * ((rest + 255) / 256), q.c * rest / 256.0) : 0.0);
-  return 2.5 + t * ((cost_stages(K, cfg) + splits - 1) / splits) + q.e * tiles / 256.0 + reduce_cost(M, N, splits);
+  const long tm = (M + kCfg[cfg].bm - 1) / kCfg[cfg].bm, tn = (N + kCfg[cfg].bn - 1) / kCfg[cfg].bn;
+  const long tiles = tm * tn * splits, round = 256l * q.fit, full = tiles / round, rest = tiles - full * round;
+  const double t = full * q.c * q.fit + (rest ? std::max(q.a + q.b * ((rest + 255) / 256), q.c * rest / 256.0) : 0.0) + q.f * panels(tm, tn, cfg, splits, q.fit);
+  return q.z + t * ((cost_stages(K, cfg) + splits - 1) / splits) + q.e * tiles / 256.0 + reduce_cost(M, N, splits);
 }
 static size_t split_bytes(int M, int N, int splits) { return splits > 1 ? (size_t)splits * ((size_t)M + 1) * N * 4 : 0; }
 static bool split_ok(int K, int splits) { return splits == 1 || splits * 4 <= stages_of(K); }
@@ -943,7 +968,7 @@ static double tile_plan(int M, int N, int K, size_t scratch, int cfgs, int *cfg,
     for (int sp = 1; sp <= (c == kWide ? 1 : kMaxSplits) && split_ok(K, sp); sp *= 2) {
       if (split_bytes(M, N, sp) > scratch) break;
       const double t = tile_cost(M, N, K, c, sp);
-      if (t < best * 0.98) { best = t; *cfg = c; *splits = sp; }
+      if (t < best) { best = t; *cfg = c; *splits = sp; }
     }
   }
   return best;
@@ -951,11 +976,13 @@ static double tile_plan(int M, int N, int K, size_t scratch, int cfgs, int *cfg,
 
 // The same for two problems in one launch (one tile size, each its own split; half of the scratch for each).  The tiles
 // of both share the machine: it is done when the work is (c per tile and stage, and what of the shorter tiles runs beside
-// nothing at the end), or when the longest tile is.  Fitted by itself, to 27 linears' backwards in every tile and split: the
-// choice costs 1.3 % more than the best on average (with the table above 3.8 %; 1536 x 1280 -> 2560 44 against 35 us).
-static const TileCost kPairCost[kWide] = {{0.69, 0.13, 0.497, 2.2, 2}, {0.454, 0.155, 0.354, 0.73, 3}, {0.376, 0.068, 0.206, 0.6, 5},
-                                          {0.268, 0.121, 0.353, 1.68, 2}, {0.198, 0.112, 0.252, 0.354, 3}, {0.034, 0.6, 0.7, 3.9, 1},
-                                          {0.19, 0.042, 0.302, 2.93, 1}, {0.117, 0.065, 0.147, 1.12, 2}, {0.073, 0.048, 0.139, 0.86, 2}};
+// nothing at the end), or when the longest tile is.  Fitted by itself.  (fit 0: no pair, 128 x 128 in a ring of four and 64 x 64 along k
+// were never the choice.)
+static const TileCost kPairCost[kWide] = {{0.728, 0.004, 0.416, 2.047, 0.043, 2.839, 2}, {0.538, 0.005, 0.247, 0.627, 0.062, 3.051, 3},
+                                          {0.426, 0.006, 0.154, 0.506, 0.049, 2.888, 4}, {0.331, 0.006, 0.239, 1.622, 0.072, 3.034, 2},
+                                          {0.254, 0.0, 0.188, 0.494, 0.044, 3.158, 3},   {},
+                                          {},                                            {0.132, 0.007, 0.118, 0.973, 0.05, 2.852, 2},
+                                          {0.089, 0.008, 0.105, 0.902, 0.028, 2.923, 2}};
 struct PairPlan { int cfg = 0, sw = 1, sd = 1; };
 // When `slots` workers are done that take n1 pieces of t1 each and then n2 of t2.
 static double deal(long n1, double t1, long n2, double t2, long slots) {
@@ -982,6 +1009,7 @@ static double pair_plan(const Shape &w, const Shape &d, size_t scratch, PairPlan
   const size_t half = half_of(scratch);
   double best = 1e30;
   for (int c = 0; c < kWide; ++c) {
+    if (!kPairCost[c].fit) continue;
     for (int sw = 1; sw <= kMaxSplits && split_ok(w.K, sw); sw *= 2) {
       if (split_bytes(w.M, w.N, sw) > half) break;
       for (int sd = 1; sd <= kMaxSplits && split_ok(d.K, sd); sd *= 2) {
@@ -990,43 +1018,48 @@ static double pair_plan(const Shape &w, const Shape &d, size_t scratch, PairPlan
         const double lw = (cost_stages(w.K, c) + sw - 1) / sw, ld = (cost_stages(d.K, c) + sd - 1) / sd, longest = std::max(lw, ld);
         const TileCost &q = kPairCost[c];
         const double n = std::min((double)q.fit, std::ceil((nw + nd) / 256.0));
-        const double tail = (nw + nd > 256.0 * q.fit ? 0.35 : 0.29) * std::min(lw, ld) * (q.a + q.b);
+        const double tail = (nw + nd > 256.0 * q.fit ? 0.359 : 0.227) * std::min(lw, ld) * (q.a + q.b);
         const double work = ((nw * lw + nd * ld) * q.c + (nw + nd) * q.e) / 256.0 + tail;
-        const double t = 2.7 + std::max(work, longest * (q.a + q.b * n) + q.e) + reduce_cost(w.M, w.N, sw) + reduce_cost(d.M, d.N, sd);
-        if (t < best * 0.98) { best = t; out->cfg = c; out->sw = sw; out->sd = sd; }
+        const auto rows = [&](int m) { return (long)(m + kCfg[c].bm - 1) / kCfg[c].bm; };
+        const auto cols = [&](int m) { return (long)(m + kCfg[c].bn - 1) / kCfg[c].bn; };
+        const double t = q.z + std::max(work, longest * (q.a + q.b * n) + q.e) + reduce_cost(w.M, w.N, sw) + reduce_cost(d.M, d.N, sd) +
+                         q.f * (panels(rows(w.M), cols(w.N), c, sw, q.fit) * lw + panels(rows(d.M), cols(d.N), c, sd, q.fit) * ld);
+        if (t < best) { best = t; out->cfg = c; out->sw = sw; out->sd = sd; }
       }
     }
   }
-  // Tiles of 256 x 128, one to a compute unit, where they are done before that: there and for unsplit 128 x 128 tiles, the other
-  // choice at such sizes, by dealing the tiles out (4096 x 2048 -> 6144 219 -> 201 us, predicted 222 and 212; 8192 x 1024 -> 4096
-  // 136 -> 124; 4096 x 2048 -> 2048 73 -> 67; 5785 x 2048 -> 2048 103 -> 95; but 3000 x 1536 -> 4608, taken too, 88 -> 98).
-  const auto dealt = [&](int c, long slots, double stage, double e) {
-    const long nw = tiles_of(w.M, w.N, c), nd = tiles_of(d.M, d.N, c);
-    const double tw = stages_of(w.K) * stage + e, td = stages_of(d.K) * stage + e;
-    return 2.7 + (stages_of(w.K) >= stages_of(d.K) ? deal(nw, tw, nd, td, slots) : deal(nd, td, nw, tw, slots));
-  };
+  // Tiles of 256 x 128, one to a compute unit, by dealing them out: 0.89 us a stage, 4.1 a tile (4096 x 2048 -> 6144 219 -> 201 us; 8192 x
+  // 1024 -> 4096 136 -> 124; 4096 x 2048 -> 2048 73 -> 67; 5785 x 2048 -> 2048 103 -> 95).
   if (tiles_of(w.M, w.N, kWide) + tiles_of(d.M, d.N, kWide) <= 2048) {
-    const double t = dealt(kWide, 256, 0.88, 4.0);
-    if (out->cfg == 0 && out->sw == 1 && out->sd == 1) best = dealt(0, 512, 0.95, 2.2);
+    const long nw = tiles_of(w.M, w.N, kWide), nd = tiles_of(d.M, d.N, kWide);
+    const double tw = stages_of(w.K) * 0.894 + 4.06, td = stages_of(d.K) * 0.894 + 4.06;
+    const double t = 4.31 + (stages_of(w.K) >= stages_of(d.K) ? deal(nw, tw, nd, td, 256) : deal(nd, td, nw, tw, 256));
     if (t < best * 0.99) { best = t; out->cfg = kWide; out->sw = out->sd = 1; }
   }
   return best;
 }
 
-// Predicted time of the 256 x 256 kernels: a round of 256 of their tiles takes about 1.62 us a stage (4096 x 6144 x 2048,
-// 384 tiles: 105 us against 111 here), a nearly empty round as long as a full one.
+// Predicted time of the 256 x 256 kernels, fitted to 362 products of such layers (standard deviation 9 %): a round of 256 of their
+// tiles takes 1.05 us a stage however empty it is and up to 0.42 more when it is full (4096 x 6144 x 2048, 384 tiles: 94 us against
+// 107 here).
 static bool large_possible(int M, int N, int K, bool transA, bool transB) {
   if (M % 256 || N % 256 || K % 64 || (long)(M / 256) * (N / 256) < 256) return false;
   return K % 128 == 0 || (!transA && transB);  // (gemm_km256_k takes its stages in pairs)
 }
-static double large_cost(int M, int N, int K) { return 3.0 + 1.62 * (((long)(M / 256) * (N / 256) + 255) / 256) * (K / 64); }
+static double large_cost(int M, int N, int K) {
+  const long tiles = (long)(M / 256) * (N / 256);
+  const double rounds = tiles / 256.0, begun = (double)((tiles + 255) / 256);
+  return (K / 64) * (1.046 * begun + 0.42 * rounds) + 4.45 * begun + 5.65 * rounds;
+}
 
-// Whether they should take a problem that suits both: one just above a multiple of 256 tiles is better off here.
+// Whether they should take a problem that suits both: unless 128 x 128 tiles would be done sooner if they kept every compute unit busy to
+// the end, which they are just above 256 tiles of 256 x 256 (5632 x 3072 x 12288, 264 tiles: 534 us, by 128 x 128 477, by 256 x 128 449;
+// 8960 x 2048 x 8192, 280 tiles: 346, 343, 309; from 288 tiles on the large ones are ahead).
 bool gemm_large_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
   if (dtype != SSDT_BF16 || !large_possible(M, N, K, transA, transB)) return false;
   if (!gemm_tile_fits(M, N, K, transA, transB, dtype)) return true;
-  int cfg, splits;
-  return tile_plan(M, N, K, 0, kOneOrder, &cfg, &splits) > 0.9 * large_cost(M, N, K);
+  const TileCost &q = kCost[0];
+  return q.z + tiles_of(M, N, 0) / 256.0 * (q.c * stages_of(K) + q.e) > large_cost(M, N, K);
 }
 
 // Whether the weight gradient w (M x N over K tokens) and the input gradient d of a linear should share a launch, given
@@ -1052,6 +1085,14 @@ size_t gemm_pair_scratch_bytes(int rows, int in, int out, int dtype) {
   if (dtype != SSDT_BF16 || !pair_wanted(w, d, ~(size_t)0, &pp)) return 0;
   return 2 * std::max(split_bytes(w.M, w.N, std::max(pp.sw, pinned_splits(false))),
                       split_bytes(d.M, d.N, std::max(pp.sd, pinned_splits(true)))) + 512;
+}
+
+// For tests: the tile that a forward product takes, -1 where it goes to the 256 x 256 kernels.
+int gemm_tile_choice(int M, int N, int K, bool one_order) {
+  if (gemm_large_fits(M, N, K, false, false, SSDT_BF16)) return -1;
+  int cfg = 0, splits = 1;
+  tile_plan(M, N, K, 0, one_order ? kOneOrder : kCfgs, &cfg, &splits);
+  return cfg;
 }
 
 // Checks what the kernel needs beyond the shape and fills its arguments, the choice of tile aside.
@@ -1113,6 +1154,7 @@ hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, hipStream_t s) {
   if (e == hipSuccess) e = prepare(d, &pd);
   if (e != hipSuccess) return e;
   if (g_tile_cfg >= 0) pp.cfg = g_tile_cfg;
+  if (pp.cfg != kWide && !kPairCost[pp.cfg].fit) return hipErrorNotSupported;  // (pinned)
   if (g_tile_splits > 0) {
     const int sw = pinned_splits(false), sd = pinned_splits(true);
     if (std::max(split_bytes(pw.M, pw.N, sw), split_bytes(pd.M, pd.N, sd)) <= half_of(scratch)) { pp.sw = sw; pp.sd = sd; }
@@ -1126,8 +1168,6 @@ hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, hipStream_t s) {
     case 2: return launch_pair<64, 64, 2, false>(pw, pd, s);
     case 3: return launch_pair<64, 128, 3, false>(pw, pd, s);
     case 4: return launch_pair<64, 64, 3, false>(pw, pd, s);
-    case 5: return launch_pair<128, 128, 4, false>(pw, pd, s);
-    case 6: return launch_pair<64, 64, 3, true>(pw, pd, s);
     case 7: return launch_pair<32, 64, 3, true>(pw, pd, s);
     case 8: return launch_pair<32, 32, 4, true>(pw, pd, s);
     default: return launch_wide_pair(pw, pd, s);
