@@ -156,11 +156,15 @@ bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype);  
 bool gemm_large_fits(int M, int N, int K, bool transA, bool transB, int dtype);  // the 256 x 256 kernels should take it
 // A linear's weight gradient w (transA) and input gradient d (transB) in one launch; hipErrorNotSupported (nothing launched)
 // where two launches are better.  Neither may write what the other reads.  With w.colsum the bias sums fall out of w's kernel, in
-// fp32 here only (gemm() leaves them to colsum() there).
-hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, hipStream_t s);
+// fp32 here only (gemm() leaves them to colsum() there).  plan: what gemm_linear_bwd_scratch_bytes chose, or null.
+struct PairPlan {
+  int rows = 0, in = 0, out = 0;  // the linear
+  bool pair = false;              // one launch
+  int cfg = 0, sw = 1, sd = 1;    // its tile, the splits of w and d
+};
+hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, const PairPlan *plan, hipStream_t s);
 hipError_t gemm_pair_f32(const Gemm &w, const Gemm &d, hipStream_t s);
-size_t gemm_pair_scratch_bytes(int rows, int in, int out, int dtype);  // of gemm_pair_bf16 for a linear in -> out
-size_t gemm_tile_scratch_bytes(int M, int N, int K, bool transA, bool transB, int dtype);
+size_t gemm_linear_bwd_scratch_bytes(int rows, int in, int out, int dtype, PairPlan *plan);  // partial products of a linear's backward
 extern int g_tile_cfg, g_tile_splits;  // test hooks of that kernel: >= 0 pins the tile, > 0 the number of splits
 bool gemm_km_fits(int M, int N, int K, bool transA, bool transB, int dtype);  // shape conditions of that kernel
 extern int g_km_stagger;  // stages between the K-loop starts of neighbouring XCDs (-100 = by shape)

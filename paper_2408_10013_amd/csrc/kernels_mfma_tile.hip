@@ -930,19 +930,26 @@ static const TileCost kCost[kCfgs] = {{0.797, 0.003, 0.561, 2.467, 0, 6.771, 2},
                                       {0.054, 0.057, 0.088, 0.561, 0.072, 3.782, 2}, {0.665, 0.03, 0.971, 9.136, 0, 6.072, 1}};
 constexpr int kMaxSplits = 8;
 static int stages_of(int K) { return (K + kSK - 1) / kSK; }
-static long tiles_of(int M, int N, int cfg) { return (long)((M + kCfg[cfg].bm - 1) / kCfg[cfg].bm) * ((N + kCfg[cfg].bn - 1) / kCfg[cfg].bn); }
 static double reduce_cost(int M, int N, int splits) { return splits > 1 ? 3.1 + 8.0 * splits * M * N / 8.6e6 : 0.0; }
-// stages of 64 k
-static int cost_stages(int K, int cfg) { return (K + kCfg[cfg].sk - 1) / kCfg[cfg].sk * (kCfg[cfg].sk / kSK); }
+// A problem in tiles of a kind: rows and columns of tiles, stages of 64 k.  (Everything from here to the launch is on the path of each
+// call: a layer's plans, forward and backward, take 1.5 to 4 us, candidates that cannot win are left out early.)
+struct Tiling { int tm, tn, stages; long n; };
+static Tiling tiling(int M, int N, int K, int cfg) {
+  const auto up = [](int x, int by) { return (x + by - 1) >> __builtin_ctz(by); };  // (all powers of two)
+  const TileCfg &q = kCfg[cfg];
+  Tiling t{up(M, q.bm), up(N, q.bn), up(K, q.sk) * (q.sk / kSK), 0};
+  t.n = (long)t.tm * t.tn;
+  return t;
+}
 // Megabytes that the panels of one stage bring to the eight XCDs, each panel once to every XCD that has a tile of it, times the rounds
 // of workgroups.  tile_of deals a number of tiles that is a multiple of eight out in eight compact pieces; others go round the XCDs
 // one by one, and each XCD reads every panel of B.
-static double panels(long tiles_m, long tiles_n, int cfg, int splits, int fit) {
-  const double tm = (double)tiles_m, tn = (double)tiles_n, nt = tm * tn, n = nt * splits, round = 256.0 * fit;
-  const int g = (int)std::min<long>(tiles_m >= tiles_n ? 4 : 8, tiles_m);  // rows of tiles in a group, see choose
+static double panels(const Tiling &p, int cfg, int splits, int fit) {
+  const double tm = p.tm, tn = p.tn, nt = (double)p.n, n = nt * splits, round = 256.0 * fit;
+  const int g = std::min(p.tm >= p.tn ? 4 : 8, p.tm);  // rows of tiles in a group, see choose
   const double at = std::min(n, round), one = std::min(nt, at), beside = at / one, w = std::max(one / 8, 1.0);  // tiles of an XCD
   double rows, cols;
-  if (tiles_m * tiles_n % 8 == 0) {
+  if (p.n % 8 == 0) {
     rows = std::min(tm, g * std::ceil(w / (g * tn)));
     cols = std::min(tn, std::ceil(w / g));
   } else {
@@ -951,24 +958,37 @@ static double panels(long tiles_m, long tiles_n, int cfg, int splits, int fit) {
   }
   return (rows * kCfg[cfg].bm + cols * kCfg[cfg].bn) * 8 * (2 * kSK) * 1e-6 * std::max(n / round, beside);
 }
-static double tile_cost(int M, int N, int K, int cfg, int splits) {
-  const TileCost &q = kCost[cfg];
-  const long tm = (M + kCfg[cfg].bm - 1) / kCfg[cfg].bm, tn = (N + kCfg[cfg].bn - 1) / kCfg[cfg].bn;
-  const long tiles = tm * tn * splits, round = 256l * q.fit, full = tiles / round, rest = tiles - full * round;
-  const double t = full * q.c * q.fit + (rest ? std::max(q.a + q.b * ((rest + 255) / 256), q.c * rest / 256.0) : 0.0) + q.f * panels(tm, tn, cfg, splits, q.fit);
-  return q.z + t * ((cost_stages(K, cfg) + splits - 1) / splits) + q.e * tiles / 256.0 + reduce_cost(M, N, splits);
-}
 static size_t split_bytes(int M, int N, int splits) { return splits > 1 ? (size_t)splits * ((size_t)M + 1) * N * 4 : 0; }
 static bool split_ok(int K, int splits) { return splits == 1 || splits * 4 <= stages_of(K); }
 
+// How often the contraction can be halved, given `scratch` bytes for partial products.
+static int most_halvings(int M, int N, int K, size_t scratch) {
+  int h = 0;
+  while ((2 << h) <= kMaxSplits && split_ok(K, 2 << h) && split_bytes(M, N, 2 << h) <= scratch) ++h;
+  return h;
+}
+
+// Small tiles are the likely choice: looked at first, they rule the others out.
+static bool few_tiles(int M, int N) { return (long)M * N < 96l * 128 * 128; }
+
 // The choice for a problem given `scratch` bytes for partial products, among the first `cfgs` tiles; returns its predicted time.
 static double tile_plan(int M, int N, int K, size_t scratch, int cfgs, int *cfg, int *splits) {
+  const int most = scratch ? most_halvings(M, N, K, scratch) : 0;
+  const bool small = few_tiles(M, N);
   double best = 1e30;
-  for (int c = 0; c < cfgs; ++c) {
-    for (int sp = 1; sp <= (c == kWide ? 1 : kMaxSplits) && split_ok(K, sp); sp *= 2) {
-      if (split_bytes(M, N, sp) > scratch) break;
-      const double t = tile_cost(M, N, K, c, sp);
-      if (t < best) { best = t; *cfg = c; *splits = sp; }
+  for (int i = 0; i < cfgs; ++i) {
+    const int c = small ? cfgs - 1 - i : i;
+    const TileCost &q = kCost[c];
+    const Tiling p = tiling(M, N, K, c);
+    if (q.z + p.n * (q.c * p.stages + q.e) / 256.0 >= best) continue;  // (every unit busy to the end, nothing to reduce)
+    for (int h = 0; h <= (c == kWide ? 0 : most); ++h) {
+      const long tiles = p.n << h, round = 256l * q.fit, full = tiles < round ? 0 : tiles / round, rest = tiles - full * round;
+      const double stages = (p.stages + (1 << h) - 1) >> h;
+      const double fixed = q.z + q.e * tiles / 256.0 + reduce_cost(M, N, 1 << h);
+      const double stage = full * q.c * q.fit + (rest ? std::max(q.a + q.b * ((rest + 255) / 256), q.c * rest / 256.0) : 0.0);
+      if (fixed + stage * stages >= best) continue;
+      const double t = fixed + (stage + q.f * panels(p, c, 1 << h, q.fit)) * stages;
+      if (t < best) { best = t; *cfg = c; *splits = 1 << h; }
     }
   }
   return best;
@@ -983,7 +1003,6 @@ static const TileCost kPairCost[kWide] = {{0.728, 0.004, 0.416, 2.047, 0.043, 2.
                                           {0.254, 0.0, 0.188, 0.494, 0.044, 3.158, 3},   {},
                                           {},                                            {0.132, 0.007, 0.118, 0.973, 0.05, 2.852, 2},
                                           {0.089, 0.008, 0.105, 0.902, 0.028, 2.923, 2}};
-struct PairPlan { int cfg = 0, sw = 1, sd = 1; };
 // When `slots` workers are done that take n1 pieces of t1 each and then n2 of t2.
 static double deal(long n1, double t1, long n2, double t2, long slots) {
   struct { double at; long n; } g[64] = {{0.0, slots}};  // workers by the time they are free
@@ -1007,33 +1026,39 @@ struct Shape { int M, N, K; };
 static size_t half_of(size_t scratch) { return scratch / 2 / 256 * 256; }
 static double pair_plan(const Shape &w, const Shape &d, size_t scratch, PairPlan *out) {
   const size_t half = half_of(scratch);
-  double best = 1e30;
-  for (int c = 0; c < kWide; ++c) {
-    if (!kPairCost[c].fit) continue;
-    for (int sw = 1; sw <= kMaxSplits && split_ok(w.K, sw); sw *= 2) {
-      if (split_bytes(w.M, w.N, sw) > half) break;
-      for (int sd = 1; sd <= kMaxSplits && split_ok(d.K, sd); sd *= 2) {
-        if (split_bytes(d.M, d.N, sd) > half) break;
-        const double nw = (double)tiles_of(w.M, w.N, c) * sw, nd = (double)tiles_of(d.M, d.N, c) * sd;
-        const double lw = (cost_stages(w.K, c) + sw - 1) / sw, ld = (cost_stages(d.K, c) + sd - 1) / sd, longest = std::max(lw, ld);
-        const TileCost &q = kPairCost[c];
-        const double n = std::min((double)q.fit, std::ceil((nw + nd) / 256.0));
-        const double tail = (nw + nd > 256.0 * q.fit ? 0.359 : 0.227) * std::min(lw, ld) * (q.a + q.b);
+  const int most_w = most_halvings(w.M, w.N, w.K, half), most_d = most_halvings(d.M, d.N, d.K, half);
+  double best = 1e30, rw[4], rd[4];
+  for (int h = 0; h <= most_w; ++h) rw[h] = reduce_cost(w.M, w.N, 1 << h);
+  for (int h = 0; h <= most_d; ++h) rd[h] = reduce_cost(d.M, d.N, 1 << h);
+  const bool small = few_tiles(w.M, w.N) && few_tiles(d.M, d.N);
+  for (int i = 0; i < kWide; ++i) {
+    const int c = small ? kWide - 1 - i : i;
+    const TileCost &q = kPairCost[c];
+    if (!q.fit) continue;
+    const Tiling pw = tiling(w.M, w.N, w.K, c), pd = tiling(d.M, d.N, d.K, c);
+    const double busy = q.z + ((double)(pw.n * pw.stages + pd.n * pd.stages) * q.c + (double)(pw.n + pd.n) * q.e) / 256.0;
+    for (int hw = 0; hw <= most_w; ++hw) {
+      if (busy + rw[hw] >= best) break;  // (as in tile_plan; the reduction takes longer with every split)
+      for (int hd = 0; hd <= most_d; ++hd) {
+        if (busy + rw[hw] + rd[hd] >= best) break;
+        const double nw = (double)(pw.n << hw), nd = (double)(pd.n << hd), n256 = (nw + nd) / 256.0;
+        const double lw = (pw.stages + (1 << hw) - 1) >> hw, ld = (pd.stages + (1 << hd) - 1) >> hd;
+        const double n = std::min((double)q.fit, std::ceil(n256));
+        const double tail = (n256 > q.fit ? 0.359 : 0.227) * std::min(lw, ld) * (q.a + q.b);
         const double work = ((nw * lw + nd * ld) * q.c + (nw + nd) * q.e) / 256.0 + tail;
-        const auto rows = [&](int m) { return (long)(m + kCfg[c].bm - 1) / kCfg[c].bm; };
-        const auto cols = [&](int m) { return (long)(m + kCfg[c].bn - 1) / kCfg[c].bn; };
-        const double t = q.z + std::max(work, longest * (q.a + q.b * n) + q.e) + reduce_cost(w.M, w.N, sw) + reduce_cost(d.M, d.N, sd) +
-                         q.f * (panels(rows(w.M), cols(w.N), c, sw, q.fit) * lw + panels(rows(d.M), cols(d.N), c, sd, q.fit) * ld);
-        if (t < best) { best = t; out->cfg = c; out->sw = sw; out->sd = sd; }
+        double t = q.z + std::max(work, std::max(lw, ld) * (q.a + q.b * n) + q.e) + rw[hw] + rd[hd];
+        if (t >= best) continue;
+        t += q.f * (panels(pw, c, 1 << hw, q.fit) * lw + panels(pd, c, 1 << hd, q.fit) * ld);
+        if (t < best) { best = t; out->cfg = c; out->sw = 1 << hw; out->sd = 1 << hd; }
       }
     }
   }
   // Tiles of 256 x 128, one to a compute unit, by dealing them out: 0.89 us a stage, 4.1 a tile (4096 x 2048 -> 6144 219 -> 201 us; 8192 x
   // 1024 -> 4096 136 -> 124; 4096 x 2048 -> 2048 73 -> 67; 5785 x 2048 -> 2048 103 -> 95).
-  if (tiles_of(w.M, w.N, kWide) + tiles_of(d.M, d.N, kWide) <= 2048) {
-    const long nw = tiles_of(w.M, w.N, kWide), nd = tiles_of(d.M, d.N, kWide);
-    const double tw = stages_of(w.K) * 0.894 + 4.06, td = stages_of(d.K) * 0.894 + 4.06;
-    const double t = 4.31 + (stages_of(w.K) >= stages_of(d.K) ? deal(nw, tw, nd, td, 256) : deal(nd, td, nw, tw, 256));
+  const Tiling pw = tiling(w.M, w.N, w.K, kWide), pd = tiling(d.M, d.N, d.K, kWide);
+  const double tw = pw.stages * 0.894 + 4.06, td = pd.stages * 0.894 + 4.06;
+  if (pw.n + pd.n <= 2048 && 4.31 + std::max((pw.n * tw + pd.n * td) / 256.0, std::max(tw, td)) < best * 0.99) {
+    const double t = 4.31 + (pw.stages >= pd.stages ? deal(pw.n, tw, pd.n, td, 256) : deal(pd.n, td, pw.n, tw, 256));
     if (t < best * 0.99) { best = t; out->cfg = kWide; out->sw = out->sd = 1; }
   }
   return best;
@@ -1059,32 +1084,52 @@ bool gemm_large_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
   if (dtype != SSDT_BF16 || !large_possible(M, N, K, transA, transB)) return false;
   if (!gemm_tile_fits(M, N, K, transA, transB, dtype)) return true;
   const TileCost &q = kCost[0];
-  return q.z + tiles_of(M, N, 0) / 256.0 * (q.c * stages_of(K) + q.e) > large_cost(M, N, K);
+  const Tiling p = tiling(M, N, K, 0);
+  return q.z + p.n / 256.0 * (q.c * p.stages + q.e) > large_cost(M, N, K);
 }
 
+static bool tiles_take(const Shape &p, bool transA, bool transB) {
+  return gemm_tile_fits(p.M, p.N, p.K, transA, transB, SSDT_BF16) && !gemm_large_fits(p.M, p.N, p.K, transA, transB, SSDT_BF16);
+}
+// No tile takes less: the least of the bounds that tile_plan starts from.
+static double least_cost(const Shape &p) {
+  double least = 1e30;
+  for (int c = 0; c < kCfgs; ++c) {
+    const Tiling t = tiling(p.M, p.N, p.K, c);
+    least = std::min(least, kCost[c].z + t.n * (kCost[c].c * t.stages + kCost[c].e) / 256.0);
+  }
+  return least;
+}
 // Whether the weight gradient w (M x N over K tokens) and the input gradient d of a linear should share a launch, given
 // `scratch` bytes; *out is the choice then.
 static bool pair_wanted(const Shape &w, const Shape &d, size_t scratch, PairPlan *out) {
-  if (!gemm_tile_fits(w.M, w.N, w.K, true, false, SSDT_BF16) || !gemm_tile_fits(d.M, d.N, d.K, false, true, SSDT_BF16)) return false;
-  if (gemm_large_fits(w.M, w.N, w.K, true, false, SSDT_BF16) || gemm_large_fits(d.M, d.N, d.K, false, true, SSDT_BF16)) return false;
+  if (!tiles_take(w, true, false) || !tiles_take(d, false, true)) return false;
+  const double together = pair_plan(w, d, scratch, out);
+  if (together < least_cost(w) + least_cost(d)) return true;
   int c, sp;
-  const double alone = tile_plan(w.M, w.N, w.K, scratch, kCfgs, &c, &sp) + tile_plan(d.M, d.N, d.K, scratch, kCfgs, &c, &sp);
-  return pair_plan(w, d, scratch, out) < alone;
+  return together < tile_plan(w.M, w.N, w.K, scratch, kCfgs, &c, &sp) + tile_plan(d.M, d.N, d.K, scratch, kCfgs, &c, &sp);
 }
 
-// Scratch that the choices use where there is enough of it: a problem alone, and a linear's two backward products (rows tokens, in -> out).
-size_t gemm_tile_scratch_bytes(int M, int N, int K, bool transA, bool transB, int dtype) {
-  if (!gemm_tile_fits(M, N, K, transA, transB, dtype) || gemm_large_fits(M, N, K, transA, transB, dtype)) return 0;
-  int cfg = 0, splits = 1;
-  tile_plan(M, N, K, ~(size_t)0, kCfgs, &cfg, &splits);
-  return split_bytes(M, N, std::max(splits, pinned_splits(transB)));
-}
-size_t gemm_pair_scratch_bytes(int rows, int in, int out, int dtype) {
-  PairPlan pp;
+// Scratch that the choices for a linear's two backward products (rows tokens, in -> out) use where there is enough of it, each by
+// itself or both in one launch (*plan).
+size_t gemm_linear_bwd_scratch_bytes(int rows, int in, int out, int dtype, PairPlan *plan) {
+  *plan = PairPlan{rows, in, out};
+  if (dtype != SSDT_BF16) return 0;
   const Shape w{in, out, rows}, d{rows, in, out};
-  if (dtype != SSDT_BF16 || !pair_wanted(w, d, ~(size_t)0, &pp)) return 0;
-  return 2 * std::max(split_bytes(w.M, w.N, std::max(pp.sw, pinned_splits(false))),
-                      split_bytes(d.M, d.N, std::max(pp.sd, pinned_splits(true)))) + 512;
+  const size_t all = ~(size_t)0;
+  const bool tw = tiles_take(w, true, false), td = tiles_take(d, false, true);
+  int c = 0, sw = 1, sd = 1;
+  double alone = 0;
+  if (tw) alone += tile_plan(w.M, w.N, w.K, all, kCfgs, &c, &sw);
+  if (td) alone += tile_plan(d.M, d.N, d.K, all, kCfgs, &c, &sd);
+  const auto bytes_w = [&](int s) { return split_bytes(w.M, w.N, std::max(s, pinned_splits(false))); };
+  const auto bytes_d = [&](int s) { return split_bytes(d.M, d.N, std::max(s, pinned_splits(true))); };
+  size_t bytes = std::max(tw ? bytes_w(sw) : 0, td ? bytes_d(sd) : 0);
+  if (tw && td && pair_plan(w, d, all, plan) < alone) {
+    plan->pair = true;
+    bytes = std::max(bytes, 2 * std::max(bytes_w(plan->sw), bytes_d(plan->sd)) + 512);
+  }
+  return bytes;
 }
 
 // For tests: the tile that a forward product takes, -1 where it goes to the 256 x 256 kernels.
@@ -1144,12 +1189,15 @@ hipError_t gemm_mfma_tile_bf16(const Gemm &g, hipStream_t s) {
   return launch_cfg<false, false>(cfg, p, s);
 }
 
-hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, hipStream_t s) {
+hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, const PairPlan *plan, hipStream_t s) {
   TileP pw, pd;
   PairPlan pp;
   const size_t scratch = std::min(usable_scratch(w), usable_scratch(d));
-  if (w.transA != true || w.transB || d.transA || !d.transB || w.dtype != SSDT_BF16 || d.dtype != SSDT_BF16) return hipErrorNotSupported;
-  if (w.scratch != d.scratch || !pair_wanted(Shape{w.M, w.N, w.K}, Shape{d.M, d.N, d.K}, scratch, &pp)) return hipErrorNotSupported;
+  if (w.transA != true || w.transB || d.transA || !d.transB || w.dtype != SSDT_BF16 || d.dtype != SSDT_BF16 || w.scratch != d.scratch) return hipErrorNotSupported;
+  // A plan made for any amount of scratch is the one for this much if it fits: the best of more is the best of fewer that it is among.
+  if (plan && plan->rows == w.K && plan->in == w.M && plan->out == w.N && plan->pair &&
+      std::max(split_bytes(w.M, w.N, plan->sw), split_bytes(d.M, d.N, plan->sd)) <= half_of(scratch)) pp = *plan;
+  else if (!pair_wanted(Shape{w.M, w.N, w.K}, Shape{d.M, d.N, d.K}, scratch, &pp)) return hipErrorNotSupported;
   hipError_t e = prepare(w, &pw);
   if (e == hipSuccess) e = prepare(d, &pd);
   if (e != hipSuccess) return e;

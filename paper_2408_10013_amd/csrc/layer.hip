@@ -3,7 +3,9 @@
 // every tensor the backward needs allocated from the context's arena and passed through the
 // pack hook in the order autograd would register it (Sec. 3.2), and fetched back through the
 // unpack hook in backward (Algorithm 1).
+#include <algorithm>
 #include <cmath>
+#include <iterator>
 #include <mutex>
 
 #include "ctx.h"
@@ -58,7 +60,7 @@ size_t max3(size_t a, size_t b, size_t c) { return std::max(a, std::max(b, c)); 
 
 // Scratch of the GEMMs of a backward pass: `copies` is what transposed copies of operands need (kernels that read operands as
 // stored need none), `splits` what partial products of a split contraction would use.
-struct Scratch { size_t copies = 0, splits = 0; };
+struct Scratch { size_t copies = 0, splits = 0; k::PairPlan plans[5]; };
 // (Forward products are never split: their bits then do not depend on the workspace a caller hands over, and a layer
 // that is run again in its backward gives what it gave before.)
 size_t fwd_scratch(const Dims &D) {
@@ -70,16 +72,13 @@ size_t fwd_scratch(const Dims &D) {
 }
 Scratch bwd_scratch(const Dims &D) {
   Scratch s;
-  auto g = [&](int M, int N, int K, bool ta, bool tb) {
-    s.copies = std::max(s.copies, k::gemm_scratch_bytes(M, N, K, ta, tb, D.dt));
-    s.splits = std::max(s.splits, k::gemm_tile_scratch_bytes(M, N, K, ta, tb, D.dt));
+  k::PairPlan *plan = s.plans;
+  auto linear = [&](int rows, int in, int out) {
+    s.copies = std::max(s.copies, std::max(k::gemm_scratch_bytes(in, out, rows, true, false, D.dt), k::gemm_scratch_bytes(rows, in, out, false, true, D.dt)));
+    s.splits = std::max(s.splits, k::gemm_linear_bwd_scratch_bytes(rows, in, out, D.dt, plan++));
   };
-  g(D.F, D.H, D.T, true, false); g(D.H, D.F, D.T, true, false); g(D.H, 3 * D.H, D.T, true, false); g(D.H, D.H, D.T, true, false);
-  g(D.T, D.F, D.H, false, true); g(D.T, D.H, D.F, false, true); g(D.T, D.H, 3 * D.H, false, true); g(D.T, D.H, D.H, false, true);
-  if (D.dec) { g(D.H, 2 * D.H, D.Te, true, false); g(D.Te, D.H, 2 * D.H, false, true); }
-  auto pair = [&](int rows, int in, int out) { s.splits = std::max(s.splits, k::gemm_pair_scratch_bytes(rows, in, out, D.dt)); };
-  pair(D.T, D.F, D.H); pair(D.T, D.H, D.F); pair(D.T, D.H, 3 * D.H); pair(D.T, D.H, D.H);
-  if (D.dec) pair(D.Te, D.H, 2 * D.H);
+  linear(D.T, D.F, D.H); linear(D.T, D.H, D.F); linear(D.T, D.H, 3 * D.H); linear(D.T, D.H, D.H);
+  if (D.dec) linear(D.Te, D.H, 2 * D.H);
   return s;
 }
 
@@ -87,6 +86,12 @@ struct BwdBufs {
   void *dh1, *t0, *t1, *t2, *dqkv, *dkvx, *denc, *scratch;
   float *partial, *delta;
   size_t scratch_bytes, partial_floats;
+  k::PairPlan plans[5];  // how each of the layer's linears goes back, made once for its scratch and its launches
+  const k::PairPlan *plan(int rows, int in, int out) const {
+    for (const k::PairPlan &p : plans)
+      if (p.rows == rows && p.in == in && p.out == out) return &p;
+    return nullptr;
+  }
 };
 // `splits`: with room for partial products
 void bwd_layout(const Dims &D, Ws &w, BwdBufs *b, bool splits = true) {
@@ -103,6 +108,7 @@ void bwd_layout(const Dims &D, Ws &w, BwdBufs *b, bool splits = true) {
   // Partial products are a matter of speed only: they do not push a layer beyond what ssdt_layer_bwd_static can serve, and
   // a workspace without room for them will do.  All of it or none: sums come in one of two orders, whatever the size.
   const Scratch sc = bwd_scratch(D);
+  std::copy(std::begin(sc.plans), std::end(sc.plans), b->plans);
   const size_t base = up(w.used, 256) + 512;
   b->scratch_bytes = splits ? std::max(sc.copies, sc.splits) : sc.copies;
   if (base + sc.copies <= SSDT_STATIC_WS_BYTES) b->scratch_bytes = std::min(b->scratch_bytes, (SSDT_STATIC_WS_BYTES - base) / 256 * 256);
@@ -424,7 +430,7 @@ ssdt_status layer_bwd_impl(ssdt_ctx *ctx, const ssdt_layer_desc *desc, const ssd
     const bool apart = i0 + bytes <= o0 || o0 + bytes <= i0;
     hipError_t e = hipErrorNotSupported;
     g.colsum = db; g.colsum_accumulate = accum;
-    if (apart) e = dt == SSDT_F32 ? k::gemm_pair_f32(g, d, st) : k::gemm_pair_bf16(g, d, st);
+    if (apart) e = dt == SSDT_F32 ? k::gemm_pair_f32(g, d, st) : k::gemm_pair_bf16(g, d, bf.plan(rows, Kin, Nout), st);
     if (e != hipErrorNotSupported) return e;
     e = k::gemm(g, st);
     if (e == hipErrorNotSupported) {  // (operands that the kernels with the bias sums do not take)
