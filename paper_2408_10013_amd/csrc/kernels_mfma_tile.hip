@@ -59,8 +59,10 @@ constexpr int kSK = 64;  // k per stage (SK below: 64, or 128 where the wavefron
 //   touch at one unit lie in eight different groups of eight banks.
 //   A stage of 128 k: K-contiguous rows have 256 bytes, chunk c of row r at c ^ (r & 15); k-major rows of 64 bytes, four of
 //   which make up the 64 banks, have key (k >> 3) & 1.
-template <int ROWS, bool KM, int NT, int SK>
+//   BIG: an operand of 2^34 elements and more, whose end is kept in 64 bits.
+template <int ROWS, bool KM, int NT, int SK, bool BIG = false>
 struct Side {
+  typedef typename std::conditional<BIG, long, int>::type Ext;
   static constexpr int LJ = ROWS * SK / 8 / NT, CPR = (KM ? ROWS : SK) / 8;
   static constexpr unsigned kBytes = ROWS * SK * 2;
   static __device__ __forceinline__ int key(int i) {
@@ -78,29 +80,34 @@ struct Side {
     }
   }
   // Where the next stage starts, units of 16 bytes from there to the end of the operand (everything is a whole number of them;
-  // prepare() checks that 31 bits hold it) and from stage to stage, the k it starts at.
+  // prepare() sees whether 31 bits hold it) and from stage to stage, the k it starts at.  (Scalar instructions count: a small
+  // problem is one wavefront per SIMD, bound by what it issues.  With 64-bit extents a stage took 30 to 50 ns longer.)
   uint64_t at;
-  int left, step, k;
+  Ext left;
+  int step, k;
   // `ext` = the operand's extent in its own dimension, r0 / k0 = the tile's origin
   __device__ __forceinline__ void start(const uint16_t *base, long ld, int r0, int ext, int k0, int K) {
     at = (uint64_t)(uintptr_t)(KM ? base + (long)k0 * ld + r0 : base + (long)r0 * ld + k0);
-    left = (int)((KM ? (long)(K - 1 - k0) * ld + ext - r0 : (long)(ext - 1 - r0) * ld + K - k0) / 8);
+    left = (Ext)((KM ? (long)(K - 1 - k0) * ld + ext - r0 : (long)(ext - 1 - r0) * ld + K - k0) / 8);
     step = KM ? SK / 8 * (int)ld : SK / 8;
     k = k0;
   }
-  // The next stage piece by piece: its descriptor, piece j, and on to the stage behind it.
+  // The next stage piece by piece: its descriptor, piece j (tail: the stage may be the last one), and on to the stage behind it.
   __device__ __forceinline__ v4i_t desc() {
-    asm volatile("" : "+s"(at), "+s"(left));
+    asm volatile("" : "+s"(at), "+s"(left));  // (addresses computed ahead would fill the scalar registers)
     v4i_t rsrc;
     rsrc[0] = (int)(unsigned)at;
     rsrc[1] = (int)(unsigned)(at >> 32) & 0xffff;
-    const int rest = left & ~(left >> 31);
-    rsrc[2] = (rest >> 27) ? 0x7fffffff : rest << 4;
+    const Ext rest = left & ~(left >> (8 * sizeof(Ext) - 1));
+    rsrc[2] = (rest >> 27) ? 0x7fffffff : (int)rest << 4;  // (2^31 is out of range)
     rsrc[3] = 0x00020000;
+    // a scalar register written by a vector instruction (readfirstlane) needs five wait states before a vector memory
+    // instruction reads it; the compiler does not look into the loads' assembly for that
     asm volatile("s_nop 4" : "+s"(rsrc));
     return rsrc;
   }
   __device__ __forceinline__ void piece(const v4i_t &rsrc, int j, int K, unsigned dst, bool tail) {
+    // the tail of a K-contiguous row continues in the next row: such chunks are sent out of range
     const bool dead = !KM && tail && k + chunk * 8 >= K;
     load_lds16(rsrc, dead ? 0x80000000u : voff[j], dst + j * NT * 16);
   }
@@ -109,27 +116,13 @@ struct Side {
     left -= step;
     k += SK;
   }
-  // TAIL: the stage may be the last one.  (Scalar instructions count here: a small problem is one wavefront per SIMD, bound by
-  // what it issues.  With the descriptor's extent computed in 64 bits a stage took 30 to 50 ns longer.)
   __device__ __forceinline__ void load(int K, unsigned lds, int wave, bool tail) {
     unsigned dst = __builtin_amdgcn_readfirstlane(lds + wave * 1024);
-    asm volatile("" : "+s"(at), "+s"(left), "+s"(dst));  // (addresses computed ahead would fill the scalar registers)
-    v4i_t rsrc;
-    rsrc[0] = (int)(unsigned)at;
-    rsrc[1] = (int)(unsigned)(at >> 32) & 0xffff;
-    const int rest = left & ~(left >> 31);
-    rsrc[2] = (rest >> 27) ? 0x7fffffff : rest << 4;  // (2^31 is out of range)
-    rsrc[3] = 0x00020000;
-    // a scalar register written by a vector instruction (readfirstlane) needs five wait states before a vector memory
-    // instruction reads it; the compiler does not look into the loads' assembly for that
-    asm volatile("s_nop 4" : "+s"(rsrc));
-    // the tail of a K-contiguous row continues in the next row: such chunks are sent out of range
-    const bool dead = !KM && tail && k + chunk * 8 >= K;
+    asm volatile("" : "+s"(dst));
+    const v4i_t rsrc = desc();
 #pragma unroll
-    for (int j = 0; j < LJ; ++j) load_lds16(rsrc, dead ? 0x80000000u : voff[j], dst + j * NT * 16);
-    at += 16l * step;
-    left -= step;
-    k += SK;
+    for (int j = 0; j < LJ; ++j) piece(rsrc, j, K, dst, tail);
+    next();
   }
   // The same fragments from a lane's base of a step (k-major, a row of 256 bytes and more: the block is XOR-ed into it): one address
   // register instead of one for each block.
@@ -251,11 +244,11 @@ __device__ __forceinline__ void store_colsum(const TileP &p, int n, int split, f
 // One tile: workgroup `bid` of the problem's tiles_m * tiles_n * splits (tiles of a split after each other); 256 threads,
 // 2 x 2 wavefronts.
 // R: stages in the ring.  These kernels differ in nothing but tile, ring and speed: every output is the same sum in the same order.
-template <int BM, int BN, int R, bool AKM, bool BKM>
+template <int BM, int BN, int R, bool AKM, bool BKM, bool BIG = false>
 __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *smem) {
   constexpr int NT = 256, WGN = 2, WTM = BM / 2, WTN = BN / 2, TM = WTM / 16, TN = WTN / 16;
-  typedef Side<BM, AKM, NT, kSK> SA;
-  typedef Side<BN, BKM, NT, kSK> SB;
+  typedef Side<BM, AKM, NT, kSK, BIG> SA;
+  typedef Side<BN, BKM, NT, kSK, BIG> SB;
   constexpr unsigned kStage = SA::kBytes + SB::kBytes;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WGN, wn = wave % WGN;
@@ -738,15 +731,15 @@ __global__ __launch_bounds__(512) void gemm_wide_pair_k(TileP w, TileP d, int fi
 }
 
 // KW: wavefronts along k
-template <int BM, int BN, int R, bool KW, bool AKM, bool BKM>
+template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG = false>
 __device__ __forceinline__ void any_body(const TileP &p, int bid, uint16_t *smem) {
   if constexpr (KW) kwave_body<BM, BN, R, AKM, BKM>(p, bid, smem);
-  else tile_body<BM, BN, R, AKM, BKM>(p, bid, smem);
+  else tile_body<BM, BN, R, AKM, BKM, BIG>(p, bid, smem);
 }
-template <int BM, int BN, int R, bool KW, bool AKM, bool BKM>
+template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG>
 __global__ __launch_bounds__(256, 2) void gemm_tile_k(TileP p) {
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
-  any_body<BM, BN, R, KW, AKM, BKM>(p, blockIdx.x, smem);
+  any_body<BM, BN, R, KW, AKM, BKM, BIG>(p, blockIdx.x, smem);
 }
 
 // The two products of a linear's backward in one launch: the weight gradient (both operands k-major) and the input
@@ -821,16 +814,16 @@ static constexpr size_t smem_of() {
   constexpr size_t stages = (size_t)R * (BM + BN) * (KW ? 128 : kSK) * 2;
   return stg > stages ? stg : stages;
 }
-template <int BM, int BN, int R, bool KW, bool AKM, bool BKM>
+template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG = false>
 static hipError_t launch_tile(const TileP &p, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_k<BM, BN, R, KW, AKM, BKM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN, R, KW>());
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_k<BM, BN, R, KW, AKM, BKM, BIG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN, R, KW>());
     if (e != hipSuccess) return e;
     attr_set = true;
   }
   prof::Scope ps(prof::GEMM_MFMA_TILE, 2.0 * p.M * p.N * p.K, 0, s);
-  hipLaunchKernelGGL((gemm_tile_k<BM, BN, R, KW, AKM, BKM>), dim3(blocks_of(p)), dim3(256), (smem_of<BM, BN, R, KW>()), s, p);
+  hipLaunchKernelGGL((gemm_tile_k<BM, BN, R, KW, AKM, BKM, BIG>), dim3(blocks_of(p)), dim3(256), (smem_of<BM, BN, R, KW>()), s, p);
   hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : launch_reduce(p, s);
 }
@@ -860,9 +853,11 @@ static hipError_t launch_wide_pair(const TileP &w, const TileP &d, hipStream_t s
                      (int)(w_first ? blocks_of(w) : blocks_of(d)), w_first ? 1 : 0);
   return hipGetLastError();
 }
+constexpr int kBig = kCfgs;  // 128 x 128 with 64-bit extents
 template <bool AKM, bool BKM>
 static hipError_t launch_cfg(int cfg, const TileP &p, hipStream_t s) {
   switch (cfg) {
+    case kBig: return launch_tile<128, 128, 2, false, AKM, BKM, true>(p, s);
     case 0: return launch_tile<128, 128, 2, false, AKM, BKM>(p, s);
     case 1: return launch_tile<64, 128, 2, false, AKM, BKM>(p, s);
     case 2: return launch_tile<64, 64, 2, false, AKM, BKM>(p, s);
@@ -1140,8 +1135,9 @@ int gemm_tile_choice(int M, int N, int K, bool one_order) {
   return cfg;
 }
 
-// Checks what the kernel needs beyond the shape and fills its arguments, the choice of tile aside.
-static hipError_t prepare(const Gemm &g, TileP *p) {
+// Checks what the kernel needs beyond the shape and fills its arguments, the choice of tile aside.  *big: an operand whose extent 31
+// bits do not hold in units of 16 bytes (Side::left; w_2 of 524288 tokens, F 32776).
+static hipError_t prepare(const Gemm &g, TileP *p, bool *big) {
   if (!gemm_tile_fits(g.M, g.N, g.K, g.transA, g.transB, g.dtype)) return hipErrorNotSupported;
   const bool akm = g.transA, bkm = !g.transB;
   auto al16 = [](const void *q) { return ((uintptr_t)q & 15) == 0; };
@@ -1153,7 +1149,7 @@ static hipError_t prepare(const Gemm &g, TileP *p) {
     return hipErrorNotSupported;
   const long ea = akm ? (long)(g.K - 1) * g.lda + g.M : (long)(g.M - 1) * g.lda + g.K;
   const long eb = bkm ? (long)(g.K - 1) * g.ldb + g.N : (long)(g.N - 1) * g.ldb + g.K;
-  if ((ea | eb) >> 34) return hipErrorNotSupported;  // (Side::left)
+  *big = (ea | eb) >> 34;
   if (g.epi == EPI_BIAS_ACT && !g.C2) return hipErrorInvalidValue;
   if (g.epi == EPI_BIAS_RESID && !g.resid) return hipErrorInvalidValue;
   if (g.epi == EPI_ACTBWD && !g.aux) return hipErrorInvalidValue;
@@ -1176,14 +1172,17 @@ static size_t usable_scratch(const Gemm &g) { return g.split && g.scratch && ((u
 
 hipError_t gemm_mfma_tile_bf16(const Gemm &g, hipStream_t s) {
   TileP p;
-  hipError_t e = prepare(g, &p);
+  bool big;
+  hipError_t e = prepare(g, &p, &big);
   if (e != hipSuccess) return e;
   int cfg = 0, splits = 1;
   tile_plan(g.M, g.N, g.K, usable_scratch(g), g.one_order ? kOneOrder : kCfgs, &cfg, &splits);
   if (g_tile_cfg >= 0) cfg = g_tile_cfg;
   if (g_tile_splits > 0 && split_bytes(g.M, g.N, pinned_splits(g.transB)) <= g.scratch_bytes) splits = pinned_splits(g.transB);
   if (cfg == kWide) splits = 1;
+  if (big) cfg = 0;
   choose(&p, cfg, splits, (float *)g.scratch);
+  if (big) cfg = kBig;
   if (g.transA) return launch_cfg<true, true>(cfg, p, s);
   if (!g.transB) return launch_cfg<false, true>(cfg, p, s);
   return launch_cfg<false, false>(cfg, p, s);
@@ -1198,9 +1197,11 @@ hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, const PairPlan *plan, hi
   if (plan && plan->rows == w.K && plan->in == w.M && plan->out == w.N && plan->pair &&
       std::max(split_bytes(w.M, w.N, plan->sw), split_bytes(d.M, d.N, plan->sd)) <= half_of(scratch)) pp = *plan;
   else if (!pair_wanted(Shape{w.M, w.N, w.K}, Shape{d.M, d.N, d.K}, scratch, &pp)) return hipErrorNotSupported;
-  hipError_t e = prepare(w, &pw);
-  if (e == hipSuccess) e = prepare(d, &pd);
+  bool big_w, big_d;
+  hipError_t e = prepare(w, &pw, &big_w);
+  if (e == hipSuccess) e = prepare(d, &pd, &big_d);
   if (e != hipSuccess) return e;
+  if (big_w || big_d) return hipErrorNotSupported;  // (each by itself)
   if (g_tile_cfg >= 0) pp.cfg = g_tile_cfg;
   if (pp.cfg != kWide && !kPairCost[pp.cfg].fit) return hipErrorNotSupported;  // (pinned)
   if (g_tile_splits > 0) {

@@ -421,6 +421,42 @@ def test_more_workgroups_than_one_axis_of_a_grid_holds(dtype, B, S, A):
     assert max(errs.values()) <= hp.TOL[dtype], errs
 
 
+def test_operands_of_more_than_2_to_the_34_elements():
+    """524288 tokens, F 32776: the MLP's activations and their gradients as K-contiguous and as k-major operands, the tiles at their
+    far end included, by the matrix-core kernels.  First, middle and last sequences against the checker; all others have no
+    gradient."""
+    B, S, F = 8192, 64, 32776
+    some, v = [0, 1, B // 2, B - 1], dict(GPT, act="relu", dtype="bf16", S=S, H=8, A=1, F=F)
+    l, ref = runner.Layer(B=B, **v), runner.Layer(B=4, **v)
+    assert l.T * F >= 1 << 34
+    case = hp.make_layer_case(ref, 8950, bias_std=0.05)
+    st = runner.Stack([l], 2 * l.T * F + 64 * l.T * l.H + (64 << 20), 0, "cuda:0", budget_bytes=0)
+    hp.load_weights(l, case["w"], st.dev)
+    rows = torch.cat([torch.arange(b * S, (b + 1) * S) for b in some]).to(st.dev)
+    data = {k: torch.full((l.T, l.H), fill, dtype=torch.bfloat16, device=st.dev) for k, fill in (("x", 1), ("dy", 0))}
+    for k in data:
+        data[k][rows] = runner.to_device(case[k], "bf16", st.dev)
+    dx = torch.zeros_like(data["dy"])
+    sb.ssdt_profile(st.ctx, True)
+    sb.ssdt_step_begin(st.ctx, 1)
+    y, saved = sb.ssdt_layer_fwd(st.ctx, l.desc, l.wstruct, 0, data["x"].data_ptr(), 0, 0, st.ws_ptr, st.ws_bytes, st.stream)
+    sb.ssdt_layer_bwd(st.ctx, l.desc, l.wstruct, saved, 0, data["dy"].data_ptr(), dx.data_ptr(), 0, l.gstruct, st.ws_ptr, st.ws_bytes,
+                      st.stream)
+    torch.cuda.synchronize()
+    ran = {p["name"] for p in sb.ssdt_profile_read(st.ctx)}
+    sb.ssdt_profile(st.ctx, False)
+    res = {"y": runner.to_host(st.view(y, (l.T, l.H))[rows]), "dx": runner.to_host(dx[rows])}
+    g = runner.to_host(st.view(saved.e[sb.SV_NAMES.index("g")].ptr, (l.T, F))[rows])
+    res.update({k: runner.to_host(t) for k, t in l.g.items()})
+    st.close()
+    assert "gemm_tile_k" in ran and not ran & {"gemm_generic_k", "gemm_nt128_k", "transpose_k"}, ran
+    d = hp.oracle_desc(ref)
+    y_ref, sv = lo.layer_fwd(d, case["w"], case["x"])
+    dx_ref, _, gr = hp.layer_bwd_same_relu_decisions(d, case["w"], sv, case["dy"], None, g)
+    bad = {k: e for k, e in ((k, hp.rel_err(res[k], r)) for k, r in dict(gr, y=y_ref, dx=dx_ref).items()) if not e <= hp.TOL["bf16"]}
+    assert not bad, bad
+
+
 PRECISE = {
     "d32": dict(GPT, B=2, S=333, H=128, A=4, F=64),
     "d64": dict(BERT, B=2, S=333, H=128, A=2, F=64),
