@@ -364,6 +364,31 @@ def test_operands_that_are_not_16_byte_aligned(dtype, n, what):
     check_against_oracle(l, case, run_backward(l, case, x=x), hp.TOL[dtype])
 
 
+@pytest.mark.parametrize("n", [0, 1, 4])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_encoder_gradient_is_added_to_what_there_is(dtype, n):
+    """A decoder layer's gradient of the encoder output, by the product's epilogue (aligned) and by a pass of its own: added to a sum
+    of its own size, rounded to the type once or, in that pass, twice."""
+    l = runner.Layer(dtype=dtype, **dict(T5, B=3, S=37, S_kv=45, H=64, A=2, F=72))
+    case = hp.make_layer_case(l, 8750)
+    d = hp.oracle_desc(l)
+    _, sv = lo.layer_fwd(d, case["w"], case["x"], case["enc"], None)
+    _, ref, _ = lo.layer_bwd(d, case["w"], sv, case["dy"], None)
+    st = runner.Stack([l], 4 * runner.saved_bytes_per_layer(l) + (1 << 20), 0, "cuda:0", budget_bytes=0)
+    hp.load_weights(l, case["w"], st.dev)
+    x, dy, enc = (runner.to_device(case[k], dtype, st.dev) for k in ("x", "dy", "enc"))
+    start = torch.randn(enc.shape, generator=torch.Generator().manual_seed(87)).to(enc.dtype).to(st.dev) * float(np.abs(ref).max())
+    guard, dx = shifted(torch.cat([start, torch.full_like(start, 7)]), n), torch.empty_like(dy)
+    sb.ssdt_step_begin(st.ctx, 1)
+    _, saved = sb.ssdt_layer_fwd(st.ctx, l.desc, l.wstruct, 0, x.data_ptr(), enc.data_ptr(), 0, st.ws_ptr, st.ws_bytes, st.stream)
+    sb.ssdt_layer_bwd(st.ctx, l.desc, l.wstruct, saved, 0, dy.data_ptr(), dx.data_ptr(), guard.data_ptr(), l.gstruct, st.ws_ptr,
+                      st.ws_bytes, st.stream)
+    torch.cuda.synchronize()
+    got, behind = runner.to_host(guard[:len(start)]), runner.to_host(guard[len(start):])
+    st.close()
+    assert hp.rel_err(got, runner.to_host(start) + ref) <= hp.TOL[dtype] and (behind == 7).all()
+
+
 @pytest.mark.parametrize("name", list(SIZES))
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_edges_of_tiles(name, dtype):
