@@ -894,38 +894,39 @@ bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
   return !(transA && transB);  // (the layer has no such product)
 }
 
-// DISPATCH.  Predicted time of a problem in microseconds, fitted to what the products of 470 layers took inside the layer, weights and
-// activations where the layer has them (MI355X; 32 to 16000 tokens, widths 128 to 4200): 2288 products by themselves and 1476
-// linears' backwards, every tile and split.  The choice costs 1.3 % more than the best tile on average, a linear's backward 2.0 %.
-// (Fitted to products by themselves, operands in the caches and widths to 2048, it cost 4.4 and 5.6 %: 944 x 9984 x 3328 took 64 x
-// 128 tiles, 150 us, for 128 x 128, 84; the layer of 4 x 236 tokens, H 3328 1217 us against 1125 before those tiles came.)
+// DISPATCH.  Predicted time of a problem in microseconds, fitted to what the products of 525 layers took inside the layer: three layers
+// in turn, with and without the last-level cache emptied between two passes (MI355X; 32 to 16000 tokens, widths 128 to 4200; 3900 products
+// by themselves, 2000 linears' backwards, every tile and split).  The choice costs 1.5 % more than the best tile on average, a
+// linear's backward 1.7 %; on layers that were not fitted 1.6 and 2.1 %.  (Fitted to products by themselves, operands in the caches and
+// widths to 2048, it cost 4.8 and 5.1 %: 944 x 9984 x 3328 took 64 x 128 tiles, 147 us, for 128 x 128, 102; the layer of 4 x 236
+// tokens, H 3328 1217 us against 1125 before those tiles came.)
 // A launch takes z us and e for each tile of a compute unit.  Whole rounds of as many workgroups as fit take c for each of a unit's
 // and stage of 64 k; in the last one a stage takes a + b n when n workgroups share a unit, and never less than c for each of
 // them, averaged over the machine.  f: us for each megabyte that a stage's panels bring from memory to the XCDs (panels()): small tiles
 // read an operand more often than the L2s catch.
-//   128 x 128, ring of 2: 0.80 us alone, 0.56 each together (1.0 PFLOP/s on 4096 x 2048 x 8192, 512 tiles);
-//              ring of 4: 0.64, and alone it is: for 192 tiles and long K (1024 x 3072 x 8192: 77 us against 106);
-//    64 x 128, ring of 2: 0.34 each from three on: where three share a unit;
-//              ring of 3: 0.30 alone (2331 x 1024 x 4096, 296 tiles: 39 us against 52 and, 128 x 128, 44);
-//    64 x 64,  ring of 2: 0.18 each, four to a unit (160 KiB of LDS would hold a fifth, but it waits: 1056 tiles of 33 stages 47 us,
+//   128 x 128, ring of 2: 0.76 us alone, 0.56 each together (1.0 PFLOP/s on 4096 x 2048 x 8192, 512 tiles);
+//              ring of 4: 0.61, and alone it is: for 192 tiles and long K (1024 x 3072 x 8192: 77 us against 106);
+//    64 x 128, ring of 2: 0.33 each from three on: where three share a unit;
+//              ring of 3: 0.31 alone (2331 x 1024 x 4096, 296 tiles: 39 us against 52 and, 128 x 128, 44);
+//    64 x 64,  ring of 2: 0.20 each, four to a unit (160 KiB of LDS would hold a fifth, but it waits: 1056 tiles of 33 stages 47 us,
 //              1014 of 52 50);
-//              ring of 3: 0.19 alone: for the smaller (512 x 2304 x 576: 9 us, by 64 x 128 13).
-//   wavefronts along k (a stage of 128 counts twice): 64 x 64 0.17 alone; 32 x 64 0.11; 32 x 32 0.11: for fewer tiles than
+//              ring of 3: 0.20 alone: for the smaller (512 x 2304 x 576: 9 us, by 64 x 128 13).
+//   wavefronts along k (a stage of 128 counts twice): 64 x 64 0.18 alone; 32 x 64 0.14; 32 x 32 0.14: for fewer tiles than
 //              compute units, where a stage is bound by the LDS reads of one workgroup: of a 64 x 64 tile four wavefronts side by
 //              side read half as much as four quarters of it, and 32 x 32 tiles leave each unit a quarter of the loads.
 //              (256 x 256 x 1024 7.4 -> 5.2 us, 128 x 1280 x 5120 22.3 -> 14.6, 256 x 1280 x 5120 25.1 -> 17.7 by 32 x 64, 1024 x 1024
 //              x 4096 25.7 -> 21.6 by 64 x 64; both products of 256 x 256 -> 1024's backward 8.5 -> 6.0.)
-//  256 x 128: 0.97 us a stage, 0.70 in a last round that leaves much of the machine over.
-// Splitting the contraction costs a second launch and the partial products' way out and back, from the caches at about 8.6 TB/s.
+//  256 x 128: 0.94 us a stage, 0.69 in a last round that leaves much of the machine over.
+// Splitting the contraction costs a second launch and the partial products' way out and back, from the caches at about 12 TB/s.
 struct TileCost { double a, b, c, e, f, z; int fit; };  // fit: workgroups that share a compute unit at most
-static const TileCost kCost[kCfgs] = {{0.797, 0.003, 0.561, 2.467, 0, 6.771, 2},     {0.513, 0.054, 0.342, 0.76, 0.042, 5.291, 3},
-                                      {0.414, 0.034, 0.183, 0.627, 0.045, 4.394, 4}, {0.121, 0.18, 0.341, 1.685, 0.056, 6.116, 2},
-                                      {0.036, 0.151, 0.198, 0.506, 0.067, 4.985, 3}, {0.077, 0.436, 0.643, 5.364, 0, 6.31, 1},
-                                      {0.125, 0.044, 0.186, 1.233, 0.044, 5.442, 1}, {0.073, 0.04, 0.141, 0.498, 0.068, 4.251, 2},
-                                      {0.054, 0.057, 0.088, 0.561, 0.072, 3.782, 2}, {0.665, 0.03, 0.971, 9.136, 0, 6.072, 1}};
+static const TileCost kCost[kCfgs] = {{0.746, 0.01, 0.562, 2.776, 0, 7.409, 2},      {0.544, 0.078, 0.332, 0.536, 0.042, 5.313, 3},
+                                      {0.41, 0.041, 0.195, 0.568, 0.048, 4.39, 4},   {0.142, 0.17, 0.311, 1.486, 0.053, 5.658, 2},
+                                      {0.05, 0.153, 0.19, 0.412, 0.066, 4.996, 3},   {0.071, 0.437, 0.605, 5.625, 0, 6.424, 1},
+                                      {0.134, 0.042, 0.182, 1.33, 0.054, 4.884, 1},  {0.052, 0.089, 0.177, 0.478, 0.045, 4.333, 2},
+                                      {0.064, 0.073, 0.117, 0.418, 0.049, 3.756, 2}, {0.663, 0.026, 0.943, 9.984, 0, 6.252, 1}};
 constexpr int kMaxSplits = 8;
 static int stages_of(int K) { return (K + kSK - 1) / kSK; }
-static double reduce_cost(int M, int N, int splits) { return splits > 1 ? 3.1 + 8.0 * splits * M * N / 8.6e6 : 0.0; }
+static double reduce_cost(int M, int N, int splits) { return splits > 1 ? 3.1 + 8.0 * splits * M * N / 12e6 : 0.0; }
 // A problem in tiles of a kind: rows and columns of tiles, stages of 64 k.  (Everything from here to the launch is on the path of each
 // call: a layer's plans, forward and backward, take 1.5 to 4 us, candidates that cannot win are left out early.)
 struct Tiling { int tm, tn, stages; long n; };
@@ -967,7 +968,9 @@ static int most_halvings(int M, int N, int K, size_t scratch) {
 static bool few_tiles(int M, int N) { return (long)M * N < 96l * 128 * 128; }
 
 // The choice for a problem given `scratch` bytes for partial products, among the first `cfgs` tiles; returns its predicted time.
-static double tile_plan(int M, int N, int K, size_t scratch, int cfgs, int *cfg, int *splits) {
+// kmajor: both operands are, and a fragment of either is two LDS reads.  128 x 128 alone on a unit feels it most (4096 x 1024 x 8192 87 us
+// against 78 by two splits in a ring of two).
+static double tile_plan(int M, int N, int K, bool kmajor, size_t scratch, int cfgs, int *cfg, int *splits) {
   const int most = scratch ? most_halvings(M, N, K, scratch) : 0;
   const bool small = few_tiles(M, N);
   double best = 1e30;
@@ -982,7 +985,8 @@ static double tile_plan(int M, int N, int K, size_t scratch, int cfgs, int *cfg,
       const double fixed = q.z + q.e * tiles / 256.0 + reduce_cost(M, N, 1 << h);
       const double stage = full * q.c * q.fit + (rest ? std::max(q.a + q.b * ((rest + 255) / 256), q.c * rest / 256.0) : 0.0);
       if (fixed + stage * stages >= best) continue;
-      const double t = fixed + (stage + q.f * panels(p, c, 1 << h, q.fit)) * stages;
+      double t = fixed + (stage + q.f * panels(p, c, 1 << h, q.fit)) * stages;
+      if (kmajor && c == 5) t *= 1.05;
       if (t < best) { best = t; *cfg = c; *splits = 1 << h; }
     }
   }
@@ -993,11 +997,11 @@ static double tile_plan(int M, int N, int K, size_t scratch, int cfgs, int *cfg,
 // of both share the machine: it is done when the work is (c per tile and stage, and what of the shorter tiles runs beside
 // nothing at the end), or when the longest tile is.  Fitted by itself.  (fit 0: no pair, 128 x 128 in a ring of four and 64 x 64 along k
 // were never the choice.)
-static const TileCost kPairCost[kWide] = {{0.728, 0.004, 0.416, 2.047, 0.043, 2.839, 2}, {0.538, 0.005, 0.247, 0.627, 0.062, 3.051, 3},
-                                          {0.426, 0.006, 0.154, 0.506, 0.049, 2.888, 4}, {0.331, 0.006, 0.239, 1.622, 0.072, 3.034, 2},
-                                          {0.254, 0.0, 0.188, 0.494, 0.044, 3.158, 3},   {},
-                                          {},                                            {0.132, 0.007, 0.118, 0.973, 0.05, 2.852, 2},
-                                          {0.089, 0.008, 0.105, 0.902, 0.028, 2.923, 2}};
+static const TileCost kPairCost[kWide] = {{0.792, 0.014, 0.49, 1.087, 0.023, 4.489, 2}, {0.508, 0.029, 0.284, 0.385, 0.047, 3.035, 3},
+                                          {0.291, 0.04, 0.16, 0.296, 0.062, 2.816, 4},  {0.437, 0.005, 0.328, 1.165, 0.014, 2.865, 2},
+                                          {0.215, 0.01, 0.189, 0.389, 0.03, 2.72, 3},   {},
+                                          {},                                           {0.146, 0.008, 0.151, 0.463, 0.017, 2.706, 2},
+                                          {0.045, 0.032, 0.12, 0.39, 0.015, 2.908, 2}};
 // When `slots` workers are done that take n1 pieces of t1 each and then n2 of t2.
 static double deal(long n1, double t1, long n2, double t2, long slots) {
   struct { double at; long n; } g[64] = {{0.0, slots}};  // workers by the time they are free
@@ -1039,7 +1043,7 @@ static double pair_plan(const Shape &w, const Shape &d, size_t scratch, PairPlan
         const double nw = (double)(pw.n << hw), nd = (double)(pd.n << hd), n256 = (nw + nd) / 256.0;
         const double lw = (pw.stages + (1 << hw) - 1) >> hw, ld = (pd.stages + (1 << hd) - 1) >> hd;
         const double n = std::min((double)q.fit, std::ceil(n256));
-        const double tail = (n256 > q.fit ? 0.359 : 0.227) * std::min(lw, ld) * (q.a + q.b);
+        const double tail = (n256 > q.fit ? 0.421 : 0.115) * std::min(lw, ld) * (q.a + q.b);
         const double work = ((nw * lw + nd * ld) * q.c + (nw + nd) * q.e) / 256.0 + tail;
         double t = q.z + std::max(work, std::max(lw, ld) * (q.a + q.b * n) + q.e) + rw[hw] + rd[hd];
         if (t >= best) continue;
@@ -1048,13 +1052,23 @@ static double pair_plan(const Shape &w, const Shape &d, size_t scratch, PairPlan
       }
     }
   }
-  // Tiles of 256 x 128, one to a compute unit, by dealing them out: 0.89 us a stage, 4.1 a tile (4096 x 2048 -> 6144 219 -> 201 us; 8192 x
-  // 1024 -> 4096 136 -> 124; 4096 x 2048 -> 2048 73 -> 67; 5785 x 2048 -> 2048 103 -> 95).
+  // Tiles of 256 x 128, one to a compute unit, by dealing them out: 0.88 us a stage and 4 a tile (4096 x 2048 -> 6144 219 -> 195 us; 8192 x
+  // 1024 -> 4096 136 -> 124; 4096 x 2048 -> 2048 73 -> 67; 5785 x 2048 -> 2048 103 -> 95).  Against unsplit 128 x 128 tiles, the other
+  // choice at such sizes, their time by the table and their time by dealing them out count the same (2.5 % more than the best on
+  // average over 700 such linears, by either alone 2.7).
   const Tiling pw = tiling(w.M, w.N, w.K, kWide), pd = tiling(d.M, d.N, d.K, kWide);
-  const double tw = pw.stages * 0.894 + 4.06, td = pd.stages * 0.894 + 4.06;
-  if (pw.n + pd.n <= 2048 && 4.31 + std::max((pw.n * tw + pd.n * td) / 256.0, std::max(tw, td)) < best * 0.99) {
-    const double t = 4.31 + (pw.stages >= pd.stages ? deal(pw.n, tw, pd.n, td, 256) : deal(pd.n, td, pw.n, tw, 256));
-    if (t < best * 0.99) { best = t; out->cfg = kWide; out->sw = out->sd = 1; }
+  const double tw = pw.stages * 0.88 + 4.0, td = pd.stages * 0.88 + 4.0;
+  if (pw.n + pd.n <= 2048 && std::max((pw.n * tw + pd.n * td) / 256.0, std::max(tw, td)) < best * 1.1) {
+    const auto dealt = [](const Tiling &a, double ta, const Tiling &b, double tb, long slots) {
+      return a.stages >= b.stages ? deal(a.n, ta, b.n, tb, slots) : deal(b.n, tb, a.n, ta, slots);
+    };
+    const double wide = dealt(pw, tw, pd, td, 256), t = 12.94 + 0.907 * wide;
+    double against = best * 0.99 / t;
+    if (out->cfg == 0 && out->sw == 1 && out->sd == 1) {
+      const Tiling qw = tiling(w.M, w.N, w.K, 0), qd = tiling(d.M, d.N, d.K, 0);
+      against = best / t * (2.7 + dealt(qw, qw.stages * 0.95 + 2.2, qd, qd.stages * 0.95 + 2.2, 512)) / (2.7 + wide);
+    }
+    if (against > 1) { best = std::min(best, t); out->cfg = kWide; out->sw = out->sd = 1; }
   }
   return best;
 }
@@ -1102,7 +1116,7 @@ static bool pair_wanted(const Shape &w, const Shape &d, size_t scratch, PairPlan
   const double together = pair_plan(w, d, scratch, out);
   if (together < least_cost(w) + least_cost(d)) return true;
   int c, sp;
-  return together < tile_plan(w.M, w.N, w.K, scratch, kCfgs, &c, &sp) + tile_plan(d.M, d.N, d.K, scratch, kCfgs, &c, &sp);
+  return together < tile_plan(w.M, w.N, w.K, true, scratch, kCfgs, &c, &sp) + tile_plan(d.M, d.N, d.K, false, scratch, kCfgs, &c, &sp);
 }
 
 // Scratch that the choices for a linear's two backward products (rows tokens, in -> out) use where there is enough of it, each by
@@ -1115,8 +1129,8 @@ size_t gemm_linear_bwd_scratch_bytes(int rows, int in, int out, int dtype, PairP
   const bool tw = tiles_take(w, true, false), td = tiles_take(d, false, true);
   int c = 0, sw = 1, sd = 1;
   double alone = 0;
-  if (tw) alone += tile_plan(w.M, w.N, w.K, all, kCfgs, &c, &sw);
-  if (td) alone += tile_plan(d.M, d.N, d.K, all, kCfgs, &c, &sd);
+  if (tw) alone += tile_plan(w.M, w.N, w.K, true, all, kCfgs, &c, &sw);
+  if (td) alone += tile_plan(d.M, d.N, d.K, false, all, kCfgs, &c, &sd);
   const auto bytes_w = [&](int s) { return split_bytes(w.M, w.N, std::max(s, pinned_splits(false))); };
   const auto bytes_d = [&](int s) { return split_bytes(d.M, d.N, std::max(s, pinned_splits(true))); };
   size_t bytes = std::max(tw ? bytes_w(sw) : 0, td ? bytes_d(sd) : 0);
@@ -1131,7 +1145,7 @@ size_t gemm_linear_bwd_scratch_bytes(int rows, int in, int out, int dtype, PairP
 int gemm_tile_choice(int M, int N, int K, bool one_order) {
   if (gemm_large_fits(M, N, K, false, false, SSDT_BF16)) return -1;
   int cfg = 0, splits = 1;
-  tile_plan(M, N, K, 0, one_order ? kOneOrder : kCfgs, &cfg, &splits);
+  tile_plan(M, N, K, false, 0, one_order ? kOneOrder : kCfgs, &cfg, &splits);
   return cfg;
 }
 
@@ -1176,7 +1190,7 @@ hipError_t gemm_mfma_tile_bf16(const Gemm &g, hipStream_t s) {
   hipError_t e = prepare(g, &p, &big);
   if (e != hipSuccess) return e;
   int cfg = 0, splits = 1;
-  tile_plan(g.M, g.N, g.K, usable_scratch(g), g.one_order ? kOneOrder : kCfgs, &cfg, &splits);
+  tile_plan(g.M, g.N, g.K, g.transA, usable_scratch(g), g.one_order ? kOneOrder : kCfgs, &cfg, &splits);
   if (g_tile_cfg >= 0) cfg = g_tile_cfg;
   if (g_tile_splits > 0 && split_bytes(g.M, g.N, pinned_splits(g.transB)) <= g.scratch_bytes) splits = pinned_splits(g.transB);
   if (cfg == kWide) splits = 1;
