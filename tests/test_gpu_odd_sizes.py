@@ -1,6 +1,7 @@
 """The kernels that take any size, at the edges of their tiles: forward and backward of small layers against the CPU
-checker.  bf16 widths that are multiples of 8 go through the matrix-core GEMM with 64-deep stages and a split contraction; sizes as
-small as these choose its 64 x 64 tiles (fp32: 32 x 32), the larger tiles are pinned."""
+checker.  bf16 widths that are multiples of 8 go through the matrix-core GEMM; sizes as small as these choose its tiles of 32 x 32 to
+64 x 64 with the wavefronts side by side along k (fp32: 32 x 32) and split nothing by themselves: the larger tiles and the splits are
+pinned."""
 import ctypes
 
 import numpy as np
@@ -25,8 +26,8 @@ SIZES = {
     "tile_plus_one": dict(B=1, S=129, H=64, A=1, F=264),         # a tile with one row
     "stage_tail": dict(B=3, S=43, H=72, A=3, F=200),             # K = 72, 200, 129: tails of 8, 8 and 1 behind whole stages
     "narrow": dict(B=2, S=65, H=8, A=1, F=8),                    # one 16-byte chunk per row
-    "split_k": dict(B=1, S=40, H=64, A=1, F=2048),               # 32 stages on one tile: contraction split
-    "split_tokens": dict(B=5, S=333, H=64, A=1, F=128),          # 27 stages over tokens (the last one short), split, bias sums
+    "split_k": dict(B=1, S=40, H=64, A=1, F=2048),               # 32 stages of 64 on one tile
+    "split_tokens": dict(B=5, S=333, H=64, A=1, F=128),          # 27 stages of 64 over tokens (the last one short), bias sums
 }
 
 BERT = dict(GPT, arch="bert_postln", mask="keypad")
