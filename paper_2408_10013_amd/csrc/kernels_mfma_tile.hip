@@ -928,7 +928,7 @@ constexpr int kMaxSplits = 8;
 static int stages_of(int K) { return (K + kSK - 1) / kSK; }
 static double reduce_cost(int M, int N, int splits) { return splits > 1 ? 3.1 + 8.0 * splits * M * N / 12e6 : 0.0; }
 // A problem in tiles of a kind: rows and columns of tiles, stages of 64 k.  (Everything from here to the launch is on the path of each
-// call: a layer's plans, forward and backward, take 1.5 to 4 us, candidates that cannot win are left out early.)
+// call: a layer's plans, forward and backward, take 1.5 to 5 us, candidates that cannot win are left out early.)
 struct Tiling { int tm, tn, stages; long n; };
 static Tiling tiling(int M, int N, int K, int cfg) {
   const auto up = [](int x, int by) { return (x + by - 1) >> __builtin_ctz(by); };  // (all powers of two)
