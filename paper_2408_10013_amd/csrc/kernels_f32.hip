@@ -305,7 +305,7 @@ struct F32Direct {
     rsrc[1] = (int)(unsigned)(at >> 32) & 0xffff;
     rsrc[2] = (left & ~(left >> 31)) << 2;  // (no less than 0)
     rsrc[3] = 0x00020000;
-    asm volatile("s_nop 4" : "+s"(rsrc));  // (see Side::load of gemm_tile_k)
+    asm volatile("s_nop 4" : "+s"(rsrc));  // (see Side::desc of gemm_tile_k)
     const bool dead = MODE == KVEC && tail && k + chunk * 4 >= K;  // the tail of a row continues in the next row
 #pragma unroll
     for (int j = 0; j < 2; ++j) load_lds16(rsrc, dead ? 0x80000000u : voff[j], lds + j * 4096);
