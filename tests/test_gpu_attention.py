@@ -1,0 +1,100 @@
+"""bf16 attention of whole tiles by itself, forward and backward, against 64 bits: one block of 128 queries, more blocks than run at a
+time (a workgroup then does several), numbers of heads that the eight XCDs do and do not share evenly, sequences of few keys or none."""
+import ctypes
+import math
+
+import pytest
+import torch
+
+from paper_2408_10013_amd import binding as sb
+
+pytestmark = pytest.mark.gpu
+
+NONE, CAUSAL, KEYPAD = 0, 1, 2
+
+
+class Attn(ctypes.Structure):
+    """struct Attn of csrc/kernels.h."""
+    _fields_ = [(n, t) for t, names in [
+        (ctypes.c_int, "B A Sq Sk d"), (ctypes.c_float, "scale"), (ctypes.c_int, "mask"), (ctypes.c_void_p, "kv_len"), (ctypes.c_int, "dtype"),
+        (ctypes.c_void_p, "q k v"), (ctypes.c_long, "ldq ldk ldv"), (ctypes.c_void_p, "o"), (ctypes.c_long, "ldo"), (ctypes.c_void_p, "lse"),
+        (ctypes.c_bool, "ordered"), (ctypes.c_void_p, "dout"), (ctypes.c_long, "lddo"), (ctypes.c_void_p, "dq dk dv"),
+        (ctypes.c_long, "lddq lddk lddv"), (ctypes.c_void_p, "delta")] for n in names.split()]
+
+
+def call(name, a):
+    f = getattr(sb.lib(), "_ZN4ssdt1k8%sERKNS0_4AttnEP12ihipStream_t" % name)
+    f.argtypes, f.restype = [ctypes.POINTER(Attn), ctypes.c_void_p], ctypes.c_int
+    assert f(ctypes.byref(a), torch.cuda.current_stream().cuda_stream) == 0
+
+
+CASES = {
+    "one_block": (1, 1, 128, 128, 128, CAUSAL),
+    "one_block_d64": (1, 3, 128, 128, 64, CAUSAL),
+    "odd_heads_two_rounds": (3, 43, 640, 640, 64, CAUSAL),     # 645 blocks, a last row that is not full
+    "two_rounds": (4, 16, 1152, 1152, 128, CAUSAL),            # 576 blocks of nine to a head
+    "many_rounds": (1, 264, 768, 768, 128, CAUSAL),            # 1584
+    "few_keys": (5, 16, 512, 512, 64, KEYPAD),
+    "few_keys_many_rounds": (13, 8, 1024, 1024, 64, KEYPAD),
+    "few_keys_d128": (19, 8, 512, 512, 128, KEYPAD),
+    "cross": (2, 8, 128, 384, 64, NONE),
+    "cross_longer_queries": (9, 8, 1280, 128, 128, NONE),
+}
+LENGTHS = (0, 1, 63, 64, 65, 128, 200, 0, 0, 500)
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_attention_of_whole_tiles(name):
+    B, A, Sq, Sk, d, mask = CASES[name]
+    H, dev = A * d, "cuda:0"
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(len(name))
+    rnd = lambda *s: torch.randn(*s, generator=gen, device=dev).bfloat16()
+    q, k, v, do = rnd(B * Sq, H), rnd(B * Sk, H), rnd(B * Sk, H), rnd(B * Sq, H)
+    lens = [min(Sk, LENGTHS[b % len(LENGTHS)]) if mask == KEYPAD else Sk for b in range(B)]
+    ref = [t.double() for t in (q, k, v, do)]
+    for b, n in enumerate(lens):    # what lies behind the tile that holds the last key is never looked at
+        behind = slice(b * Sk + -(-n // 64) * 64, (b + 1) * Sk)
+        k[behind], v[behind] = math.nan, math.nan
+    kv_len = torch.tensor(lens, dtype=torch.int32, device=dev)
+    o, dq, dk, dv = (torch.full_like(t, math.nan) for t in (q, q, k, v))
+    lse, delta = torch.empty(B, A, Sq, device=dev), torch.empty(2, B, A, Sq, device=dev)
+    P = lambda t: t.data_ptr()
+    a = Attn(B, A, Sq, Sk, d, 1 / math.sqrt(d), mask, P(kv_len) if mask == KEYPAD else 0, sb.BF16, P(q), P(k), P(v), H, H, H,
+             P(o), H, P(lse), False, P(do), H, P(dq), P(dk), P(dv), H, H, H, P(delta))
+    call("attn_fwd", a)
+    for b, n in enumerate(lens):    # (the backward's tiles of padded keys may be read: zeros times zero probability)
+        k[b * Sk + n:(b + 1) * Sk], v[b * Sk + n:(b + 1) * Sk] = 0, 0
+    call("attn_bwd", a)
+    torch.cuda.synchronize()
+
+    def close(got, want, bound):
+        # `bound`: what one rounding to bf16 (8 bits: 2^-8 of the value) of each probability or dS can make of the sum; the result is
+        # rounded once more.  The fp32 sums and exponentials stay below 2^-16 of the sum of absolute values.
+        bound = 2 ** -8 * want.abs() + (1 + 2 ** -7) * bound + 1e-30
+        err = (got.double() - want).abs()
+        assert bool((err <= bound).all()), (err / bound).max().item()
+
+    heads = lambda t, b, n: t[b * n:(b + 1) * n].reshape(n, A, d).transpose(0, 1).contiguous()
+    flat = lambda t: t.transpose(0, 1).reshape(t.shape[1], H)
+    for b, n in enumerate(lens):
+        Q, K, V, DO = heads(ref[0], b, Sq), heads(ref[1], b, Sk), heads(ref[2], b, Sk), heads(ref[3], b, Sq)
+        s = torch.matmul(Q, K.transpose(1, 2).contiguous()) / math.sqrt(d)
+        if mask == CAUSAL:
+            s.masked_fill_(torch.ones(Sq, Sk, dtype=torch.bool, device=dev).triu(1), -math.inf)
+        s[:, :, n:] = -math.inf
+        p = torch.softmax(s, -1) if n else torch.zeros_like(s)
+        at, kat = slice(b * Sq, (b + 1) * Sq), slice(b * Sk, (b + 1) * Sk)
+        x, e = torch.matmul(p, V), 2 ** -8
+        close(o[at], flat(x), flat(torch.matmul(p * e, V.abs())))
+        want = torch.logsumexp(s, -1)
+        assert torch.equal(torch.isinf(lse[b].double()), torch.isinf(want))
+        assert n == 0 or bool(((lse[b].double() - want).abs() <= 1e-5 * (1 + want.abs())).all())
+        ds = torch.matmul(DO, V.transpose(1, 2).contiguous())
+        ds = p * (ds - (p * ds).sum(-1, keepdim=True)) / math.sqrt(d)
+        # delta is summed from the output as it is stored: rounded, and made of rounded probabilities
+        off = (DO.abs() * (x.abs() * e + torch.matmul(p * e, V.abs()))).sum(-1, keepdim=True)
+        off = ds.abs() * e + p * off / math.sqrt(d) * (1 + e)
+        close(dq[at], flat(torch.matmul(ds, K)), flat(torch.matmul(off, K.abs())))
+        close(dk[kat], flat(torch.matmul(ds.transpose(1, 2).contiguous(), Q)), flat(torch.matmul(off.transpose(1, 2).contiguous(), Q.abs())))
+        close(dv[kat], flat(torch.matmul(p.transpose(1, 2).contiguous(), DO)), flat(torch.matmul(p.transpose(1, 2).contiguous() * e, DO.abs())))
