@@ -48,6 +48,8 @@ struct TileP {
   int colsum_acc;
 };
 
+#define SSDT_FENCE __builtin_amdgcn_sched_barrier(0)
+
 constexpr int kSK = 64;  // k per stage (SK below: 64, or 128 where the wavefronts share a stage's k)
 
 // One operand's side of the loader and of the fragment reads.  ROWS: the tile's extent in this operand's own
@@ -241,12 +243,18 @@ __device__ __forceinline__ void store_colsum(const TileP &p, int n, int split, f
   *(uint2 *)(p.colsum + n) = pack4(v);
 }
 
-// One tile: workgroup `bid` of the problem's tiles_m * tiles_n * splits (tiles of a split after each other); 256 threads,
-// 2 x 2 wavefronts.
+// Wavefronts that share a tile, in two rows.  A ring of three or more has one or two workgroups on a compute unit: four wavefronts, one to
+// a SIMD, leave nothing to cover their waits for fragments and barriers, and the epilogue is theirs alone.  Eight: 128 x 128, ring of 4, 2331 x
+// 1024 x 4096 37.7 -> 31.1 us, 1024 x 2048 x 5120 45 -> 37, with GELU 2331 x 4096 x 1024 56 -> 44; 64 x 128, ring of 3, 1024 x 5120 x 2048 with GELU
+// 37.6 -> 34.5, 1024 x 2048 x 2048 15.0 -> 14.4.  (Wavefronts that do nothing but load, one, two or four of them: no faster.)
+constexpr int waves_of(int BM, int BN, int R) { return R >= 3 && BN == 128 ? 8 : 4; }
+constexpr int threads_of(int BM, int BN, int R, bool KW) { return KW ? 256 : 64 * waves_of(BM, BN, R); }
+
+// One tile: workgroup `bid` of the problem's tiles_m * tiles_n * splits (tiles of a split after each other).
 // R: stages in the ring.  These kernels differ in nothing but tile, ring and speed: every output is the same sum in the same order.
 template <int BM, int BN, int R, bool AKM, bool BKM, bool BIG = false>
 __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *smem) {
-  constexpr int NT = 256, WGN = 2, WTM = BM / 2, WTN = BN / 2, TM = WTM / 16, TN = WTN / 16;
+  constexpr int NW = waves_of(BM, BN, R), NT = 64 * NW, WGN = NW / 2, WTM = BM / 2, WTN = BN / WGN, TM = WTM / 16, TN = WTN / 16;
   typedef Side<BM, AKM, NT, kSK, BIG> SA;
   typedef Side<BN, BKM, NT, kSK, BIG> SB;
   constexpr unsigned kStage = SA::kBytes + SB::kBytes;
@@ -281,6 +289,11 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
   // of a stage's second step are the last of that stage, so its one barrier sits between the two steps: behind it the
   // next stage is read and the stage R further on is loaded over this one.  (Both steps of the next stage read behind the
   // barrier, into a second set of registers: 10 % slower.)
+  // DEALT: reads and loads stand one by one between the matrix instructions; in front of them, as the compiler has it, they keep
+  // 128-row tiles waiting (two on a unit: 1024 x 6144 x 2048 35.2 -> 31.2 us, 3000 x 2048 x 2048 33.7 -> 30.8).  With a ring of three or more the loads
+  // are spread over both steps; with two they have to land within the stage.  Four wavefronts with less to do each are 2 to 6 % faster in
+  // the compiler's order.
+  constexpr bool DEALT = BM == 128 || NW == 8;
   sa.start(p.A, p.lda, m0, p.M, s0 * kSK, p.K);
   sb.start(p.B, p.ldb, n0, p.N, s0 * kSK, p.K);
   bf16x8_t af[2][TM], bf[2][TN];
@@ -288,21 +301,28 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
     sa.load(p.K, lds0 + buf * kStage, wave, tail);
     sb.load(p.K, lds0 + buf * kStage + SA::kBytes, wave, tail);
   };
+  // fragment r of a step, in the order in which the matrix instructions want them
+  auto read_one = [&](int buf, int step, int r) {
+    if (r == 1) af[step][0] = SA::frag(lds0 + buf * kStage, wm * TM, step, lane);
+    else if (r <= TN) bf[step][r ? r - 1 : 0] = SB::frag(lds0 + buf * kStage + SA::kBytes, wn * TN + (r ? r - 1 : 0), step, lane);
+    else af[step][r - TN] = SA::frag(lds0 + buf * kStage, wm * TM + r - TN, step, lane);
+  };
   auto read_step = [&](int buf, int step) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j) bf[step][j] = SB::frag(lds0 + buf * kStage + SA::kBytes, wn * TN + j, step, lane);
+    for (int r = 0; r < TM + TN; ++r) read_one(buf, step, r);
+  };
+  auto add_sums = [&](int step) {
+    if (AKM && BKM && sum) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i) af[step][i] = SA::frag(lds0 + buf * kStage, wm * TM + i, step, lane);
+      for (int j = 0; j < TN; ++j) accs[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[step][j], ones.v, accs[j], 0, 0, 0);
+    }
   };
   auto mfma_step = [&](int step) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[step][j], af[step][i], acc[i][j], 0, 0, 0);
-    if (AKM && BKM && sum) {
-#pragma unroll
-      for (int j = 0; j < TN; ++j) accs[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[step][j], ones.v, accs[j], 0, 0, 0);
-    }
+    add_sums(step);
   };
   constexpr int L = SA::LJ + SB::LJ;  // a thread's loads per stage
   // What the epilogue reads is requested at the start of the last stage, when no load of a stage is on its way any more: read
@@ -323,20 +343,58 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
   };
   typedef std::integral_constant<int, R - 1> InFlight;
   typedef std::integral_constant<int, R - 2> InFlight2;
+  // The matrix instructions of a step, between them the reads of step `rstep` of buffer `rbuf` and pieces [l0, l1) of the next
+  // stage to load, which goes to buffer `lbuf`.
+  v4i_t ra, rb;
+  auto load_one = [&](int q, int lbuf, bool tail) {
+    const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + lbuf * kStage + wave * 1024);
+    if (q == 0) ra = sa.desc();
+    if (q < SA::LJ) sa.piece(ra, q, p.K, dst, tail);
+    if (q == SA::LJ - 1) sa.next();
+    if (q == SA::LJ) rb = sb.desc();
+    if (q >= SA::LJ) sb.piece(rb, q - SA::LJ, p.K, dst + SA::kBytes, tail);
+    if (q == L - 1) sb.next();
+  };
+  auto phase = [&](int step, bool read, int rbuf, int rstep, bool load, int lbuf, bool tail, auto first, auto last) {
+    constexpr int N = TM * TN, L0 = decltype(first)::value, L1 = decltype(last)::value;
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+      SSDT_FENCE;
+      acc[t / TN][t % TN] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[step][t % TN], af[step][t / TN], acc[t / TN][t % TN], 0, 0, 0);
+      SSDT_FENCE;
+      if (read) {
+#pragma unroll
+        for (int r = t; r < TM + TN; r += N) read_one(rbuf, rstep, r);
+      }
+      if (load) {
+#pragma unroll
+        for (int q = L0; q < L1; ++q)
+          if ((q - L0) * N / (L1 - L0) == t) load_one(q, lbuf, tail);
+      }
+    }
+    add_sums(step);
+    SSDT_FENCE;
+  };
+  typedef std::integral_constant<int, 0> None;
+  typedef std::integral_constant<int, R == 2 ? L : (L + 1) / 2> Some;
+  typedef std::integral_constant<int, L> All;
   // INNER: stage st + R exists and is not the last
   auto stage = [&](int st, int buf, auto inner) {
     constexpr bool INNER = decltype(inner)::value;
+    const bool more = INNER || st + 1 < nk, load = INNER || st + R < nk;
     if (!INNER && st + 1 == nk) fetch();
+    if (DEALT) {
+      phase(0, true, buf, 1, st > 0 && (INNER || st - 1 + R < nk), (buf + R - 1) % R, !INNER, Some(), All());
+      if (more) wait_stages<L>(INNER ? R : nk - 2 - st, InFlight2());
+      phase(1, more, (buf + 1) % R, 0, load, buf, !INNER, None(), Some());
+      return;
+    }
     read_step(buf, 1);
     mfma_step(0);
-    if (INNER || st + 1 < nk) {
+    if (more) {
       wait_stages<L>(INNER ? R : nk - 2 - st, InFlight2());
-      // (ring of four, one workgroup per compute unit: reads before loads, 128 x 1280 x 5120 49 -> 44 us; elsewhere the
-      // compiler's own order is the better one)
-      if (R < 4 && (INNER || st + R < nk)) load_stage(buf, !INNER);
+      if (load) load_stage(buf, !INNER);
       read_step((buf + 1) % R, 0);
-      if (R == 4) __builtin_amdgcn_sched_barrier(0);
-      if (R == 4 && (INNER || st + R < nk)) load_stage(buf, !INNER);
     }
     mfma_step(1);
   };
@@ -552,7 +610,6 @@ __device__ __forceinline__ void kwave_body(const TileP &p, int bid, uint16_t *sm
 // wavefront, dealt out between the blocks, three stages in a ring.
 // 4096 x 2048 x 8192 156 -> 136 us with a residual, K-contiguous 150 -> 129 (1.07 PFLOP/s; 145 at best by four-deep rings of 128 x
 // 128), 8192 x 1024 x 4096 81 -> 67, 4096 x 2048 x 2048 47 -> 39.  Both operands k-major only 103 -> 99: every fragment is two reads there.
-#define SSDT_FENCE __builtin_amdgcn_sched_barrier(0)
 template <bool AKM, bool BKM>
 __device__ __forceinline__ void wide_body(const TileP &p, int bid, uint16_t *smem) {
   constexpr int BM = 256, BN = 128, NT = 512, R = 3, MB = 8, NB = 4;
@@ -737,7 +794,7 @@ __device__ __forceinline__ void any_body(const TileP &p, int bid, uint16_t *smem
   else tile_body<BM, BN, R, AKM, BKM, BIG>(p, bid, smem);
 }
 template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG>
-__global__ __launch_bounds__(256, 2) void gemm_tile_k(TileP p) {
+__global__ __launch_bounds__(threads_of(BM, BN, R, KW), 2) void gemm_tile_k(TileP p) {
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   any_body<BM, BN, R, KW, AKM, BKM, BIG>(p, blockIdx.x, smem);
 }
@@ -747,7 +804,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_k(TileP p) {
 // second waits until the last workgroup of the first has finished; here the one with the longer tiles goes first and the
 // other fills the machine behind it.
 template <int BM, int BN, int R, bool KW>
-__global__ __launch_bounds__(256, 2) void gemm_tile_pair_k(TileP w, TileP d, int first, int w_first) {
+__global__ __launch_bounds__(threads_of(BM, BN, R, KW), 2) void gemm_tile_pair_k(TileP w, TileP d, int first, int w_first) {
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   const int bid = blockIdx.x;
   const bool head = bid < first;
@@ -810,7 +867,7 @@ static unsigned blocks_of(const TileP &p) { return (unsigned)(p.tiles_m * p.tile
 
 template <int BM, int BN, int R, bool KW>
 static constexpr size_t smem_of() {
-  constexpr size_t stg = KW ? (size_t)4 * BM * (BN + 4) * 4 + 4 * BN * 4 : (size_t)4 * 32 * (BN / 2 + 4) * 4;
+  constexpr size_t stg = KW ? (size_t)4 * BM * (BN + 4) * 4 + 4 * BN * 4 : (size_t)waves_of(BM, BN, R) * 32 * (BN * 2 / waves_of(BM, BN, R) + 4) * 4;
   constexpr size_t stages = (size_t)R * (BM + BN) * (KW ? 128 : kSK) * 2;
   return stg > stages ? stg : stages;
 }
@@ -823,7 +880,7 @@ static hipError_t launch_tile(const TileP &p, hipStream_t s) {
     attr_set = true;
   }
   prof::Scope ps(prof::GEMM_MFMA_TILE, 2.0 * p.M * p.N * p.K, 0, s);
-  hipLaunchKernelGGL((gemm_tile_k<BM, BN, R, KW, AKM, BKM, BIG>), dim3(blocks_of(p)), dim3(256), (smem_of<BM, BN, R, KW>()), s, p);
+  hipLaunchKernelGGL((gemm_tile_k<BM, BN, R, KW, AKM, BKM, BIG>), dim3(blocks_of(p)), dim3(threads_of(BM, BN, R, KW)), (smem_of<BM, BN, R, KW>()), s, p);
   hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : launch_reduce(p, s);
 }
@@ -880,7 +937,7 @@ static hipError_t launch_pair(const TileP &w, const TileP &d, hipStream_t s) {
   }
   prof::Scope ps(prof::GEMM_MFMA_TILE, 2.0 * w.M * w.N * w.K + 2.0 * d.M * d.N * d.K, 0, s);
   const bool w_first = w.stages_per_split >= d.stages_per_split;
-  hipLaunchKernelGGL((gemm_tile_pair_k<BM, BN, R, KW>), dim3(blocks_of(w) + blocks_of(d)), dim3(256), (smem_of<BM, BN, R, KW>()), s, w, d,
+  hipLaunchKernelGGL((gemm_tile_pair_k<BM, BN, R, KW>), dim3(blocks_of(w) + blocks_of(d)), dim3(threads_of(BM, BN, R, KW)), (smem_of<BM, BN, R, KW>()), s, w, d,
                      (int)(w_first ? blocks_of(w) : blocks_of(d)), w_first ? 1 : 0);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = launch_reduce(w, s);
@@ -905,7 +962,7 @@ bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
 // them, averaged over the machine.  f: us for each megabyte that a stage's panels bring from memory to the XCDs (panels()): small tiles
 // read an operand more often than the L2s catch.
 //   128 x 128, ring of 2: 0.76 us alone, 0.56 each together (1.0 PFLOP/s on 4096 x 2048 x 8192, 512 tiles);
-//              ring of 4: 0.61, and alone it is: for 192 tiles and long K (1024 x 3072 x 8192: 77 us against 106);
+//              ring of 4: 0.53, and alone it is: for 152 tiles and long K (2331 x 1024 x 4096: 31 us against 38 by 64 x 128);
 //    64 x 128, ring of 2: 0.33 each from three on: where three share a unit;
 //              ring of 3: 0.31 alone (2331 x 1024 x 4096, 296 tiles: 39 us against 52 and, 128 x 128, 44);
 //    64 x 64,  ring of 2: 0.20 each, four to a unit (160 KiB of LDS would hold a fifth, but it waits: 1056 tiles of 33 stages 47 us,
@@ -920,8 +977,8 @@ bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
 // Splitting the contraction costs a second launch and the partial products' way out and back, from the caches at about 12 TB/s.
 struct TileCost { double a, b, c, e, f, z; int fit; };  // fit: workgroups that share a compute unit at most
 static const TileCost kCost[kCfgs] = {{0.746, 0.01, 0.562, 2.776, 0, 7.409, 2},      {0.544, 0.078, 0.332, 0.536, 0.042, 5.313, 3},
-                                      {0.41, 0.041, 0.195, 0.568, 0.048, 4.39, 4},   {0.142, 0.17, 0.311, 1.486, 0.053, 5.658, 2},
-                                      {0.05, 0.153, 0.19, 0.412, 0.066, 4.996, 3},   {0.071, 0.437, 0.605, 5.625, 0, 6.424, 1},
+                                      {0.41, 0.041, 0.195, 0.568, 0.048, 4.39, 4},   {0.142, 0.17, 0.311, 1.1, 0.053, 5.658, 2},
+                                      {0.05, 0.153, 0.19, 0.412, 0.066, 4.996, 3},   {0.061, 0.379, 0.605, 5.625, 0, 6.424, 1},
                                       {0.134, 0.042, 0.182, 1.33, 0.054, 4.884, 1},  {0.052, 0.089, 0.177, 0.478, 0.045, 4.333, 2},
                                       {0.064, 0.073, 0.117, 0.418, 0.049, 3.756, 2}, {0.663, 0.026, 0.943, 9.984, 0, 6.252, 1}};
 constexpr int kMaxSplits = 8;
