@@ -240,7 +240,7 @@ __global__ __launch_bounds__(256) void norm_bwd_vec_k(const T *dy, const T *x, c
                                                       const T *gamma, const T *resid, T *dx, float *partial,
                                                       int rows, int H, int kind, int rows_per_chunk, int chunks, int col_blocks) {
   constexpr int CB = 64 * V16<T>::E, kSums = 2 * 4 * CB * 4, kGain = NCH * 64 * 16;
-  __shared__ __attribute__((aligned(16))) char lds[kSums > kGain ? kSums : kGain];  // either kind's: sums, or the gain vector
+  __shared__ __attribute__((aligned16)) char lds[kSums > kGain ? kSums : kGain];  // either kind's: sums, or the gain vector
   float (*sums)[CB] = (float (*)[CB])lds;
   const int n1 = chunks * col_blocks, bid = blockIdx.x;
   if (bid < n1) colreduce1<T, true>(dy, H, x, mean, rstd, kind, partial, rows, H, rows_per_chunk, chunks, bid % col_blocks, bid / col_blocks, sums, sums + 4);
@@ -248,10 +248,11 @@ __global__ __launch_bounds__(256) void norm_bwd_vec_k(const T *dy, const T *x, c
 }
 
 // delta[b, h, i] = sum_c o[b, i, h, c] dout[b, i, h, c] for rows that hold the heads side by side (head size a power of two of
-// 16 to 1024 bytes): one wavefront per token walks the row of o and of dout with 16-byte loads (d / E lanes per head), multiplies, and adds the lanes of a head together.
-// With lse2 set, also lse in the units that the matrix-core backward recomputes probabilities in (lse_base2).
+// 16 to 1024 bytes): 16-byte loads, d / E lanes per head, whose sums are added together.  With lse2 set, also lse in the units that the
+// matrix-core backward recomputes probabilities in (lse_base2).
+// Few tokens of up to two KiB: one wavefront per token walks the row.
 template <typename T>
-__global__ __launch_bounds__(256) void attn_delta_vec_k(const T *o, long ldo, const T *dO, long lddo, float *delta,
+__global__ __launch_bounds__(256) void attn_delta_row_k(const T *o, long ldo, const T *dO, long lddo, float *delta,
                                                         const float *lse, float *lse2, long rows, int Sq, int A, int d) {
   constexpr int E = V16<T>::E;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -275,6 +276,51 @@ __global__ __launch_bounds__(256) void attn_delta_vec_k(const T *o, long ldo, co
       delta[at] = s;
       if (lse2) lse2[at] = lse_base2(lse[at]);
     }
+  }
+}
+
+// Otherwise a workgroup has one KiB of 16 tokens' rows, each wavefront that of four: all on their way at once, and the sums stored, through
+// LDS, with the tokens of a head side by side.  What bounds it is memory: the trip there, which the kernel above makes once for each KiB,
+// and, with a store of 4 bytes per token and head, the lines they touch.  1 x 2048, 64 heads of 128: 23.0 -> 13.0 us; 16 x 2048 230 ->
+// 175; 4 x 1024, 16 heads 9.3 -> 8.5; 8 x 128, 32 heads of 64 5.7 -> 4.7.  (7 x 333, 16 heads of 64: 4.7, 5.1.)
+template <typename T>
+__global__ __launch_bounds__(256) void attn_delta_vec_k(const T *o, long ldo, const T *dO, long lddo, float *delta,
+                                                        const float *lse, float *lse2, long rows, int parts, int Sq, int A, int d) {
+  constexpr int E = V16<T>::E;
+  __shared__ float sums[64][17];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, H = A * d, lph = d / E, hp = 64 / lph;
+  const int part = blockIdx.x % parts, c = (part * 64 + lane) * E;
+  const long r0 = (long)(blockIdx.x / parts) * 16;
+  u32x4_nt a[4];
+  uint4 g[4];
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    const long row = r0 + w * 4 + n;
+    a[n] = u32x4_nt{0, 0, 0, 0};
+    g[n] = make_uint4(0, 0, 0, 0);
+    if (row < rows && c < H) {
+      a[n] = __builtin_nontemporal_load((const u32x4_nt *)(o + row * ldo + c));
+      g[n] = *(const uint4 *)(dO + row * lddo + c);  // read again by the backward kernels that follow
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    float x[E], y[E], s = 0.f;
+    V16<T>::get(make_uint4(a[n].x, a[n].y, a[n].z, a[n].w), x);
+    V16<T>::get(g[n], y);
+#pragma unroll
+    for (int t = 0; t < E; ++t) s = fmaf(x[t], y[t], s);
+    for (int m = 1; m < lph; m <<= 1) s += __shfl_xor(s, m, 64);
+    if ((lane & (lph - 1)) == 0) sums[lane / lph][w * 4 + n] = s;
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < hp * 16; k += 256) {
+    const int h = part * hp + k / 16;
+    const long row = r0 + k % 16;  // b * Sq + i
+    if (row >= rows || h >= A) continue;
+    const long at = (row / Sq * A + h) * Sq + row % Sq;
+    delta[at] = sums[k / 16][k % 16];
+    if (lse2) lse2[at] = lse_base2(lse[at]);
   }
 }
 
@@ -336,9 +382,14 @@ static hipError_t attn_delta_t(const void *o, long ldo, const void *dout, long l
   constexpr int E = V16<T>::E;
   const int lph = d / E;
   if (d % E || lph < 1 || lph > 64 || (lph & (lph - 1)) || ldo % E || lddo % E || !al16(o) || !al16(dout)) return hipErrorNotSupported;
-  const long rows = (long)B * Sq;
-  hipLaunchKernelGGL(attn_delta_vec_k<T>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, (const T *)o, ldo,
-                     (const T *)dout, lddo, delta, lse, lse2, rows, Sq, A, d);
+  const long rows = (long)B * Sq, blocks = (rows + 15) / 16;
+  const int parts = (A * d + 64 * E - 1) / (64 * E);  // KiB of a row
+  if ((parts > 2 || rows * parts >= 8192) && one_axis(blocks * parts))
+    hipLaunchKernelGGL(attn_delta_vec_k<T>, dim3((unsigned)(blocks * parts)), dim3(256), 0, s, (const T *)o, ldo, (const T *)dout, lddo, delta, lse,
+                       lse2, rows, parts, Sq, A, d);
+  else
+    hipLaunchKernelGGL(attn_delta_row_k<T>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, (const T *)o, ldo, (const T *)dout, lddo, delta, lse,
+                       lse2, rows, Sq, A, d);
   return hipGetLastError();
 }
 hipError_t attn_delta_vec(const void *o, long ldo, const void *dout, long lddo, float *delta, const float *lse, float *lse2,

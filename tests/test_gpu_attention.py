@@ -98,3 +98,27 @@ def test_attention_of_whole_tiles(name):
         close(dq[at], flat(torch.matmul(ds, K)), flat(torch.matmul(off, K.abs())))
         close(dk[kat], flat(torch.matmul(ds.transpose(1, 2).contiguous(), Q)), flat(torch.matmul(off.transpose(1, 2).contiguous(), Q.abs())))
         close(dv[kat], flat(torch.matmul(p.transpose(1, 2).contiguous(), DO)), flat(torch.matmul(p.transpose(1, 2).contiguous() * e, DO.abs())))
+
+
+@pytest.mark.parametrize("B,S,A,d,f32", [(1, 1, 1, 64, False), (3, 37, 16, 128, False), (5, 197, 43, 64, False), (9, 1000, 8, 64, False), (2, 131, 12, 64, True),
+                                         (7, 333, 3, 128, False), (64, 5, 96, 16, False)])
+def test_row_sums_of_the_backward(B, S, A, d, f32):
+    """delta = sum over a head's columns of o dO, one KiB of a token's row and more, tokens that do not fill the workgroups' sixteen."""
+    dev = "cuda:0"
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(S)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device=dev).to(torch.float32 if f32 else torch.bfloat16)
+    o, do, lse = rnd(B * S, A * d), rnd(B * S, A * d), torch.randn(B, A, S, generator=gen, device=dev)
+    lse[0, 0, 0] = -math.inf
+    out = torch.full((2, B, A, S), math.nan, device=dev)
+    f = sb.lib()._ZN4ssdt1k14attn_delta_vecEPKvlS2_lPfPKfS3_iiiiiP12ihipStream_t
+    f.argtypes = [ctypes.c_void_p, ctypes.c_long] * 2 + [ctypes.c_void_p] * 3 + [ctypes.c_int] * 5 + [ctypes.c_void_p]
+    assert f(o.data_ptr(), A * d, do.data_ptr(), A * d, out[0].data_ptr(), lse.data_ptr(), out[1].data_ptr(), B, S, A, d,
+             sb.F32 if f32 else sb.BF16, torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    prod = (o.double() * do.double()).reshape(B, S, A, d).permute(0, 2, 1, 3)
+    # d fused multiply-adds and additions in fp32, 2^-24 of the sum of absolute values each
+    assert bool(((out[0].double() - prod.sum(-1)).abs() <= d * 2.0 ** -24 * prod.abs().sum(-1)).all())
+    want = lse * 1.4426950408889634
+    want[0, 0, 0] = math.inf
+    assert torch.allclose(out[1], want, rtol=1e-6, atol=0)
