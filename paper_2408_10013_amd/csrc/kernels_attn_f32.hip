@@ -283,7 +283,8 @@ __device__ __forceinline__ void f32_dq(const FaF &p, int bx, int h, int b, float
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const bool in = j0 + kb * 16 + 4 * r + lq < own_lim && lse != -INFINITY;
-        s[kb][r] = in ? expf(s[kb][r] * p.scale - lse) * (dp[kb][r] - delta) : 0.f;
+        const float e = expf(in ? s[kb][r] * p.scale - lse : -INFINITY);
+        s[kb][r] = in ? e * (dp[kb][r] - delta) : 0.f;
       }
     cols_by_weights<D>(sK, s, lane, acc);
   }
@@ -338,7 +339,7 @@ __device__ __forceinline__ void f32_dkv(const FaF &p, int bx, int h, int b, floa
         const int i = ib * 16 + 4 * r + lq;
         const float lse = sLse[i];
         const bool in = kj < limit && lse != -INFINITY && !(p.mask == SSDT_MASK_CAUSAL && kj > i0 + i);
-        s[ib][r] = in ? expf(s[ib][r] * p.scale - lse) : 0.f;
+        s[ib][r] = expf(in ? s[ib][r] * p.scale - lse : -INFINITY);  // (not `in ? expf(..) : 0`: that is a branch per element)
         dp[ib][r] = in ? s[ib][r] * (dp[ib][r] - sDelta[i]) : 0.f;
       }
     cols_by_weights<D>(sdO, s, lane, dv);
