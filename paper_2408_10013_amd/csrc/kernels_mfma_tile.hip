@@ -962,7 +962,8 @@ bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
 // them, averaged over the machine.  f: us for each megabyte that a stage's panels bring from memory to the XCDs (panels()): small tiles
 // read an operand more often than the L2s catch.
 //   128 x 128, ring of 2: 0.76 us alone, 0.56 each together (1.0 PFLOP/s on 4096 x 2048 x 8192, 512 tiles);
-//              ring of 4: 0.53, and alone it is: for 152 tiles and long K (2331 x 1024 x 4096: 31 us against 38 by 64 x 128);
+//              ring of 4, eight wavefronts: 0.44, and alone on its unit always: for one round of tiles and long K (152 tiles of 2331 x 1024
+//              x 4096: 31 us against 38 by 64 x 128); 0.6 in whole rounds, where 128 x 128 with two buffers is the better one;
 //    64 x 128, ring of 2: 0.33 each from three on: where three share a unit;
 //              ring of 3: 0.31 alone (2331 x 1024 x 4096, 296 tiles: 39 us against 52 and, 128 x 128, 44);
 //    64 x 64,  ring of 2: 0.20 each, four to a unit (160 KiB of LDS would hold a fifth, but it waits: 1056 tiles of 33 stages 47 us,
