@@ -279,18 +279,33 @@ __global__ __launch_bounds__(256) void norm_bwd_k(const T *dy, const T *x, const
   else norm_bwd_dx<T>(dy, x, mean, rstd, gamma, resid, dx, rows, H, kind, bid - n1);
 }
 
-// Stage 2: 16 columns per block, sixteen threads per column each adding every sixteenth chunk (eight loads of either sum on
-// their way at once: all there are), their sums in order.  (One thread per column adding all chunks waited for 64 loads
-// one after the other: 20 to 28 us whatever the width; eight threads per column, 32 columns: 5 to 7.  The layer of 16 x 512,
-// H 1024 893 -> 889 us with sixteen, of 7 x 333 411.5 -> 408; level elsewhere.)
+// Stage 2: 16 columns per block, sixteen threads per column each adding every sixteenth chunk in turn, their sums in order.  What bounds it
+// is trips to memory.  Above 32 chunks eight loads of either sum are on their way at once, the last chunk read again past the end and
+// nothing added: a plain loop unrolled by eight leaves fewer than eight to its remainder, one trip each (the layer of 7 x 333, H 1024, 72 chunks: 382 ->
+// 380 us, 16 x 512, 128 chunks: 851 -> 847; up to 32 chunks, two trips, the plain loop is level or better by 0.5 us in 114).
+// (One thread per column adding all chunks: 20 to 28 us whatever the width; eight threads per column: the layer of 16 x 512, H 1024
+// 893 -> 889 us with sixteen, of 7 x 333 411.5 -> 408; level elsewhere.)
 template <typename T>
 __global__ __launch_bounds__(256) void colreduce2_k(const float *partial, int chunks, int cols, T *out_b, T *out_g, int accumulate) {
   __shared__ float sb[16][16], sg[16][16];
   const int cl = threadIdx.x & 15, grp = threadIdx.x >> 4, c = blockIdx.x * 16 + cl;
   float b = 0.f, g = 0.f;
   if (c < cols) {
-#pragma unroll 8
-    for (int k = grp; k < chunks; k += 16) {
+    for (int k0 = grp; chunks > 32 && k0 < chunks; k0 += 128) {
+      float vb[8], vg[8] = {};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) vb[i] = partial[(size_t)min(k0 + 16 * i, chunks - 1) * cols + c];
+      if (out_g) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) vg[i] = partial[(size_t)(chunks + min(k0 + 16 * i, chunks - 1)) * cols + c];
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        b += k0 + 16 * i < chunks ? vb[i] : 0.f;
+        g += k0 + 16 * i < chunks ? vg[i] : 0.f;
+      }
+    }
+    for (int k = grp; chunks <= 32 && k < chunks; k += 16) {
       b += partial[(size_t)k * cols + c];
       if (out_g) g += partial[(size_t)(chunks + k) * cols + c];
     }

@@ -413,6 +413,32 @@ def test_f32_norms_of_any_width(kind, H, A):
     check_against_oracle(l, case, run_single_layer(l, case, offload=False, fetch=False), hp.TOL["f32"])
 
 
+# 32 chunks and 33, where the second stage changes its loop, a last round of it that is not full, and all of its 128
+@pytest.mark.parametrize("rows", [32 * 32, 33 * 32, 72 * 32 + 27, 128 * 32, 6001])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_gain_and_shift_gradients_of_many_chunks(rows, accumulate):
+    H, dev = 40, "cuda:0"
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(rows)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device=dev)
+    dy, x, mean, rstd, gamma, old = rnd(rows, H), rnd(rows, H), rnd(rows), rnd(rows).abs() + 0.5, rnd(H), rnd(2, H)
+    dx, grads, partial = torch.empty_like(x), old.clone(), torch.full((2 * 128 * H,), float("nan"), device=dev)
+    f = sb.lib()._ZN4ssdt1k8norm_bwdEPKvS2_PKfS4_S2_S2_PvS5_S5_PfmiiiibP12ihipStream_t
+    f.argtypes = [ctypes.c_void_p] * 10 + [ctypes.c_size_t] + [ctypes.c_int] * 4 + [ctypes.c_bool, ctypes.c_void_p]
+    layernorm = 0
+    assert f(dy.data_ptr(), x.data_ptr(), mean.data_ptr(), rstd.data_ptr(), gamma.data_ptr(), None, dx.data_ptr(), grads[0].data_ptr(),
+             grads[1].data_ptr(), partial.data_ptr(), partial.numel(), rows, H, layernorm, sb.F32, accumulate,
+             torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    m, r = mean.double()[:, None], rstd.double()[:, None]
+    base = old.double() if accumulate else torch.zeros(2, H, dtype=torch.float64, device=dev)
+    # one addition per row of a chunk, eight chunks, sixteen threads and the old value, and three roundings of each term
+    eps = (-(-rows // min(rows // 32, 128)) + 8 + 16 + 1 + 3) * 2.0 ** -24
+    for got, term, size, b in ((grads[0], dy.double() * (x.double() - m) * r, dy.double().abs() * (x.double().abs() + m.abs()) * r, base[0]),
+                               (grads[1], dy.double(), dy.double().abs(), base[1])):
+        assert bool(((got.double() - b - term.sum(0)).abs() <= eps * (size.sum(0) + b.abs())).all())
+
+
 # One axis of a grid holds fewer than 2^24 workgroups of 256.  Attention by tiles: forward 65535 x 257 workgroups, backward
 # 2 x 65535 x 129.  Norm backward: one workgroup for four rows, and up to 128 for the first stage of the gain gradient.
 @pytest.mark.parametrize("dtype,B,S,A", [("bf16", 65535, 6, 257), ("bf16", 65535, 9, 129), ("bf16", 262143, 256, 1), ("f32", 262143, 256, 1)])
