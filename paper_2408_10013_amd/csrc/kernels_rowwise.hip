@@ -240,7 +240,7 @@ __global__ __launch_bounds__(256) void norm_bwd_vec_k(const T *dy, const T *x, c
                                                       const T *gamma, const T *resid, T *dx, float *partial,
                                                       int rows, int H, int kind, int rows_per_chunk, int chunks, int col_blocks) {
   constexpr int CB = 64 * V16<T>::E, kSums = 2 * 4 * CB * 4, kGain = NCH * 64 * 16;
-  __shared__ __attribute__((aligned16)) char lds[kSums > kGain ? kSums : kGain];  // either kind's: sums, or the gain vector
+  __shared__ __attribute__((aligned(16))) char lds[kSums > kGain ? kSums : kGain];  // either kind's: sums, or the gain vector
   float (*sums)[CB] = (float (*)[CB])lds;
   const int n1 = chunks * col_blocks, bid = blockIdx.x;
   if (bid < n1) colreduce1<T, true>(dy, H, x, mean, rstd, kind, partial, rows, H, rows_per_chunk, chunks, bid % col_blocks, bid / col_blocks, sums, sums + 4);
