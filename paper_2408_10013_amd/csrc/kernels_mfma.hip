@@ -97,7 +97,7 @@ __global__ __launch_bounds__(512) void gemm_nt256_k(NtP p) {
 // a load of the stage PTR points at into the LDS buffer whose wavefront base is SB
 #define SSDT_LD(SB, PTR, VOFF, LDSOFF)                                                                     \
   asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"                         \
-               :: "s"(SB), "v"(VOFF), "s"(PTR), "n"(LDSOFF) : "memory", "scc")
+               :: "s"(SB), "v"(VOFF), "s"(PTR), "n"(LDSOFF) : "memory", "scc", "m0")
 #define SSDT_LDA(SB, PA, j) SSDT_LD(SB, PA, voa[j], (j) * NT * 16)
 #define SSDT_LDB(SB, PB, j) SSDT_LD(SB, PB, vob[j], kBM2 * kBK2 * 2 + (j) * NT * 16)
 

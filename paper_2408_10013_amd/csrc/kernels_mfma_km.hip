@@ -167,7 +167,7 @@ __global__ __launch_bounds__(W * 64) void gemm_km256_k(NtP p) {
                    [pa] "s"(pa), [pb] "s"(pb), [voa] "v"(voa), [vob] "v"(vob), [ga0] "s"(ga0), [ga1] "s"(ga1), \
                    [gb0] "s"(gb0), [gb1] "s"(gb1), [la0] "n"(la0), [la1] "n"(la1), [lb0] "n"(lb0), [lb1] "n"(lb1) \
                    __VA_ARGS__                                                                             \
-                 : "memory", "scc")
+                 : "memory", "scc", "m0")
 #define SSDT_LOAD_STAGE(BUF)                                                                               \
   {                                                                                                        \
     unsigned ta_, tb_, va_, vb_;                                                                           \

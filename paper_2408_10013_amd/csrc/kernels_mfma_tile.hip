@@ -108,6 +108,8 @@ struct Side {
     asm volatile("s_nop 4" : "+s"(rsrc));
     return rsrc;
   }
+  // (Two wait states: in a kernel that spills no scalar registers nothing writes the descriptor between desc() and here.  With five
+  // each, rings of four took 1.6 % longer.)
   __device__ __forceinline__ void piece(const v4i_t &rsrc, int j, int K, unsigned dst, bool tail) {
     // the tail of a K-contiguous row continues in the next row: such chunks are sent out of range
     const bool dead = !KM && tail && k + chunk * 8 >= K;
@@ -293,7 +295,8 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
   // 128-row tiles waiting (two on a unit: 1024 x 6144 x 2048 35.2 -> 31.2 us, 3000 x 2048 x 2048 33.7 -> 30.8).  With a ring of three or more the loads
   // are spread over both steps; with two they have to land within the stage.  Four wavefronts with less to do each are 2 to 6 % faster in
   // the compiler's order.
-  constexpr bool DEALT = BM == 128 || NW == 8;
+  // (Nor with 64-bit extents, which would spill scalar registers.)
+  constexpr bool DEALT = (BM == 128 && !BIG) || NW == 8;
   sa.start(p.A, p.lda, m0, p.M, s0 * kSK, p.K);
   sb.start(p.B, p.ldb, n0, p.N, s0 * kSK, p.K);
   bf16x8_t af[2][TM], bf[2][TN];
