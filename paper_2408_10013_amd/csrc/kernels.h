@@ -172,6 +172,7 @@ extern int g_km_pf;       // stages that the L2 prefetch runs ahead (-1 = by sha
 extern int g_km_mode;  // 0 = off, 1 = for problems with a k-major operand (default), 2 = also for the NT form
 hipError_t attn_fwd_mfma_bf16(const Attn &a, hipStream_t s);
 hipError_t attn_bwd_mfma_bf16(const Attn &a, hipStream_t s);
+bool attn_few_keys(const Attn &a, long items);  // which of the forward's two kernels for whole tiles, by its blocks of 128 queries
 hipError_t attn_fwd_f32(const Attn &a, hipStream_t s);  // fp32 on the matrix cores, likewise
 hipError_t attn_bwd_f32(const Attn &a, hipStream_t s);
 

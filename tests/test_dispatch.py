@@ -1,4 +1,5 @@
-"""The choice of tile for bf16 forward products, against what the tiles were measured to take inside a layer (MI355X, us)."""
+"""The choice of tile for bf16 forward products, against what the tiles were measured to take inside a layer, and of kernel for whole-tile
+attention (MI355X, us)."""
 import ctypes
 import time
 
@@ -50,6 +51,31 @@ def test_the_256_tiles_are_left_alone_just_above_a_round(shape, large):
     """264 and 280 tiles: 534 us against 477 by 128 x 128 and 449 by 256 x 128, 346 against 343 and 309; 384 tiles: 94 against 107."""
     for one_order in (False, True):
         assert (choice(shape, one_order) == -1) == large
+
+
+class Attn(ctypes.Structure):
+    """The start of struct Attn of csrc/kernels.h."""
+    _fields_ = [(n, ctypes.c_int) for n in ("B", "A", "Sq", "Sk", "d")] + [("scale", ctypes.c_float), ("mask", ctypes.c_int), ("rest", ctypes.c_char * 256)]
+
+
+NONE, CAUSAL, KEYPAD = 0, 1, 2
+# B, heads, queries, keys, head size, mask: us by workgroups that take several blocks of queries in turn, and by one for each block
+ATTENTION = {
+    (8, 32, 128, 128, 64, CAUSAL): (7.5, 6.7), (8, 32, 128, 128, 64, NONE): (7.8, 6.8), (2, 2, 128, 128, 128, CAUSAL): (7.5, 6.9),
+    (16, 16, 128, 128, 64, KEYPAD): (8.0, 7.1), (32, 16, 128, 128, 128, NONE): (18.0, 16.0), (8, 32, 128, 256, 64, NONE): (9.9, 8.4),
+    (16, 16, 128, 256, 128, NONE): (15.1, 13.7), (40, 16, 128, 128, 64, NONE): (13.7, 12.5), (40, 16, 128, 512, 128, NONE): (57.0, 53.6),
+    (4, 64, 1024, 128, 64, KEYPAD): (27.3, 25.8), (10, 16, 512, 512, 128, NONE): (35.0, 37.8), (40, 16, 128, 128, 128, NONE): (21.1, 21.4),
+    (9, 8, 1280, 128, 128, NONE): (19.6, 20.8), (64, 16, 256, 256, 64, CAUSAL): (42.0, 44.0), (1, 8, 2048, 2048, 128, CAUSAL): (40.9, 43.5),
+}
+
+
+@pytest.mark.parametrize("shape", list(ATTENTION))
+def test_whole_tile_attention_takes_the_faster_kernel(shape):
+    B, A, Sq, Sk, d, mask = shape
+    f = sb.lib()._ZN4ssdt1k13attn_few_keysERKNS0_4AttnEl
+    f.argtypes, f.restype = [ctypes.POINTER(Attn), ctypes.c_long], ctypes.c_bool
+    deal, few = ATTENTION[shape]
+    assert f(ctypes.byref(Attn(B, A, Sq, Sk, d, 1.0, mask)), B * A * Sq // 128) == (few < deal)
 
 
 @pytest.mark.parametrize("B,S,H,F", [(8, 128, 2048, 5120), (3, 1000, 2048, 8192), (7, 333, 1024, 4096)])

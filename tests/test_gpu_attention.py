@@ -28,24 +28,41 @@ def call(name, a):
     assert f(ctypes.byref(a), torch.cuda.current_stream().cuda_stream) == 0
 
 
+def few_keys(B, A, Sq, Sk, d, mask, items):
+    f = sb.lib()._ZN4ssdt1k13attn_few_keysERKNS0_4AttnEl
+    f.argtypes, f.restype = [ctypes.POINTER(Attn), ctypes.c_long], ctypes.c_bool
+    return f(ctypes.byref(Attn(B, A, Sq, Sk, d, 1 / math.sqrt(d), mask)), items)
+
+
+# B, A, Sq, Sk, d, mask; the kernel: "few" keys, one block of 128 queries to a workgroup, or "deal", where workgroups take several in
+# turn; whether there are more blocks than workgroups that run at a time (768 at head size 64, 512 at 128)
 CASES = {
-    "one_block": (1, 1, 128, 128, 128, CAUSAL),
-    "one_block_d64": (1, 3, 128, 128, 64, CAUSAL),
-    "odd_heads_two_rounds": (3, 43, 640, 640, 64, CAUSAL),     # 645 blocks, a last row that is not full
-    "two_rounds": (4, 16, 1152, 1152, 128, CAUSAL),            # 576 blocks of nine to a head
-    "many_rounds": (1, 264, 768, 768, 128, CAUSAL),            # 1584
-    "few_keys": (5, 16, 512, 512, 64, KEYPAD),
-    "few_keys_many_rounds": (13, 8, 1024, 1024, 64, KEYPAD),
-    "few_keys_d128": (19, 8, 512, 512, 128, KEYPAD),
-    "cross": (2, 8, 128, 384, 64, NONE),
-    "cross_longer_queries": (9, 8, 1280, 128, 128, NONE),
+    "one_block": (1, 1, 128, 128, 128, CAUSAL, "few", False),
+    "one_block_d64": (1, 3, 128, 128, 64, CAUSAL, "few", False),
+    "few_keys": (5, 16, 512, 512, 64, KEYPAD, "few", False),
+    "few_keys_many_blocks": (27, 43, 384, 384, 64, KEYPAD, "few", True),   # 3483
+    "cross": (2, 8, 128, 384, 64, NONE, "few", False),
+    "cross_many_blocks": (35, 16, 128, 512, 128, NONE, "few", True),
+    "causal_512": (4, 5, 512, 512, 128, CAUSAL, "few", False),
+    "one_round": (3, 43, 640, 640, 64, CAUSAL, "deal", False),             # 645 blocks of 768 workgroups, a last row that is not full
+    "two_rounds": (4, 16, 1152, 1152, 128, CAUSAL, "deal", True),          # 576 blocks of nine to a head
+    "two_rounds_odd_heads": (3, 21, 1152, 1152, 128, CAUSAL, "deal", True),  # 567, numbers of heads that are no multiple of eight
+    "two_rounds_odd_heads_d64": (3, 43, 896, 896, 64, CAUSAL, "deal", True),  # 903
+    "padded_odd_heads": (7, 13, 1024, 1024, 128, KEYPAD, "deal", True),    # 728
+    "padded_odd_heads_d64": (9, 19, 640, 640, 64, KEYPAD, "deal", True),   # 855
+    "many_rounds": (1, 264, 768, 768, 128, CAUSAL, "deal", True),          # 1584
+    "padded_many_rounds": (13, 8, 1024, 1024, 64, KEYPAD, "deal", True),
+    "padded_d128": (19, 8, 512, 512, 128, KEYPAD, "deal", True),
+    "cross_longer_queries": (9, 8, 1280, 128, 128, NONE, "deal", True),
 }
 LENGTHS = (0, 1, 63, 64, 65, 128, 200, 0, 0, 500)
 
 
 @pytest.mark.parametrize("name", list(CASES))
 def test_attention_of_whole_tiles(name):
-    B, A, Sq, Sk, d, mask = CASES[name]
+    B, A, Sq, Sk, d, mask, kernel, rounds = CASES[name]
+    items = B * A * Sq // 128
+    assert few_keys(B, A, Sq, Sk, d, mask, items) == (kernel == "few") and (items > (768 if d == 64 else 512)) == rounds
     H, dev = A * d, "cuda:0"
     gen = torch.Generator(device=dev)
     gen.manual_seed(len(name))
