@@ -64,6 +64,13 @@ __device__ __forceinline__ void redo(unsigned again, F row) {
   for (; again; again &= again - 1) row(w * ROWS + __builtin_ctz(again), lane, w);
 }
 
+// The same for a caller that has no register left for the thread's index: it gives the wavefront and the lane.
+template <int ROWS, typename F>
+__device__ __forceinline__ void redo(unsigned again, int w, int lane, F row) {
+  __syncthreads();
+  for (; again; again &= again - 1) row(w * ROWS + __builtin_ctz(again), lane, w);
+}
+
 // The kernel's first argument, read again: what only the rare path needs then takes no registers before it.
 template <typename P>
 using late_args_t = const __attribute__((address_space(4))) P *;
