@@ -254,7 +254,7 @@ constexpr int threads_of(int BM, int BN, int R, bool KW) { return KW ? 256 : 64 
 
 // One tile: workgroup `bid` of the problem's tiles_m * tiles_n * splits (tiles of a split after each other).
 // R: stages in the ring.  These kernels differ in nothing but tile, ring and speed: every output is the same sum in the same order.
-template <int BM, int BN, int R, bool AKM, bool BKM, bool BIG = false>
+template <int BM, int BN, int R, bool AKM, bool BKM, bool BIG = false, bool DEAL = false>
 __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *smem) {
   constexpr int NW = waves_of(BM, BN, R), NT = 64 * NW, WGN = NW / 2, WTM = BM / 2, WTN = BN / WGN, TM = WTM / 16, TN = WTN / 16;
   typedef Side<BM, AKM, NT, kSK, BIG> SA;
@@ -292,11 +292,10 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
   // next stage is read and the stage R further on is loaded over this one.  (Both steps of the next stage read behind the
   // barrier, into a second set of registers: 10 % slower.)
   // DEALT: reads and loads stand one by one between the matrix instructions; in front of them, as the compiler has it, they keep
-  // 128-row tiles waiting (two on a unit: 1024 x 6144 x 2048 35.2 -> 31.2 us, 3000 x 2048 x 2048 33.7 -> 30.8).  With a ring of three or more the loads
-  // are spread over both steps; with two they have to land within the stage.  Four wavefronts with less to do each are 2 to 6 % faster in
-  // the compiler's order.
-  // (Nor with 64-bit extents, which would spill scalar registers.)
-  constexpr bool DEALT = (BM == 128 && !BIG) || NW == 8;
+  // eight wavefronts on a tile waiting, and four where two workgroups share the unit (see deal_of; 1024 x 6144 x 2048 32.4 -> 29.6 us, 3000 x
+  // 2048 x 2048 33.6 -> 30.6).  With a ring of three or more the loads are spread over both steps; with two they have to land within the stage.
+  // Four wavefronts alone on a unit, or with less to do each, are 1 to 6 % faster in the compiler's order.
+  constexpr bool DEALT = NW == 8 || DEAL;
   sa.start(p.A, p.lda, m0, p.M, s0 * kSK, p.K);
   sb.start(p.B, p.ldb, n0, p.N, s0 * kSK, p.K);
   bf16x8_t af[2][TM], bf[2][TN];
@@ -791,15 +790,15 @@ __global__ __launch_bounds__(512) void gemm_wide_pair_k(TileP w, TileP d, int fi
 }
 
 // KW: wavefronts along k
-template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG = false>
+template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG = false, bool DEAL = false>
 __device__ __forceinline__ void any_body(const TileP &p, int bid, uint16_t *smem) {
   if constexpr (KW) kwave_body<BM, BN, R, AKM, BKM>(p, bid, smem);
-  else tile_body<BM, BN, R, AKM, BKM, BIG>(p, bid, smem);
+  else tile_body<BM, BN, R, AKM, BKM, BIG, DEAL>(p, bid, smem);
 }
-template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG>
+template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG, bool DEAL>
 __global__ __launch_bounds__(threads_of(BM, BN, R, KW), 2) void gemm_tile_k(TileP p) {
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
-  any_body<BM, BN, R, KW, AKM, BKM, BIG>(p, blockIdx.x, smem);
+  any_body<BM, BN, R, KW, AKM, BKM, BIG, DEAL>(p, blockIdx.x, smem);
 }
 
 // The two products of a linear's backward in one launch: the weight gradient (both operands k-major) and the input
@@ -874,16 +873,22 @@ static constexpr size_t smem_of() {
   constexpr size_t stages = (size_t)R * (BM + BN) * (KW ? 128 : kSK) * 2;
   return stg > stages ? stg : stages;
 }
-template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG = false>
+// Whether four wavefronts on 128 x 128 deal out their reads and loads between the matrix instructions (see tile_body): where the last
+// round of workgroups has two to a unit.  Time in the compiler's order against it, 633 forward products: 1.01 to 1.04 there, up to 1.15; 0.96 to 1.0
+// where the last round has one to a unit, 0.98 with up to eight stages.  Backward products, alone or both in one launch: 0.96 to 1.0, 0.994 on average
+// over 300 pairs; they keep the compiler's order.
+static bool deal_of(const TileP &p) { return p.K > 512 && (blocks_of(p) - 1) % 512 >= 256; }
+
+template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG = false, bool DEAL = false>
 static hipError_t launch_tile(const TileP &p, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_k<BM, BN, R, KW, AKM, BKM, BIG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN, R, KW>());
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_k<BM, BN, R, KW, AKM, BKM, BIG, DEAL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN, R, KW>());
     if (e != hipSuccess) return e;
     attr_set = true;
   }
   prof::Scope ps(prof::GEMM_MFMA_TILE, 2.0 * p.M * p.N * p.K, 0, s);
-  hipLaunchKernelGGL((gemm_tile_k<BM, BN, R, KW, AKM, BKM, BIG>), dim3(blocks_of(p)), dim3(threads_of(BM, BN, R, KW)), (smem_of<BM, BN, R, KW>()), s, p);
+  hipLaunchKernelGGL((gemm_tile_k<BM, BN, R, KW, AKM, BKM, BIG, DEAL>), dim3(blocks_of(p)), dim3(threads_of(BM, BN, R, KW)), (smem_of<BM, BN, R, KW>()), s, p);
   hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : launch_reduce(p, s);
 }
@@ -918,7 +923,11 @@ template <bool AKM, bool BKM>
 static hipError_t launch_cfg(int cfg, const TileP &p, hipStream_t s) {
   switch (cfg) {
     case kBig: return launch_tile<128, 128, 2, false, AKM, BKM, true>(p, s);
-    case 0: return launch_tile<128, 128, 2, false, AKM, BKM>(p, s);
+    case 0:
+      if constexpr (!AKM && BKM) {
+        if (deal_of(p)) return launch_tile<128, 128, 2, false, AKM, BKM, false, true>(p, s);
+      }
+      return launch_tile<128, 128, 2, false, AKM, BKM>(p, s);
     case 1: return launch_tile<64, 128, 2, false, AKM, BKM>(p, s);
     case 2: return launch_tile<64, 64, 2, false, AKM, BKM>(p, s);
     case 3: return launch_tile<64, 128, 3, false, AKM, BKM>(p, s);

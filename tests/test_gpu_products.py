@@ -1,0 +1,60 @@
+"""bf16 products by themselves: kernels of one tile that differ in the order in which they load and read, not in that of their sums."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2408_10013_amd import binding as sb
+
+pytestmark = pytest.mark.gpu
+P, I, L, B = ctypes.c_void_p, ctypes.c_int, ctypes.c_long, ctypes.c_bool
+
+
+class Gemm(ctypes.Structure):
+    """struct Gemm of csrc/kernels.h."""
+    _fields_ = [("M", I), ("N", I), ("K", I), ("A", P), ("lda", L), ("transA", B), ("B", P), ("ldb", L), ("transB", B), ("C", P), ("ldc", L),
+                ("epi", I), ("bias", P), ("resid", P), ("ldr", L), ("C2", P), ("aux", P), ("act", I), ("dtype", I), ("colsum", P),
+                ("colsum_accumulate", B), ("scratch", P), ("scratch_bytes", ctypes.c_size_t), ("split", B), ("one_order", B), ("ordered", B)]
+
+
+@pytest.fixture
+def tile():
+    hook = ctypes.c_int.in_dll(sb.lib(), "_ZN4ssdt1k10g_tile_cfgE")
+
+    def pin(cfg):
+        hook.value = cfg
+    yield pin
+    hook.value = -1
+
+
+def rnd(*shape):
+    return torch.randn(*shape, device="cuda:0").bfloat16()
+
+
+def close(got, a, b):
+    """To the last bit but for the fp32 sums: a result rounded to bf16, 2^-9 of it, and K additions of 2^-24 of the absolute sum."""
+    a, b = a.double(), b.double()
+    want, size = a @ b, a.abs() @ b.abs()
+    assert bool(((got.double() - want).abs() <= 2.0 ** -8 * want.abs() + a.shape[1] * 2.0 ** -24 * size).all())
+
+
+# 128 x 128 tiles; "dealt": the last round of 512 workgroups holds more than 256 and there are more than eight stages of 64 k
+@pytest.mark.parametrize("M,N,K,dealt", [(2300, 1920, 584, True), (2176, 2048, 520, True), (2100, 1928, 1000, True), (5000, 2560, 528, True),
+                                         (4090, 2040, 640, True), (2300, 1920, 512, False), (2048, 2048, 576, False), (2400, 3440, 640, False)])
+def test_loads_and_reads_dealt_out(tile, M, N, K, dealt):
+    """270, 272, 272, 800 and 512 tiles, 270 with too few stages, 256 and 513; contractions with tails, of 9 stages and more."""
+    tiles = -(-M // 128) * -(-N // 128)
+    assert dealt == (K > 512 and (tiles - 1) % 512 >= 256)
+    torch.manual_seed(M)
+    a, b, out = rnd(M, K), rnd(K, N), []
+    f = sb.lib()._ZN4ssdt1k4gemmERKNS0_4GemmEP12ihipStream_t
+    f.argtypes, f.restype = [ctypes.POINTER(Gemm), ctypes.c_void_p], ctypes.c_int
+    for cfg in (0, 1):  # 1: 64 x 128, the compiler's order always
+        tile(cfg)
+        c = torch.full((M, N), float("nan"), device="cuda:0", dtype=torch.bfloat16)
+        g = Gemm(M=M, N=N, K=K, A=a.data_ptr(), lda=K, B=b.data_ptr(), ldb=N, C=c.data_ptr(), ldc=N, dtype=sb.BF16)
+        assert f(ctypes.byref(g), torch.cuda.current_stream().cuda_stream) == 0
+        out.append(c)
+    torch.cuda.synchronize()
+    assert torch.equal(*out)
+    close(out[0], a, b)
