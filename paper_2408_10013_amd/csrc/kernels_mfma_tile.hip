@@ -250,13 +250,13 @@ __device__ __forceinline__ void store_colsum(const TileP &p, int n, int split, f
 // 1024 x 4096 37.7 -> 31.1 us, 1024 x 2048 x 5120 45 -> 37, with GELU 2331 x 4096 x 1024 56 -> 44; 64 x 128, ring of 3, 1024 x 5120 x 2048 with GELU
 // 37.6 -> 34.5, 1024 x 2048 x 2048 15.0 -> 14.4.  (Wavefronts that do nothing but load, one, two or four of them: no faster.)
 constexpr int waves_of(int BM, int BN, int R) { return R >= 3 && BN == 128 ? 8 : 4; }
-constexpr int threads_of(int BM, int BN, int R, bool KW) { return KW ? 256 : 64 * waves_of(BM, BN, R); }
+constexpr int threads_of(bool KW, int NW) { return KW ? 256 : 64 * NW; }
 
 // One tile: workgroup `bid` of the problem's tiles_m * tiles_n * splits (tiles of a split after each other).
 // R: stages in the ring.  These kernels differ in nothing but tile, ring and speed: every output is the same sum in the same order.
-template <int BM, int BN, int R, bool AKM, bool BKM, bool BIG = false, bool DEAL = false>
+template <int BM, int BN, int R, bool AKM, bool BKM, bool BIG = false, bool DEAL = false, int NW = waves_of(BM, BN, R)>
 __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *smem) {
-  constexpr int NW = waves_of(BM, BN, R), NT = 64 * NW, WGN = NW / 2, WTM = BM / 2, WTN = BN / WGN, TM = WTM / 16, TN = WTN / 16;
+  constexpr int NT = 64 * NW, WGN = NW / 2, WTM = BM / 2, WTN = BN / WGN, TM = WTM / 16, TN = WTN / 16;
   typedef Side<BM, AKM, NT, kSK, BIG> SA;
   typedef Side<BN, BKM, NT, kSK, BIG> SB;
   constexpr unsigned kStage = SA::kBytes + SB::kBytes;
@@ -790,13 +790,13 @@ __global__ __launch_bounds__(512) void gemm_wide_pair_k(TileP w, TileP d, int fi
 }
 
 // KW: wavefronts along k
-template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG = false, bool DEAL = false>
+template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG = false, bool DEAL = false, int NW = waves_of(BM, BN, R)>
 __device__ __forceinline__ void any_body(const TileP &p, int bid, uint16_t *smem) {
   if constexpr (KW) kwave_body<BM, BN, R, AKM, BKM>(p, bid, smem);
-  else tile_body<BM, BN, R, AKM, BKM, BIG, DEAL>(p, bid, smem);
+  else tile_body<BM, BN, R, AKM, BKM, BIG, DEAL, NW>(p, bid, smem);
 }
 template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG, bool DEAL>
-__global__ __launch_bounds__(threads_of(BM, BN, R, KW), 2) void gemm_tile_k(TileP p) {
+__global__ __launch_bounds__(threads_of(KW, waves_of(BM, BN, R)), 2) void gemm_tile_k(TileP p) {
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   any_body<BM, BN, R, KW, AKM, BKM, BIG, DEAL>(p, blockIdx.x, smem);
 }
@@ -805,13 +805,13 @@ __global__ __launch_bounds__(threads_of(BM, BN, R, KW), 2) void gemm_tile_k(Tile
 // gradient (both K-contiguous) read the same dY and do not depend on each other.  Launched one after the other, the
 // second waits until the last workgroup of the first has finished; here the one with the longer tiles goes first and the
 // other fills the machine behind it.
-template <int BM, int BN, int R, bool KW>
-__global__ __launch_bounds__(threads_of(BM, BN, R, KW), 2) void gemm_tile_pair_k(TileP w, TileP d, int first, int w_first) {
+template <int BM, int BN, int R, bool KW, int NW>
+__global__ __launch_bounds__(threads_of(KW, NW), 2) void gemm_tile_pair_k(TileP w, TileP d, int first, int w_first) {
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   const int bid = blockIdx.x;
   const bool head = bid < first;
-  if (head == (w_first != 0)) any_body<BM, BN, R, KW, true, true>(w, head ? bid : bid - first, smem);
-  else any_body<BM, BN, R, KW, false, false>(d, head ? bid : bid - first, smem);
+  if (head == (w_first != 0)) any_body<BM, BN, R, KW, true, true, false, false, NW>(w, head ? bid : bid - first, smem);
+  else any_body<BM, BN, R, KW, false, false, false, false, NW>(d, head ? bid : bid - first, smem);
 }
 
 // Second half of a split product: adds the partial products in the order of the splits and applies the epilogue;
@@ -888,7 +888,7 @@ static hipError_t launch_tile(const TileP &p, hipStream_t s) {
     attr_set = true;
   }
   prof::Scope ps(prof::GEMM_MFMA_TILE, 2.0 * p.M * p.N * p.K, 0, s);
-  hipLaunchKernelGGL((gemm_tile_k<BM, BN, R, KW, AKM, BKM, BIG, DEAL>), dim3(blocks_of(p)), dim3(threads_of(BM, BN, R, KW)), (smem_of<BM, BN, R, KW>()), s, p);
+  hipLaunchKernelGGL((gemm_tile_k<BM, BN, R, KW, AKM, BKM, BIG, DEAL>), dim3(blocks_of(p)), dim3(threads_of(KW, waves_of(BM, BN, R))), (smem_of<BM, BN, R, KW>()), s, p);
   hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : launch_reduce(p, s);
 }
@@ -939,17 +939,17 @@ static hipError_t launch_cfg(int cfg, const TileP &p, hipStream_t s) {
     default: return launch_wide<AKM, BKM>(p, s);
   }
 }
-template <int BM, int BN, int R, bool KW>
+template <int BM, int BN, int R, bool KW, int NW = waves_of(BM, BN, R)>
 static hipError_t launch_pair(const TileP &w, const TileP &d, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_pair_k<BM, BN, R, KW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN, R, KW>());
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_pair_k<BM, BN, R, KW, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN, R, KW>());
     if (e != hipSuccess) return e;
     attr_set = true;
   }
   prof::Scope ps(prof::GEMM_MFMA_TILE, 2.0 * w.M * w.N * w.K + 2.0 * d.M * d.N * d.K, 0, s);
   const bool w_first = w.stages_per_split >= d.stages_per_split;
-  hipLaunchKernelGGL((gemm_tile_pair_k<BM, BN, R, KW>), dim3(blocks_of(w) + blocks_of(d)), dim3(threads_of(BM, BN, R, KW)), (smem_of<BM, BN, R, KW>()), s, w, d,
+  hipLaunchKernelGGL((gemm_tile_pair_k<BM, BN, R, KW, NW>), dim3(blocks_of(w) + blocks_of(d)), dim3(threads_of(KW, NW)), (smem_of<BM, BN, R, KW>()), s, w, d,
                      (int)(w_first ? blocks_of(w) : blocks_of(d)), w_first ? 1 : 0);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = launch_reduce(w, s);
@@ -1299,7 +1299,12 @@ hipError_t gemm_pair_bf16(const Gemm &w, const Gemm &d, const PairPlan *plan, hi
     case 0: return launch_pair<128, 128, 2, false>(pw, pd, s);
     case 1: return launch_pair<64, 128, 2, false>(pw, pd, s);
     case 2: return launch_pair<64, 64, 2, false>(pw, pd, s);
-    case 3: return launch_pair<64, 128, 3, false>(pw, pd, s);
+    case 3:
+      // Eight wavefronts on a tile are no help in the second round of two workgroups to a unit: from 960 workgroups on four took 0.98 of their time
+      // on average over 57 linears (512 x 2880 -> 2880 35.8 -> 32.0 us, 512 x 2752 -> 2752 33.4 -> 31.2); below 896, 124 linears, eight are the better
+      // by 2 % on average.
+      if (blocks_of(pw) + blocks_of(pd) >= 960) return launch_pair<64, 128, 3, false, 4>(pw, pd, s);
+      return launch_pair<64, 128, 3, false>(pw, pd, s);
     case 4: return launch_pair<64, 64, 3, false>(pw, pd, s);
     case 7: return launch_pair<32, 64, 3, true>(pw, pd, s);
     case 8: return launch_pair<32, 32, 4, true>(pw, pd, s);

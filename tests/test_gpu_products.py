@@ -58,3 +58,27 @@ def test_loads_and_reads_dealt_out(tile, M, N, K, dealt):
     torch.cuda.synchronize()
     assert torch.equal(*out)
     close(out[0], a, b)
+
+
+@pytest.mark.parametrize("rows,width,out,four", [(512, 2880, 2880, True), (440, 2696, 2696, True), (384, 2520, 2520, False), (300, 1600, 1928, False)])
+def test_both_products_of_a_linears_backward(tile, rows, width, out, four):
+    """64 x 128 tiles in a ring of three, by four wavefronts from 960 workgroups on, by eight below; bias sums with the weight gradient."""
+    up = lambda n, by: -(-n // by)
+    assert four == (up(width, 64) * up(out, 128) + up(rows, 64) * up(width, 128) >= 960)
+    torch.manual_seed(rows)
+    x, w, dy, res = rnd(rows, width), rnd(width, out), rnd(rows, out), []
+    f = sb.lib()._ZN4ssdt1k14gemm_pair_bf16ERKNS0_4GemmES3_PKNS0_8PairPlanEP12ihipStream_t
+    f.argtypes, f.restype = [ctypes.POINTER(Gemm), ctypes.POINTER(Gemm), ctypes.c_void_p, ctypes.c_void_p], ctypes.c_int
+    for cfg in (3, 1):
+        tile(cfg)
+        dw, dx, db = (torch.full(s, float("nan"), device="cuda:0", dtype=torch.bfloat16) for s in ((width, out), (rows, width), (out,)))
+        gw = Gemm(M=width, N=out, K=rows, A=x.data_ptr(), lda=width, transA=True, B=dy.data_ptr(), ldb=out, C=dw.data_ptr(), ldc=out,
+                  dtype=sb.BF16, colsum=db.data_ptr())
+        gd = Gemm(M=rows, N=width, K=out, A=dy.data_ptr(), lda=out, B=w.data_ptr(), ldb=out, transB=True, C=dx.data_ptr(), ldc=width, dtype=sb.BF16)
+        assert f(ctypes.byref(gw), ctypes.byref(gd), None, torch.cuda.current_stream().cuda_stream) == 0
+        res.append((dw, dx, db))
+    torch.cuda.synchronize()
+    assert all(torch.equal(*p) for p in zip(*res))
+    close(res[0][0], x.t().contiguous(), dy)
+    close(res[0][1], dy, w.t().contiguous())
+    close(res[0][2], torch.ones(1, rows, device="cuda:0"), dy)
