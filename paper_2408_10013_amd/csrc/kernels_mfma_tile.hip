@@ -874,10 +874,10 @@ static constexpr size_t smem_of() {
   return stg > stages ? stg : stages;
 }
 // Whether four wavefronts on 128 x 128 deal out their reads and loads between the matrix instructions (see tile_body): where the last
-// round of workgroups has two to a unit.  Time in the compiler's order against it, 633 forward products: 1.01 to 1.04 there, up to 1.15; 0.96 to 1.0
-// where the last round has one to a unit, 0.98 with up to eight stages.  Backward products, alone or both in one launch: 0.96 to 1.0, 0.994 on average
-// over 300 pairs; they keep the compiler's order.
-static bool deal_of(const TileP &p) { return p.K > 512 && (blocks_of(p) - 1) % 512 >= 256; }
+// round of workgroups has two to a unit, or there are so many rounds that the last one does not matter.  Time in the compiler's order against it,
+// 633 forward products: 1.01 to 1.04 with two to a unit in the last round, up to 1.15; 0.96 to 1.0 with one, and from 2305 workgroups on 1.00 to 1.04; 0.98
+// with up to eight stages.  Backward products, alone or both in one launch: 0.96 to 1.0, 0.994 on average over 300 pairs; they keep the compiler's order.
+static bool deal_of(const TileP &p) { return p.K > 512 && (blocks_of(p) > 2304 || (blocks_of(p) - 1) % 512 >= 256); }
 
 template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG = false, bool DEAL = false>
 static hipError_t launch_tile(const TileP &p, hipStream_t s) {
