@@ -965,19 +965,23 @@ bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
 
 // DISPATCH.  Predicted time of a problem in microseconds, fitted to what the products of 525 layers took inside the layer: three layers
 // in turn, with and without the last-level cache emptied between two passes (MI355X; 32 to 16000 tokens, widths 128 to 4200; 3900 products
-// by themselves, 2000 linears' backwards, every tile and split).  The choice costs 1.5 % more than the best tile on average, a
-// linear's backward 1.7 %; on layers that were not fitted 1.6 and 2.1 %.  (Fitted to products by themselves, operands in the caches and
-// widths to 2048, it cost 4.8 and 5.1 %: 944 x 9984 x 3328 took 64 x 128 tiles, 147 us, for 128 x 128, 102; the layer of 4 x 236
-// tokens, H 3328 1217 us against 1125 before those tiles came.)
+// by themselves, 2000 linears' backwards, every tile and split).  A linear's backward took 1.7 % longer than by the best choice, 2.1 on layers that were
+// not fitted.  (Fitted to products by themselves, operands in the caches and widths to 2048, it took 5.1 % longer.)
+// The two tiles of eight wavefronts, rings of 3 and 4, were fitted anew, to 9700 forward products each among its layer's others (2450 layers, norms in
+// between, the weights of 3 to 16 layers in turn).  There the choice costs 1.2 % more than the best tile on average, 7.9 % at the 95th percentile; with
+// the entries of the four-wavefront kernels 1.8 and 11.1 %, with those entries' launch cost lowered 1.7 and 10.8 % (384 x 3392 x 13568 took 128 x 128, 121
+// us, for 64 x 128, 99).  (Products by themselves say otherwise here too: 768 x 5376 x 1792, 25 us by either, makes its layer 9 us longer by 128 x 128 in
+// the ring of 4.)  The other entries and kPairCost are from the 525 layers; 128 x 128 with its loads dealt out (deal_of) and pairs of 64 x 128 in a
+// ring of 3 are up to 4 % faster than they say.
 // A launch takes z us and e for each tile of a compute unit.  Whole rounds of as many workgroups as fit take c for each of a unit's
 // and stage of 64 k; in the last one a stage takes a + b n when n workgroups share a unit, and never less than c for each of
 // them, averaged over the machine.  f: us for each megabyte that a stage's panels bring from memory to the XCDs (panels()): small tiles
 // read an operand more often than the L2s catch.
 //   128 x 128, ring of 2: 0.76 us alone, 0.56 each together (1.0 PFLOP/s on 4096 x 2048 x 8192, 512 tiles);
-//              ring of 4, eight wavefronts: 0.44, and alone on its unit always: for one round of tiles and long K (152 tiles of 2331 x 1024
-//              x 4096: 31 us against 38 by 64 x 128); 0.6 in whole rounds, where 128 x 128 with two buffers is the better one;
+//              ring of 4, eight wavefronts: 0.47, and alone on its unit always: for one round of tiles and long K (152 tiles of 2331 x 1024
+//              x 4096: 31 us against 38 by 64 x 128); 0.60 in whole rounds, where 128 x 128 with two buffers is the better one;
 //    64 x 128, ring of 2: 0.33 each from three on: where three share a unit;
-//              ring of 3: 0.31 alone (2331 x 1024 x 4096, 296 tiles: 39 us against 52 and, 128 x 128, 44);
+//              ring of 3, eight wavefronts: 0.33 alone (384 x 3392 x 13568, 162 tiles: 99 us against 160 and, 128 x 128, 121);
 //    64 x 64,  ring of 2: 0.20 each, four to a unit (160 KiB of LDS would hold a fifth, but it waits: 1056 tiles of 33 stages 47 us,
 //              1014 of 52 50);
 //              ring of 3: 0.20 alone: for the smaller (512 x 2304 x 576: 9 us, by 64 x 128 13).
@@ -990,8 +994,8 @@ bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
 // Splitting the contraction costs a second launch and the partial products' way out and back, from the caches at about 12 TB/s.
 struct TileCost { double a, b, c, e, f, z; int fit; };  // fit: workgroups that share a compute unit at most
 static const TileCost kCost[kCfgs] = {{0.746, 0.01, 0.562, 2.776, 0, 7.409, 2},      {0.544, 0.078, 0.332, 0.536, 0.042, 5.313, 3},
-                                      {0.41, 0.041, 0.195, 0.568, 0.048, 4.39, 4},   {0.142, 0.17, 0.311, 1.1, 0.053, 5.658, 2},
-                                      {0.05, 0.153, 0.19, 0.412, 0.066, 4.996, 3},   {0.061, 0.379, 0.605, 5.625, 0, 6.424, 1},
+                                      {0.41, 0.041, 0.195, 0.568, 0.048, 4.39, 4},   {0.108, 0.221, 0.337, 1.31, 0.039, 5.121, 2},
+                                      {0.05, 0.153, 0.19, 0.412, 0.066, 4.996, 3},   {0.135, 0.336, 0.599, 4.448, 0.012, 5.435, 1},
                                       {0.134, 0.042, 0.182, 1.33, 0.054, 4.884, 1},  {0.052, 0.089, 0.177, 0.478, 0.045, 4.333, 2},
                                       {0.064, 0.073, 0.117, 0.418, 0.049, 3.756, 2}, {0.663, 0.026, 0.943, 9.984, 0, 6.252, 1}};
 constexpr int kMaxSplits = 8;

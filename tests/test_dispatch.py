@@ -1,4 +1,4 @@
-"""The choice of tile for bf16 forward products, against what the tiles were measured to take inside a layer, and of kernel for whole-tile
+"""The choice of tile for bf16 forward products, against what the tiles were measured to take, and of kernel for whole-tile
 attention (MI355X, us)."""
 import ctypes
 import time
@@ -9,23 +9,34 @@ from paper_2408_10013_amd import binding as sb
 from paper_2408_10013_amd import runner
 
 # M, N, K: 128 x 128, 64 x 128, 64 x 64, the last two in a ring of three, 128 x 128 in a ring of four, along k 64 x 64, 32 x 64 and
-# 32 x 32, 256 x 128
+# 32 x 32, 256 x 128; by themselves, weights from memory, activations as the product before leaves them
 MEASURED = {
-    (256, 1024, 256): [14.8, 9.8, 7.0, 9.6, 6.9, 15.6, 7.3, 5.5, 5.0, 19.3],
-    (333, 4320, 1728): [30.0, 24.8, 17.4, 21.0, 15.3, 27.1, 21.5, 29.5, 34.8, 31.4],
-    (512, 2304, 576): [16.8, 13.0, 9.5, 12.8, 9.1, 17.4, 14.4, 12.4, 14.1, 19.6],
-    (588, 16128, 4032): [143.4, 190.2, 159.2, 183.5, 152.8, 140.4, 202.7, 343.0, 336.3, 131.9],
-    (640, 3328, 13312): [185.4, 161.1, 146.7, 137.4, 142.2, 123.5, 160.5, 165.4, 261.1, 165.4],
-    (777, 11328, 3776): [129.7, 160.8, 174.0, 161.0, 166.4, 126.7, 188.5, 288.1, 331.1, 107.6],
-    (900, 1344, 448): [14.2, 10.0, 7.5, 10.7, 7.2, 14.7, 11.9, 10.7, 11.6, 17.6],
-    (944, 9984, 3328): [102.3, 147.3, 161.5, 156.3, 170.9, 104.9, 190.7, 162.8, 271.6, 91.5],
-    (944, 3328, 13312): [170.1, 162.5, 167.8, 215.2, 258.6, 120.6, 266.5, 235.6, 379.0, 162.5],
-    (1024, 2048, 2048): [27.0, 21.7, 19.1, 16.6, 16.5, 25.6, 20.5, 23.8, 32.8, 31.4],
-    (1308, 2816, 11264): [155.0, 140.4, 166.5, 178.4, 222.9, 109.4, 216.2, 369.9, 338.2, 144.6],
-    (1408, 2816, 704): [20.5, 14.8, 14.8, 15.3, 17.0, 21.3, 28.1, 24.1, 36.4, 23.3],
-    (2331, 1024, 4096): [58.6, 51.9, 48.3, 39.6, 49.8, 42.3, 51.9, 54.1, 76.1, 56.5],
-    (3000, 8192, 2048): [131.4, 133.8, 153.8, 137.4, 155.4, 164.2, 250.7, 226.3, 361.9, 119.0],
-    (8192, 1024, 4096): [76.8, 114.4, 118.4, 96.9, 119.9, 88.2, 150.7, 166.6, 251.0, 62.4],
+    (256, 1024, 256): [13.2, 8.5, 6.0, 6.9, 6.1, 9.5, 6.4, 5.2, 4.7, 16.3],
+    (333, 4320, 1728): [28.0, 25.0, 22.1, 17.8, 18.7, 20.4, 21.9, 29.4, 36.7, 26.4],
+    (512, 2304, 576): [11.2, 8.7, 7.8, 7.4, 7.3, 9.4, 11.2, 9.0, 11.4, 15.2],
+    (588, 16128, 4032): [141.2, 193.2, 156.6, 183.1, 151.3, 130.3, 199.1, 343.0, 329.8, 110.5],
+    (640, 3328, 13312): [170.8, 155.1, 143.5, 138.4, 140.6, 117.7, 154.4, 164.7, 256.4, 135.6],
+    (777, 11328, 3776): [127.2, 160.1, 173.2, 160.0, 165.7, 119.7, 185.2, 286.5, 330.2, 97.9],
+    (900, 1344, 448): [10.2, 7.9, 7.0, 6.7, 6.6, 9.0, 10.5, 8.6, 10.4, 14.1],
+    (944, 9984, 3328): [97.3, 145.3, 161.2, 156.2, 171.0, 85.7, 189.1, 162.2, 268.0, 89.3],
+    (944, 3328, 13312): [168.3, 157.4, 165.9, 217.1, 259.7, 99.4, 270.7, 232.1, 377.9, 142.1],
+    (1024, 2048, 2048): [31.9, 27.3, 24.8, 18.4, 20.8, 22.5, 24.6, 30.2, 42.9, 31.0],
+    (1308, 2816, 11264): [144.1, 134.7, 167.3, 181.4, 224.9, 89.0, 218.6, 371.0, 336.8, 117.8],
+    (1408, 2816, 704): [18.7, 13.7, 13.2, 12.5, 15.6, 14.1, 27.0, 23.3, 36.5, 21.3],
+    (2331, 1024, 4096): [54.5, 49.7, 45.8, 41.4, 48.8, 33.2, 50.5, 49.2, 73.0, 47.2],
+    (3000, 8192, 2048): [121.0, 130.5, 154.3, 138.0, 155.0, 135.5, 249.1, 227.7, 359.7, 111.4],
+    (8192, 1024, 4096): [62.6, 92.3, 103.7, 85.9, 108.3, 73.3, 132.4, 143.8, 228.1, 58.5],
+    (384, 3392, 13568): [176.3, 160.0, 145.3, 98.9, 119.6, 120.8, 128.7, 154.5, 168.2, 139.3],
+    (735, 2624, 10496): [134.8, 123.9, 112.9, 73.8, 85.3, 87.0, 97.3, 181.8, 248.5, 119.6],
+    (640, 3136, 12544): [163.1, 149.0, 135.2, 93.5, 108.2, 111.1, 119.2, 210.9, 223.6, 130.6],
+    (702, 2944, 11776): [148.4, 137.7, 127.0, 87.0, 105.1, 87.2, 119.2, 221.9, 217.9, 129.0],
+    (274, 6624, 2208): [34.7, 32.6, 28.4, 37.2, 29.1, 24.6, 31.8, 35.4, 56.1, 32.1],
+    (7345, 2592, 10368): [478.2, 902.9, 1190.9, 817.9, 1149.9, 554.0, 1310.4, 2389.1, 3379.3, 405.9],
+    (13824, 512, 512): [14.7, 17.0, 16.3, 17.2, 17.5, 18.6, 35.2, 30.0, 46.8, 15.3],
+    (1024, 2048, 5120): [70.6, 61.7, 56.8, 40.9, 46.5, 49.9, 51.5, 69.6, 99.2, 64.8],
+    (3000, 6144, 2048): [87.2, 94.0, 113.9, 96.8, 112.8, 95.8, 173.3, 169.9, 276.2, 91.8],
+    (2331, 4096, 1024): [42.8, 35.2, 40.3, 35.0, 38.6, 43.7, 75.3, 60.7, 93.6, 47.7],
+    (1024, 6144, 2048): [44.6, 41.5, 53.0, 43.5, 53.3, 44.0, 70.6, 77.4, 124.8, 31.4],
 }
 
 
@@ -37,8 +48,8 @@ def choice(shape, one_order):
 
 @pytest.mark.parametrize("shape", list(MEASURED))
 def test_the_chosen_tile_is_a_fast_one(shape):
-    """Within a tenth of the best: over 2276 such products the choice costs 1.4 % on average and 8.8 % at the 95th percentile.
-    Small and large widths, weights far beyond the caches among them."""
+    """Within a tenth of the best: over 9700 products, each in its layer, the choice costs 1.2 % on average and 7.9 % at the 95th
+    percentile.  Small and large widths, weights far beyond the caches among them."""
     t = MEASURED[shape]
     assert t[choice(shape, False)] <= 1.1 * min(t)
     one = choice(shape, True)     # layers with ReLU: among the tiles of one order
