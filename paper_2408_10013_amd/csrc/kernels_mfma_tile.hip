@@ -254,7 +254,7 @@ constexpr int threads_of(bool KW, int NW) { return KW ? 256 : 64 * NW; }
 
 // One tile: workgroup `bid` of the problem's tiles_m * tiles_n * splits (tiles of a split after each other).
 // R: stages in the ring.  These kernels differ in nothing but tile, ring and speed: every output is the same sum in the same order.
-template <int BM, int BN, int R, bool AKM, bool BKM, bool BIG = false, bool DEAL = false, int NW = waves_of(BM, BN, R)>
+template <int BM, int BN, int R, bool AKM, bool BKM, bool BIG = false, int NW = waves_of(BM, BN, R)>
 __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *smem) {
   constexpr int NT = 64 * NW, WGN = NW / 2, WTM = BM / 2, WTN = BN / WGN, TM = WTM / 16, TN = WTN / 16;
   typedef Side<BM, AKM, NT, kSK, BIG> SA;
@@ -291,11 +291,11 @@ __device__ __forceinline__ void tile_body(const TileP &p, int bid, uint16_t *sme
   // of a stage's second step are the last of that stage, so its one barrier sits between the two steps: behind it the
   // next stage is read and the stage R further on is loaded over this one.  (Both steps of the next stage read behind the
   // barrier, into a second set of registers: 10 % slower.)
-  // DEALT: reads and loads stand one by one between the matrix instructions; in front of them, as the compiler has it, they keep
-  // eight wavefronts on a tile waiting, and four where two workgroups share the unit (see deal_of; 1024 x 6144 x 2048 32.4 -> 29.6 us, 3000 x
-  // 2048 x 2048 33.6 -> 30.6).  With a ring of three or more the loads are spread over both steps; with two they have to land within the stage.
-  // Four wavefronts alone on a unit, or with less to do each, are 1 to 6 % faster in the compiler's order.
-  constexpr bool DEALT = NW == 8 || DEAL;
+  // DEALT: eight wavefronts' reads and loads stand one by one between the matrix instructions, the loads spread over both steps; in front of
+  // them, as the compiler has it, they keep the tile waiting.  Four wavefronts are better off in the compiler's order: 64-row tiles by 2 to
+  // 6 %, 128 x 128 in a ring of two by 1 to 2 % of its time among a layer's other products, 10 % and more with up to 24 stages (3500 products of 1170 layers; by
+  // themselves some are 10 % faster with everything dealt out, 1024 x 6144 x 2048 32.4 -> 29.6 us, and make their layer slower all the same).
+  constexpr bool DEALT = NW == 8;
   sa.start(p.A, p.lda, m0, p.M, s0 * kSK, p.K);
   sb.start(p.B, p.ldb, n0, p.N, s0 * kSK, p.K);
   bf16x8_t af[2][TM], bf[2][TN];
@@ -790,15 +790,15 @@ __global__ __launch_bounds__(512) void gemm_wide_pair_k(TileP w, TileP d, int fi
 }
 
 // KW: wavefronts along k
-template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG = false, bool DEAL = false, int NW = waves_of(BM, BN, R)>
+template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG = false, int NW = waves_of(BM, BN, R)>
 __device__ __forceinline__ void any_body(const TileP &p, int bid, uint16_t *smem) {
   if constexpr (KW) kwave_body<BM, BN, R, AKM, BKM>(p, bid, smem);
-  else tile_body<BM, BN, R, AKM, BKM, BIG, DEAL, NW>(p, bid, smem);
+  else tile_body<BM, BN, R, AKM, BKM, BIG, NW>(p, bid, smem);
 }
-template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG, bool DEAL>
+template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG>
 __global__ __launch_bounds__(threads_of(KW, waves_of(BM, BN, R)), 2) void gemm_tile_k(TileP p) {
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
-  any_body<BM, BN, R, KW, AKM, BKM, BIG, DEAL>(p, blockIdx.x, smem);
+  any_body<BM, BN, R, KW, AKM, BKM, BIG>(p, blockIdx.x, smem);
 }
 
 // The two products of a linear's backward in one launch: the weight gradient (both operands k-major) and the input
@@ -810,8 +810,8 @@ __global__ __launch_bounds__(threads_of(KW, NW), 2) void gemm_tile_pair_k(TileP 
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   const int bid = blockIdx.x;
   const bool head = bid < first;
-  if (head == (w_first != 0)) any_body<BM, BN, R, KW, true, true, false, false, NW>(w, head ? bid : bid - first, smem);
-  else any_body<BM, BN, R, KW, false, false, false, false, NW>(d, head ? bid : bid - first, smem);
+  if (head == (w_first != 0)) any_body<BM, BN, R, KW, true, true, false, NW>(w, head ? bid : bid - first, smem);
+  else any_body<BM, BN, R, KW, false, false, false, NW>(d, head ? bid : bid - first, smem);
 }
 
 // Second half of a split product: adds the partial products in the order of the splits and applies the epilogue;
@@ -873,22 +873,16 @@ static constexpr size_t smem_of() {
   constexpr size_t stages = (size_t)R * (BM + BN) * (KW ? 128 : kSK) * 2;
   return stg > stages ? stg : stages;
 }
-// Whether four wavefronts on 128 x 128 deal out their reads and loads between the matrix instructions (see tile_body): where the last
-// round of workgroups has two to a unit, or there are so many rounds that the last one does not matter.  Time in the compiler's order against it,
-// 633 forward products: 1.01 to 1.04 with two to a unit in the last round, up to 1.15; 0.96 to 1.0 with one, and from 2305 workgroups on 1.00 to 1.04; 0.98
-// with up to eight stages.  Backward products, alone or both in one launch: 0.96 to 1.0, 0.994 on average over 300 pairs; they keep the compiler's order.
-static bool deal_of(const TileP &p) { return p.K > 512 && (blocks_of(p) > 2304 || (blocks_of(p) - 1) % 512 >= 256); }
-
-template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG = false, bool DEAL = false>
+template <int BM, int BN, int R, bool KW, bool AKM, bool BKM, bool BIG = false>
 static hipError_t launch_tile(const TileP &p, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_k<BM, BN, R, KW, AKM, BKM, BIG, DEAL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN, R, KW>());
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_tile_k<BM, BN, R, KW, AKM, BKM, BIG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_of<BM, BN, R, KW>());
     if (e != hipSuccess) return e;
     attr_set = true;
   }
   prof::Scope ps(prof::GEMM_MFMA_TILE, 2.0 * p.M * p.N * p.K, 0, s);
-  hipLaunchKernelGGL((gemm_tile_k<BM, BN, R, KW, AKM, BKM, BIG, DEAL>), dim3(blocks_of(p)), dim3(threads_of(KW, waves_of(BM, BN, R))), (smem_of<BM, BN, R, KW>()), s, p);
+  hipLaunchKernelGGL((gemm_tile_k<BM, BN, R, KW, AKM, BKM, BIG>), dim3(blocks_of(p)), dim3(threads_of(KW, waves_of(BM, BN, R))), (smem_of<BM, BN, R, KW>()), s, p);
   hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : launch_reduce(p, s);
 }
@@ -923,11 +917,7 @@ template <bool AKM, bool BKM>
 static hipError_t launch_cfg(int cfg, const TileP &p, hipStream_t s) {
   switch (cfg) {
     case kBig: return launch_tile<128, 128, 2, false, AKM, BKM, true>(p, s);
-    case 0:
-      if constexpr (!AKM && BKM) {
-        if (deal_of(p)) return launch_tile<128, 128, 2, false, AKM, BKM, false, true>(p, s);
-      }
-      return launch_tile<128, 128, 2, false, AKM, BKM>(p, s);
+    case 0: return launch_tile<128, 128, 2, false, AKM, BKM>(p, s);
     case 1: return launch_tile<64, 128, 2, false, AKM, BKM>(p, s);
     case 2: return launch_tile<64, 64, 2, false, AKM, BKM>(p, s);
     case 3: return launch_tile<64, 128, 3, false, AKM, BKM>(p, s);
@@ -971,8 +961,7 @@ bool gemm_tile_fits(int M, int N, int K, bool transA, bool transB, int dtype) {
 // between, the weights of 3 to 16 layers in turn).  There the choice costs 1.2 % more than the best tile on average, 7.9 % at the 95th percentile; with
 // the entries of the four-wavefront kernels 1.8 and 11.1 %, with those entries' launch cost lowered 1.7 and 10.8 % (384 x 3392 x 13568 took 128 x 128, 121
 // us, for 64 x 128, 99).  (Products by themselves say otherwise here too: 768 x 5376 x 1792, 25 us by either, makes its layer 9 us longer by 128 x 128 in
-// the ring of 4.)  The other entries and kPairCost are from the 525 layers; 128 x 128 with its loads dealt out (deal_of) and pairs of 64 x 128 in a
-// ring of 3 are up to 4 % faster than they say.
+// the ring of 4.)  The other entries and kPairCost are from the 525 layers; pairs of 64 x 128 in a ring of 3 are up to 4 % faster than it says.
 // A launch takes z us and e for each tile of a compute unit.  Whole rounds of as many workgroups as fit take c for each of a unit's
 // and stage of 64 k; in the last one a stage takes a + b n when n workgroups share a unit, and never less than c for each of
 // them, averaged over the machine.  f: us for each megabyte that a stage's panels bring from memory to the XCDs (panels()): small tiles

@@ -38,20 +38,17 @@ def close(got, a, b):
     assert bool(((got.double() - want).abs() <= 2.0 ** -8 * want.abs() + a.shape[1] * 2.0 ** -24 * size).all())
 
 
-# 128 x 128 tiles; "dealt": the last round of 512 workgroups holds more than 256, or there are more than 2304, and more than eight stages of 64 k
-@pytest.mark.parametrize("M,N,K,dealt", [(2300, 1920, 584, True), (2176, 2048, 520, True), (2100, 1928, 1000, True), (5000, 2560, 528, True),
-                                         (4090, 2040, 640, True), (2300, 1920, 512, False), (2048, 2048, 576, False), (2400, 3440, 640, False),
-                                         (1660, 25144, 528, True), (1660, 12152, 528, False)])
-def test_loads_and_reads_dealt_out(tile, M, N, K, dealt):
-    """270, 272, 272, 800 and 512 tiles, 270 with too few stages, 256 and 513, 2561 and 1235; contractions with tails, of 9 stages and more."""
-    tiles = -(-M // 128) * -(-N // 128)
-    assert dealt == (K > 512 and (tiles > 2304 or (tiles - 1) % 512 >= 256))
+# 128 x 128 in a ring of two, 64 x 128 in one of three, 128 x 128 in one of four; contractions with tails, of 1 stage, 9, 10 and 16, and sizes that end inside a
+# tile, more tiles than run at a time
+@pytest.mark.parametrize("cfg", [0, 3, 5])
+@pytest.mark.parametrize("M,N,K", [(130, 136, 40), (2300, 1920, 584), (2100, 1928, 1000), (4090, 2040, 520), (1660, 25144, 528)])
+def test_every_order_of_loads_and_reads(tile, M, N, K, cfg):
     torch.manual_seed(M)
     a, b, out = rnd(M, K), rnd(K, N), []
     f = sb.lib()._ZN4ssdt1k4gemmERKNS0_4GemmEP12ihipStream_t
     f.argtypes, f.restype = [ctypes.POINTER(Gemm), ctypes.c_void_p], ctypes.c_int
-    for cfg in (0, 1):  # 1: 64 x 128, the compiler's order always
-        tile(cfg)
+    for which in (cfg, 1):  # 1: 64 x 128 in a ring of two
+        tile(which)
         c = torch.full((M, N), float("nan"), device="cuda:0", dtype=torch.bfloat16)
         g = Gemm(M=M, N=N, K=K, A=a.data_ptr(), lda=K, B=b.data_ptr(), ldb=N, C=c.data_ptr(), ldc=N, dtype=sb.BF16)
         assert f(ctypes.byref(g), torch.cuda.current_stream().cuda_stream) == 0
