@@ -247,8 +247,9 @@ __device__ __forceinline__ void store_colsum(const TileP &p, int n, int split, f
 
 // Wavefronts that share a tile, in two rows.  A ring of three or more has one or two workgroups on a compute unit: four wavefronts, one to
 // a SIMD, leave nothing to cover their waits for fragments and barriers, and the epilogue is theirs alone.  Eight: 128 x 128, ring of 4, 2331 x
-// 1024 x 4096 37.7 -> 31.1 us, 1024 x 2048 x 5120 45 -> 37, with GELU 2331 x 4096 x 1024 56 -> 44; 64 x 128, ring of 3, 1024 x 5120 x 2048 with GELU
-// 37.6 -> 34.5, 1024 x 2048 x 2048 15.0 -> 14.4.  (Wavefronts that do nothing but load, one, two or four of them: no faster.)
+// 1024 x 4096 37.7 -> 31.1 us; 64 x 128, ring of 3, 1024 x 2048 x 5120 30.3 -> 29.3, 1024 x 5120 x 2048 with GELU 37.6 -> 34.5, 1024 x 2048 x 2048
+// 15.0 -> 14.4.  Among a layer's other products it saves 20 % of a product's time at 0.6 PFLOP/s by 128 x 128 (1330 of them), 9 % by 64 x 128 (2700).
+// (Wavefronts that do nothing but load, one, two or four of them: no faster.)
 constexpr int waves_of(int BM, int BN, int R) { return R >= 3 && BN == 128 ? 8 : 4; }
 constexpr int threads_of(bool KW, int NW) { return KW ? 256 : 64 * NW; }
 
